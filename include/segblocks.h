@@ -440,6 +440,36 @@ int segblocks_conv2d(const void* x, int dtype, int layout, int N, int C_in, int 
 int segblocks_maxpool(const void* x, int dtype, int layout, int N, int C, int H, int W,
                       int ksize, int stride, int pad, void* y, hipStream_t stream);
 
+/* The stem of a ResNet fused with the max-pool after it:
+ *   y = maxpool 3x3/2 pad 1 (max(0, bias + conv 7x7/2 pad 3 (x)))
+ * x [N,C_in,H,W] -> y [N,C_out,Hp,Wp], Ho = (H - 1) / 2 + 1,
+ * Hp = (Ho - 1) / 2 + 1 (W alike): segblocks_conv2d with SB_FLAG_RELU, then
+ * segblocks_maxpool, without the map between them in memory; the same values.
+ * Channels-last fp16 / bf16, C_in <= 4, C_out % 8 == 0, W even, x 4-byte and y
+ * 16-byte aligned (else SB_EINVAL).  weight OHWI [C_out][7][7][C_in], bias
+ * [C_out] or NULL. */
+int segblocks_stem_pool(const void* x, int dtype, int layout, int N, int C_in, int H, int W,
+                        const void* weight, const void* bias, int C_out, void* y, hipStream_t stream);
+
+/* The 7x7/2 stem on image blocks, straight from the image: segblocks_split,
+ * segblocks_pad_halo with 3 pixels (average sampling) and segblocks_conv_halo
+ * in one kernel, without the stacks between them in memory.
+ * x [N,C_in,H,W] -> hi_out [nh,C_out,bs/2,bs/2], lo_out [nl,C_out,bs/4,bs/4].
+ * flags: SB_FLAG_RELU.  Types, sizes and alignment as segblocks_stem_pool
+ * (outputs 16-byte aligned); bs a multiple of 4, 8 <= bs <= 256. */
+int segblocks_stem_blocks(const void* x, int dtype, int layout, int N, int C_in, int H, int W,
+                          const uint8_t* mask, int bs, const void* weight, const void* bias, int C_out,
+                          int flags, void* hi_out, int hi_cap, void* lo_out, int lo_cap, hipStream_t stream);
+
+/* 3x3/2 max-pooling of packed stacks with BlockPad (average sampling) fused:
+ * segblocks_pad_halo with 1 pixel and segblocks_maxpool_halo in one kernel.
+ * hi [nh,C,bs,bs], lo -> hi_out [nh,C,bs/2,bs/2], lo_out [nl,C,bs/4,bs/4].
+ * Channels-last fp16 / bf16, C % 8 == 0, bs a multiple of 4, 16-byte aligned
+ * (else SB_EINVAL). */
+int segblocks_maxpool_blocks(const void* hi, const void* lo, int dtype, int layout, int N, int C, int H,
+                             int W, const uint8_t* mask, int bs, void* hi_out, void* lo_out, int hi_cap,
+                             int lo_cap, hipStream_t stream);
+
 /* Description of the last failure on the calling thread ("" if none).  The
  * string stays valid until the next call on the same thread. */
 const char* segblocks_last_error(void);

@@ -22,7 +22,8 @@ __all__ = ["count", "split", "pad", "conv3x3", "combine", "block_conv3x3", "bloc
            "maxpool", "layout_of", "block_conv3x3_workspace_size", "block_conv_ex_workspace_size",
            "layer_workspace_size", "policy_heuristic", "combine_backward", "split_backward", "pad_backward",
            "conv3x3_backward_data", "conv3x3_backward_weight", "layer_backward", "pad_halo", "conv_halo",
-           "maxpool_halo", "block_conv_chain", "block_conv_chain_workspace_size", "block_conv_chain_reads_half"]
+           "maxpool_halo", "block_conv_chain", "block_conv_chain_workspace_size", "block_conv_chain_reads_half",
+           "stem_pool", "stem_blocks", "maxpool_blocks", "stem_fits"]
 
 _DT = {torch.float32: _b.SB_F32, torch.float16: _b.SB_F16, torch.bfloat16: _b.SB_BF16}
 
@@ -377,6 +378,63 @@ def maxpool(x: torch.Tensor, k: int = 3, stride: int = 2, padding: int = 1, out=
     y = _empty((N, C, Ho, Wo), x, layout) if out is None else out
     _b.call("segblocks_maxpool", _ptr(x), _dt(x), layout, N, C, H, W, k, stride, padding, _ptr(y), _stream(x))
     return y
+
+
+def stem_fits(x: torch.Tensor, weight: torch.Tensor) -> bool:
+    """Whether the fused stems (stem_pool, stem_blocks) take this image and
+    these filters: 7x7, channels-last fp16 / bf16, at most 4 input channels,
+    an even width and C_out % 8 == 0."""
+    return (x.dim() == 4 and x.dtype in (torch.float16, torch.bfloat16) and x.shape[1] <= 4 and x.shape[3] % 2 == 0
+            and tuple(weight.shape[1:]) == (x.shape[1], 7, 7) and weight.shape[0] % 8 == 0 and weight.dtype == x.dtype
+            and layout_of(x) == _b.SB_NHWC and x.data_ptr() % 4 == 0)
+
+
+def stem_pool(x: torch.Tensor, weight: torch.Tensor, bias=None):
+    """maxpool(conv2d(x, weight, bias, 2, 3, relu=True), 3, 2, 1) in one kernel
+    (the same values), for what stem_fits takes."""
+    layout = _b.SB_NHWC
+    _check_layout(layout, x)
+    N, C_in, H, W = x.shape
+    weight = _weight(weight, layout, 7)
+    bias = None if bias is None else bias.contiguous()
+    y = _empty((N, weight.shape[0], (H - 1) // 2 // 2 + 1, (W - 1) // 2 // 2 + 1), x, layout)
+    _b.call("segblocks_stem_pool", _ptr(x), _dt(x), layout, N, C_in, H, W, _ptr(weight), _ptr(bias), weight.shape[0],
+            _ptr(y), _stream(x))
+    return y
+
+
+def stem_blocks(x: torch.Tensor, mask: torch.Tensor, bs: int, weight: torch.Tensor, bias=None, counts=None,
+                relu: bool = False):
+    """split, pad_halo(3) and conv_halo(7x7, stride 2) of an image in one
+    kernel: (hi [nh,C_out,bs/2,bs/2], lo [nl,C_out,bs/4,bs/4]), for what
+    stem_fits takes."""
+    mask = _mask(mask)
+    layout = _b.SB_NHWC
+    _check_layout(layout, x)
+    N, C_in, H, W = x.shape
+    weight = _weight(weight, layout, 7)
+    bias = None if bias is None else bias.contiguous()
+    nh, nl = counts if counts is not None else count(mask)
+    hi = _empty((nh, weight.shape[0], bs // 2, bs // 2), x, layout)
+    lo = _empty((nl, weight.shape[0], bs // 4, bs // 4), x, layout)
+    _b.call("segblocks_stem_blocks", _ptr(x), _dt(x), layout, N, C_in, H, W, _ptr(mask), bs, _ptr(weight), _ptr(bias),
+            weight.shape[0], _b.SB_FLAG_RELU if relu else 0, _ptr(hi), nh, _ptr(lo), nl, _stream(x))
+    return hi, lo
+
+
+def maxpool_blocks(hi: torch.Tensor, lo: torch.Tensor, mask: torch.Tensor, bs: int, H: int, W: int):
+    """pad_halo(1) and maxpool_halo(3, 2) of channels-last fp16 / bf16 stacks
+    (C % 8 == 0, bs a multiple of 4) in one kernel: (hi_out, lo_out)."""
+    mask = _mask(mask)
+    ref = hi if hi.shape[0] else lo
+    layout = _b.SB_NHWC
+    _check_layout(layout, hi, lo)
+    C, N = ref.shape[1], mask.shape[0]
+    ho = _empty((hi.shape[0], C, bs // 2, bs // 2), ref, layout)
+    lo_o = _empty((lo.shape[0], C, bs // 4, bs // 4), ref, layout)
+    _b.call("segblocks_maxpool_blocks", _ptr(hi), _ptr(lo), _dt(ref), layout, N, C, H, W, _ptr(mask), bs, _ptr(ho),
+            _ptr(lo_o), hi.shape[0], lo.shape[0], _stream(ref))
+    return ho, lo_o
 
 
 def policy_heuristic(x: torch.Tensor, bs: int, tau_high: float, layout=None, out=None):

@@ -877,4 +877,76 @@ int segblocks_maxpool(const void* x, int dtype, int layout, int N, int C, int H,
     return hip_status(fn, sb::launch_maxpool(dtype, x, N, C, H, W, ksize, stride, pad, y, stream));
 }
 
+int segblocks_stem_pool(const void* x, int dtype, int layout, int N, int C_in, int H, int W, const void* weight,
+                        const void* bias, int C_out, void* y, hipStream_t stream) {
+    const char* fn = "segblocks_stem_pool";
+    if (N <= 0 || C_in <= 0 || H <= 0 || W <= 0 || C_out <= 0)
+        return fail(SB_EINVAL, fn, "N, C_in, H, W, C_out must be positive");
+    if (!x || !weight || !y) return fail(SB_EINVAL, fn, "x, weight or y is NULL");
+    if (!sb::stem_fits(dtype, layout, C_in, W, C_out, x, y))
+        return fail(SB_EINVAL, fn, "supported: channels-last fp16 / bf16, C_in <= 4, C_out %% 8 == 0, even W, aligned");
+    const long long Hp = ((H - 1) / 2) / 2 + 1, Wp = ((W - 1) / 2) / 2 + 1, es = 2;
+    if ((long long)N * H * W * C_in > (1LL << 40) || (long long)N * Hp * Wp * C_out > (1LL << 38) ||
+        N * ((Hp + 15) / 16) * ((Wp + 31) / 32) >= (1LL << 31))
+        return fail(SB_ESHAPE, fn, "problem too large");
+    const Range rx{x, (long long)N * C_in * H * W * es}, ry{y, (long long)N * C_out * Hp * Wp * es};
+    const Range rw{weight, (long long)C_out * C_in * 49 * es}, rb{bias, bias ? C_out * es : 0};
+    if (any_overlap({ry}, {rx, rw, rb})) return fail(SB_EINVAL, fn, "y overlaps an input");
+    return hip_status(fn, sb::launch_stem_pool(dtype, x, N, C_in, H, W, weight, bias, C_out, y, stream));
+}
+
+int segblocks_stem_blocks(const void* x, int dtype, int layout, int N, int C_in, int H, int W, const uint8_t* mask,
+                          int bs, const void* weight, const void* bias, int C_out, int flags, void* hi_out, int hi_cap,
+                          void* lo_out, int lo_cap, hipStream_t stream) {
+    const char* fn = "segblocks_stem_blocks";
+    sb::Geo g;
+    int s;
+    if ((s = check_geo(fn, dtype, layout, N, C_in, H, W, mask, bs, g))) return s;
+    if (!x) return fail(SB_EINVAL, fn, "x is NULL");
+    if ((s = check_conv_shape(fn, C_in, C_out, bs, weight))) return s;
+    if (bs % 4 || bs < 8) return fail(SB_ESHAPE, fn, "block size must be a multiple of 4, at least 8 (got %d)", bs);
+    if (flags & ~SB_FLAG_RELU) return fail(SB_EINVAL, fn, "unknown flags 0x%x", flags);
+    if ((s = check_caps(fn, hi_cap, lo_cap)) || (s = check_stack(fn, "hi_out", hi_out, hi_cap)) ||
+        (s = check_stack(fn, "lo_out", lo_out, lo_cap)))
+        return s;
+    if (!sb::stem_fits(dtype, layout, C_in, W, C_out, x, hi_out) || reinterpret_cast<uintptr_t>(lo_out) % 16)
+        return fail(SB_EINVAL, fn, "supported: channels-last fp16 / bf16, C_in <= 4, C_out %% 8 == 0, even W, aligned");
+    const long long es = 2, eo = bs / 2, el = bs / 4;
+    if (((long long)hi_cap + lo_cap) * ((eo + 15) / 16) * ((eo + 31) / 32) >= (1LL << 31))
+        return fail(SB_ESHAPE, fn, "problem too large");
+    const Range rx{x, (long long)N * C_in * H * W * es}, rw{weight, (long long)C_out * C_in * 49 * es};
+    const Range rb{bias, bias ? C_out * es : 0};
+    const Range rho{hi_out, hi_cap * (long long)C_out * eo * eo * es}, rlo{lo_out, lo_cap * (long long)C_out * el * el * es};
+    if (any_overlap({rho, rlo}, {rx, rw, rb, Range{mask, g.B}}))
+        return fail(SB_EINVAL, fn, "output buffers overlap inputs or each other");
+    return hip_status(fn, sb::launch_stem_blocks(dtype, g, mask, x, weight, bias, C_out, flags & SB_FLAG_RELU, hi_out,
+                                                 hi_cap, lo_out, lo_cap, stream));
+}
+
+int segblocks_maxpool_blocks(const void* hi, const void* lo, int dtype, int layout, int N, int C, int H, int W,
+                             const uint8_t* mask, int bs, void* hi_out, void* lo_out, int hi_cap, int lo_cap,
+                             hipStream_t stream) {
+    const char* fn = "segblocks_maxpool_blocks";
+    sb::Geo g;
+    int s;
+    if ((s = check_geo(fn, dtype, layout, N, C, H, W, mask, bs, g))) return s;
+    if ((s = check_caps(fn, hi_cap, lo_cap)) || (s = check_stack(fn, "hi", hi, hi_cap)) ||
+        (s = check_stack(fn, "lo", lo, lo_cap)) || (s = check_stack(fn, "hi_out", hi_out, hi_cap)) ||
+        (s = check_stack(fn, "lo_out", lo_out, lo_cap)))
+        return s;
+    if (bs % 4) return fail(SB_ESHAPE, fn, "block size must be a multiple of 4 (got %d)", bs);
+    const uintptr_t any = reinterpret_cast<uintptr_t>(hi) | reinterpret_cast<uintptr_t>(lo) |
+                          reinterpret_cast<uintptr_t>(hi_out) | reinterpret_cast<uintptr_t>(lo_out);
+    if (layout != SB_NHWC || dtype == SB_F32 || C % 8 || any % 16)
+        return fail(SB_EINVAL, fn, "supported: channels-last fp16 / bf16, C %% 8 == 0, 16-byte aligned");
+    const long long es = 2, lb = bs / 2, eo = bs / 2, el = bs / 4;
+    if (eo * eo * (C / 8) >= (1LL << 31) || ((long long)hi_cap + lo_cap) * ((eo * eo * (C / 8) + 255) / 256) >= (1LL << 31))
+        return fail(SB_ESHAPE, fn, "problem too large");
+    const Range rh{hi, hi_cap * (long long)C * bs * bs * es}, rl{lo, lo_cap * (long long)C * lb * lb * es};
+    const Range rho{hi_out, hi_cap * (long long)C * eo * eo * es}, rlo{lo_out, lo_cap * (long long)C * el * el * es};
+    if (any_overlap({rho, rlo}, {rh, rl, Range{mask, g.B}}))
+        return fail(SB_EINVAL, fn, "output buffers overlap inputs or each other");
+    return hip_status(fn, sb::launch_pool_blocks(dtype, g, mask, hi, lo, hi_out, lo_out, hi_cap, lo_cap, stream));
+}
+
 }  // extern "C"

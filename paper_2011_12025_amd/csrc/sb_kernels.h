@@ -143,6 +143,21 @@ hipError_t launch_maxpool_halo(int dtype, int layout, const Geo& g, const void* 
                                const uint8_t* mask, int halo, int K, int st, void* ho, void* lo, int hi_cap,
                                int lo_cap, hipStream_t s);
 
+// The 7x7/2 stem of an image (sb_stem.hip, channels-last fp16 / bf16, at most
+// four channels, an even width, C_out % 8 == 0: stem_fits): with ReLU and the
+// 3x3/2 max-pool (launch_stem_pool, dense), or on image blocks straight from
+// the image (launch_stem_blocks; g.C input channels, g.bs a multiple of 4 and
+// at least 8), whose 3x3/2 max-pool on packed stacks, BlockPad fused, is
+// launch_pool_blocks (g.C % 8 == 0, g.bs a multiple of 4, 16-byte aligned).
+bool stem_fits(int dtype, int layout, int C_in, int W, int C_out, const void* x, const void* y);
+hipError_t launch_stem_pool(int dtype, const void* x, int N, int C_in, int H, int W, const void* w, const void* bias,
+                            int C_out, void* y, hipStream_t st);
+hipError_t launch_stem_blocks(int dtype, const Geo& g, const uint8_t* mask, const void* x, const void* w,
+                              const void* bias, int C_out, int relu, void* ho, int hi_cap, void* lo, int lo_cap,
+                              hipStream_t st);
+hipError_t launch_pool_blocks(int dtype, const Geo& g, const uint8_t* mask, const void* hi, const void* lo, void* ho,
+                              void* lo_o, int hi_cap, int lo_cap, hipStream_t st);
+
 // Heuristic downsampling policy: per-block scores [N*GH*GW] (fp32), then the
 // mask with khigh high blocks per image (at most policy_max_blocks() per image).
 int policy_max_blocks();

@@ -19,8 +19,8 @@ from __future__ import annotations
 import torch
 
 from . import (block_conv3x3, block_conv3x3_workspace_size, block_conv_chain, block_conv_chain_reads_half,
-               block_conv_ex, block_conv_ex_workspace_size, combine, conv2d, conv_halo, count, maxpool, maxpool_halo,
-               pad_halo, split)
+               block_conv_ex, block_conv_ex_workspace_size, combine, conv2d, conv_halo, count, maxpool, maxpool_blocks,
+               maxpool_halo, pad_halo, split, stem_blocks, stem_fits, stem_pool)
 from ._binding import SB_NHWC
 
 WIDTHS = (64, 128, 256, 512)
@@ -46,6 +46,8 @@ class BlockEncoder:
                   for k, v in weights.items()}
 
     def stem(self, x: torch.Tensor) -> torch.Tensor:
+        if stem_fits(x, self.w["stem.w"]):
+            return stem_pool(x, self.w["stem.w"], self.w["stem.b"])
         h = conv2d(x, self.w["stem.w"], self.w["stem.b"], stride=2, padding=3, relu=True)
         return maxpool(h, 3, 2, 1)
 
@@ -74,6 +76,9 @@ class BlockEncoder:
         """The blockwise stem: image blocks -> stacks at stride 4."""
         N, C, H, W = x.shape
         blk = self.image_block
+        if stem_fits(x, self.w["stem.w"]):
+            sh, sl = stem_blocks(x, mask, blk, self.w["stem.w"], self.w["stem.b"], counts=counts, relu=True)
+            return maxpool_blocks(sh, sl, mask, blk // 2, H // 2, W // 2)
         hi, lo = split(x, mask, blk, counts=counts)
         hp, lp = pad_halo(hi, lo, mask, blk, H, W, 3)
         sh, sl = conv_halo(hp, lp, mask, blk, H, W, 3, self.w["stem.w"], self.w["stem.b"], stride=2, relu=True)
