@@ -14,8 +14,8 @@
 //
 // Selection: per image, the k = round(tau * GH * GW) blocks with the highest
 // scores are high resolution; equal scores are ranked by block id (lower
-// first).  One workgroup per image ranks every block against all others in
-// LDS: exact and independent of timing.
+// first).  Every block is ranked against all others of its image in LDS: exact
+// and independent of timing.
 #include "sb_common.h"
 #include "sb_kernels.h"
 
@@ -30,80 +30,157 @@ __device__ __forceinline__ T px(const T* __restrict__ x, int n, int C, int H, in
     else                     return x[(((size_t)n * C + c) * H + Y) * W + X];
 }
 
-template <typename T, int L>
-__global__ __launch_bounds__(WG) void k_policy_score(const T* __restrict__ x, int C, int H, int W, int bs, int GH,
+// Squared distances of the four pixels a, b, cc, d of a cell to its average, one channel.
+template <typename T>
+__device__ __forceinline__ void cell_channel(T a, T b, T cc, T d, float (&d2)[4]) {
+    const float m = to_f32(avg4(a, b, cc, d));
+    const float e0 = to_f32(a) - m, e1 = to_f32(b) - m, e2 = to_f32(cc) - m, e3 = to_f32(d) - m;
+    d2[0] += e0 * e0;
+    d2[1] += e1 * e1;
+    d2[2] += e2 * e2;
+    d2[3] += e3 * e3;
+}
+__device__ __forceinline__ float cell_norms(const float (&d2)[4]) {
+    return (__builtin_sqrtf(d2[0]) + __builtin_sqrtf(d2[1])) + (__builtin_sqrtf(d2[2]) + __builtin_sqrtf(d2[3]));
+}
+
+// Two horizontally adjacent pixels of an image of C <= 4 channels, from an
+// even column: 2 C elements, loaded together (aligned to two elements).
+// Channels-last: they are contiguous; NCHW: two elements of every plane.
+template <typename T, int L, int C>
+struct PixPair {
+    T e[2 * C];  // [channel][pixel] for NCHW, [pixel][channel] for NHWC
+    __device__ __forceinline__ void load(const T* __restrict__ x, int n, int H, int W, int Y, int X) {
+        if constexpr (L == NHWC) {
+            __builtin_memcpy(e, __builtin_assume_aligned(x + (((size_t)n * H + Y) * W + X) * C, 2 * sizeof(T)),
+                             sizeof(e));
+        } else {
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+                __builtin_memcpy(e + 2 * c,
+                                 __builtin_assume_aligned(x + (((size_t)n * C + c) * H + Y) * W + X, 2 * sizeof(T)),
+                                 2 * sizeof(T));
+        }
+    }
+    __device__ __forceinline__ T at(int k, int c) const { return L == NHWC ? e[k * C + c] : e[2 * c + k]; }
+};
+
+// C = 0: any channel count, element by element.  C = 1..4 (the images the
+// policy runs on; W is even and x aligned to two elements): a cell is two
+// loads a channel plane or two loads in all, four cells of a thread in flight
+// together.  Bound by the latency of those loads: at 1x3x1024x2048 fp16 with
+// 128-pixel blocks there are 128 workgroups, so each takes 1024 threads
+// (16 waves a CU) instead of 256: 17.4 -> 7.3 us, the selection 4.3 -> 2.5.
+template <typename T, int L, int C, int NT>
+__global__ __launch_bounds__(NT) void k_policy_score(const T* __restrict__ x, int Cn, int H, int W, int bs, int GH,
                                                      int GW, float* __restrict__ score) {
     const int k = (int)blockIdx.x;
     const int per = GH * GW;
     const int n = k / per, r = k - n * per, gy = r / GW, gx = r - gy * GW;
     const int lb = bs >> 1, cells = lb * lb;
     float acc = 0.0f;
-    for (int cell = (int)threadIdx.x; cell < cells; cell += WG) {
-        const int ci = cell / lb, cj = cell - ci * lb;
-        const int Y = gy * bs + 2 * ci, X = gx * bs + 2 * cj;
-        float d2[4] = {0.f, 0.f, 0.f, 0.f};
-        for (int c = 0; c < C; ++c) {
-            const T a = px<T, L>(x, n, C, H, W, Y, X, c);
-            const T b = px<T, L>(x, n, C, H, W, Y, X + 1, c);
-            const T cc = px<T, L>(x, n, C, H, W, Y + 1, X, c);
-            const T d = px<T, L>(x, n, C, H, W, Y + 1, X + 1, c);
-            const float m = to_f32(avg4(a, b, cc, d));
-            const float e0 = to_f32(a) - m, e1 = to_f32(b) - m, e2 = to_f32(cc) - m, e3 = to_f32(d) - m;
-            d2[0] += e0 * e0;
-            d2[1] += e1 * e1;
-            d2[2] += e2 * e2;
-            d2[3] += e3 * e3;
+    if constexpr (C > 0) {
+        constexpr int U = 4;
+        for (int base = (int)threadIdx.x; base < cells; base += U * NT) {
+            PixPair<T, L, C> t[U], b[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int cell = min(base + u * NT, cells - 1);  // past the end: a load that is not used
+                const int ci = cell / lb, cj = cell - ci * lb;
+                const int Y = gy * bs + 2 * ci, X = gx * bs + 2 * cj;
+                t[u].load(x, n, H, W, Y, X);
+                b[u].load(x, n, H, W, Y + 1, X);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                float d2[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int c = 0; c < C; ++c) cell_channel(t[u].at(0, c), t[u].at(1, c), b[u].at(0, c), b[u].at(1, c), d2);
+                acc += base + u * NT < cells ? cell_norms(d2) : 0.0f;
+            }
         }
-        acc += (__builtin_sqrtf(d2[0]) + __builtin_sqrtf(d2[1])) + (__builtin_sqrtf(d2[2]) + __builtin_sqrtf(d2[3]));
+    } else {
+        for (int cell = (int)threadIdx.x; cell < cells; cell += NT) {
+            const int ci = cell / lb, cj = cell - ci * lb;
+            const int Y = gy * bs + 2 * ci, X = gx * bs + 2 * cj;
+            float d2[4] = {0.f, 0.f, 0.f, 0.f};
+            for (int c = 0; c < Cn; ++c)
+                cell_channel(px<T, L>(x, n, Cn, H, W, Y, X, c), px<T, L>(x, n, Cn, H, W, Y, X + 1, c),
+                             px<T, L>(x, n, Cn, H, W, Y + 1, X, c), px<T, L>(x, n, Cn, H, W, Y + 1, X + 1, c), d2);
+            acc += cell_norms(d2);
+        }
     }
     // fixed-order reduction: lanes of a wave, then the waves in order
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
-    __shared__ float s_part[WG / 64];
+    __shared__ float s_part[NT / 64];
     if ((threadIdx.x & 63) == 0) s_part[threadIdx.x >> 6] = acc;
     __syncthreads();
     if (threadIdx.x == 0) {
         float t = 0.0f;
 #pragma unroll
-        for (int w = 0; w < WG / 64; ++w) t += s_part[w];
+        for (int w = 0; w < NT / 64; ++w) t += s_part[w];
         score[k] = t / (float)(bs * bs);
     }
 }
 
 constexpr int POL_MAXB = 8192;  // blocks per image the LDS score table holds
+constexpr int POL_ROWS = 64;    // blocks ranked by one workgroup, four threads each
 
-__global__ __launch_bounds__(WG) void k_policy_select(const float* __restrict__ score, int per, int khigh,
+// Workgroup (image, group of 64 blocks): a block's rank is the number of
+// blocks ahead of it; its four threads count a quarter of the scores each
+// (neighbouring lanes, so the four reads of a step are one LDS word apart).
+__global__ __launch_bounds__(WG) void k_policy_select(const float* __restrict__ score, int per, int groups, int khigh,
                                                       uint8_t* __restrict__ mask) {
     __shared__ float s[POL_MAXB];
-    const int n = (int)blockIdx.x;
+    const int n = (int)blockIdx.x / groups, grp = (int)blockIdx.x - n * groups;
     const float* sc = score + (size_t)n * per;
     for (int i = (int)threadIdx.x; i < per; i += WG) s[i] = sc[i];
     __syncthreads();
-    for (int b = (int)threadIdx.x; b < per; b += WG) {
-        const float v = s[b];
-        int rank = 0;
-        for (int j = 0; j < per; ++j) {
-            const float t = s[j];
-            rank += (t > v || (t == v && j < b)) ? 1 : 0;
-        }
-        mask[(size_t)n * per + b] = rank < khigh ? 1 : 0;
+    const int b = grp * POL_ROWS + ((int)threadIdx.x >> 2), q = (int)threadIdx.x & 3;
+    const float v = s[min(b, per - 1)];
+    int rank = 0;
+#pragma unroll 8
+    for (int j = q; j < per; j += 4) {
+        const float t = s[j];
+        rank += (t > v || (t == v && j < b)) ? 1 : 0;
     }
+    rank += __shfl_xor(rank, 1, 64);
+    rank += __shfl_xor(rank, 2, 64);
+    if (b < per && q == 0) mask[(size_t)n * per + b] = rank < khigh ? 1 : 0;
 }
 
-template <typename T>
-hipError_t policy_t(int layout, const void* x, int N, int C, int H, int W, int bs, float* score, int khigh,
-                    uint8_t* mask, hipStream_t st) {
+template <typename T, int L, int C>
+void score_run(const void* x, int Cn, int H, int W, int bs, int GH, int GW, long long B, float* score, hipStream_t st) {
+    // 1024 threads where the blocks alone would leave less than two
+    // workgroups of 256 for every CU, and a block has cells for them
+    if (B < 2LL * device_cus() && (bs / 2) * (bs / 2) >= 1024)
+        hipLaunchKernelGGL((k_policy_score<T, L, C, 1024>), dim3((unsigned)B), dim3(1024), 0, st, (const T*)x, Cn, H, W,
+                           bs, GH, GW, score);
+    else
+        hipLaunchKernelGGL((k_policy_score<T, L, C, WG>), dim3((unsigned)B), dim3(WG), 0, st, (const T*)x, Cn, H, W, bs,
+                           GH, GW, score);
+}
+
+template <typename T, int L>
+hipError_t policy_t(const void* x, int N, int C, int H, int W, int bs, float* score, int khigh, uint8_t* mask,
+                    hipStream_t st) {
     const int GH = H / bs, GW = W / bs;
     const long long B = (long long)N * GH * GW;
-    if (layout == NHWC)
-        hipLaunchKernelGGL((k_policy_score<T, NHWC>), dim3((unsigned)B), dim3(WG), 0, st, (const T*)x, C, H, W, bs,
-                           GH, GW, score);
-    else
-        hipLaunchKernelGGL((k_policy_score<T, NCHW>), dim3((unsigned)B), dim3(WG), 0, st, (const T*)x, C, H, W, bs,
-                           GH, GW, score);
+    // (W is even: blocks are)
+    const bool pairs = (reinterpret_cast<uintptr_t>(x) & (2 * sizeof(T) - 1)) == 0;
+    switch (pairs ? C : 0) {
+    case 1: score_run<T, L, 1>(x, C, H, W, bs, GH, GW, B, score, st); break;
+    case 2: score_run<T, L, 2>(x, C, H, W, bs, GH, GW, B, score, st); break;
+    case 3: score_run<T, L, 3>(x, C, H, W, bs, GH, GW, B, score, st); break;
+    case 4: score_run<T, L, 4>(x, C, H, W, bs, GH, GW, B, score, st); break;
+    default: score_run<T, L, 0>(x, C, H, W, bs, GH, GW, B, score, st); break;
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_policy_select, dim3((unsigned)N), dim3(WG), 0, st, (const float*)score, GH * GW, khigh, mask);
+    const int groups = (GH * GW + POL_ROWS - 1) / POL_ROWS;
+    hipLaunchKernelGGL(k_policy_select, dim3((unsigned)(N * groups)), dim3(WG), 0, st, (const float*)score, GH * GW,
+                       groups, khigh, mask);
     return hipGetLastError();
 }
 
@@ -114,9 +191,12 @@ int policy_max_blocks() { return POL_MAXB; }
 hipError_t launch_policy(int dtype, int layout, const void* x, int N, int C, int H, int W, int bs, float* score,
                          int khigh, uint8_t* mask, hipStream_t st) {
     switch (dtype) {
-    case 0: return policy_t<float>(layout, x, N, C, H, W, bs, score, khigh, mask, st);
-    case 1: return policy_t<f16>(layout, x, N, C, H, W, bs, score, khigh, mask, st);
-    default: return policy_t<bf16>(layout, x, N, C, H, W, bs, score, khigh, mask, st);
+    case 0: return layout == NHWC ? policy_t<float, NHWC>(x, N, C, H, W, bs, score, khigh, mask, st)
+                                  : policy_t<float, NCHW>(x, N, C, H, W, bs, score, khigh, mask, st);
+    case 1: return layout == NHWC ? policy_t<f16, NHWC>(x, N, C, H, W, bs, score, khigh, mask, st)
+                                  : policy_t<f16, NCHW>(x, N, C, H, W, bs, score, khigh, mask, st);
+    default: return layout == NHWC ? policy_t<bf16, NHWC>(x, N, C, H, W, bs, score, khigh, mask, st)
+                                  : policy_t<bf16, NCHW>(x, N, C, H, W, bs, score, khigh, mask, st);
     }
 }
 

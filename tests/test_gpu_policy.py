@@ -99,3 +99,27 @@ def test_policy_ties_rank_by_block_id():
     want = np.zeros(32, np.uint8)
     want[:k] = 1
     np.testing.assert_array_equal(mask.cpu().numpy().reshape(-1), want)
+
+
+@pytest.mark.parametrize("C", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("dtype,layout,offset", [("f16", "nchw", 0), ("bf16", "nhwc", 0), ("f32", "nhwc", 0),
+                                                 ("f16", "nhwc", 1), ("f32", "nchw", 1)])
+def test_policy_small_images(dtype, layout, offset, C):
+    """One to five channels, an image that is and one that is not aligned to
+    two elements, blocks whose cells are no multiple of the workgroup, more
+    than one group of blocks in the ranking (9 x 9 blocks), and one block big
+    enough for the 1024-thread kernel."""
+    import paper_2011_12025_amd as sb
+    for bs, g, tau in ((6, 9, 0.37), (68, 1, 1.0)):
+        x = inputs.feature_map(159, 1, C, g * bs, g * bs, dtype)
+        buf = torch.zeros(x.numel() + offset, dtype=x.dtype, device="cuda")
+        shape, N = x.shape, x.shape[0]
+        fmt = torch.channels_last if layout == "nhwc" else torch.contiguous_format
+        xd = torch.empty(shape, dtype=x.dtype, device="cuda", memory_format=fmt)
+        xd = torch.as_strided(buf, shape, xd.stride(), offset).copy_(x)
+        ref_mask, ref_sc = oracle.policy(x.float().numpy(), bs, tau, dtype)
+        mask, sc = sb.policy_heuristic(xd, bs, tau, layout=1 if layout == "nhwc" else 0)
+        torch.cuda.synchronize()
+        sc = sc.cpu().numpy().astype(np.float64)
+        assert np.all(np.abs(sc - ref_sc) <= SCORE_RTOL * np.abs(ref_sc) + 1e-6)
+        np.testing.assert_array_equal(mask.cpu().numpy(), oracle.policy_select(sc, tau))
