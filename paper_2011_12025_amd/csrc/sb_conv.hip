@@ -1,27 +1,45 @@
-// 3x3 block convolution as an MFMA implicit GEMM for gfx950.
+// 3x3 block convolution as an MFMA implicit GEMM for gfx950: the general
+// kernel, for every type, layout, channel count and block size.
 //
 // GEMM view per block: output pixels x output channels, K = 9 taps x C_in.
-// One workgroup (4 waves) computes a tile of up to 256 output pixels (whole
-// rows of one block) x 64 output channels.  K is walked in chunks of 64
-// bytes of input channels (32 fp16/bf16 or 16 fp32): the padded input rows
-// of the tile and the chunk's weights are staged in LDS with an XOR swizzle
-// of the 16-byte sub-chunks, and every tap reads its pixel fragments at a
-// constant offset from the same LDS tile.
+// One workgroup (4 waves) computes a tile of whole rows of one block (about
+// 64, 128 or 256 output pixels, chosen per call) x up to 64 output channels.
+// K is walked in chunks of 64 bytes of input channels (32 fp16/bf16 or 16
+// fp32): the padded input rows of the tile and the chunk's weights are staged
+// in LDS with an XOR swizzle of the 16-byte sub-chunks, and every tap reads
+// its pixel fragments at a constant offset from the same LDS tile.
 //
 // MFMA: v_mfma_f32_16x16x32_{f16,bf16} (8 K values per lane) or
 // v_mfma_f32_16x16x4_f32, with the weights as the A operand (16 output
-// channels) and the pixels as the B operand (16 pixels).  A lane's result is
-// then 4 consecutive output channels of one pixel, which the epilogue stores
-// directly (8 bytes for fp16/bf16) without a trip through LDS.  Each wave
-// owns up to four 16-pixel sub-tiles and all four 16-channel sub-tiles (64
-// fp32 accumulators per lane).
+// channels) and the pixels as the B operand (16 pixels).  A lane reads 16
+// bytes of a row either way: for fp32 its four channels go to four MFMAs (K
+// index kg of MFMA i is channel 4 kg + i of the chunk, in both operands).
+// A lane's result is 4 consecutive output channels of one pixel, which the
+// epilogue stores directly without a trip through LDS.  Each wave owns up to
+// four 16-pixel sub-tiles and all 16-channel sub-tiles (64 fp32 accumulators
+// per lane); channel sub-tiles past C_out are not computed.
 //
-// Staging is batched: every thread computes the sources of several 16-byte
-// vectors, issues all their loads, then writes LDS.  While the MFMAs of
-// chunk kc run, the weights and the first input batch of chunk kc+1 are
-// already being loaded into registers.  LDS use (58.6 KiB for 32-pixel
-// blocks) allows two workgroups per CU, so one workgroup's loads overlap
-// the other's MFMAs.
+// Start-up: chunk 0's weights are requested first (they do not depend on the
+// mask), then the block plan gives every pixel of the padded tile a source
+// descriptor in LDS (an address, and whether it is a copy or a 2x2 average),
+// which every chunk only adds its channel offset to.  While the MFMAs of
+// chunk kc run, the weights and the first inputs of chunk kc + 1 are already
+// being loaded into registers.  LDS (58.6 KiB for 32-pixel blocks at 256
+// pixels a tile) leaves room for two workgroups per CU, so one workgroup's
+// loads overlap the other's MFMAs.
+//
+// Staging follows the memory: channels-last tensors of whole 16-byte vectors
+// move those (a thread takes one sub-chunk of one pixel); NCHW tensors are
+// read along x (neighbouring lanes take neighbouring pixels of one channel
+// plane, a 2x2 cell is two loads of two pixels, the weights of a filter are one
+// run of words), other channels-last ones element by element.
+//
+// Bounds: fp32 by MFMA issue and by the staging beside it
+// (the 256x512, 64-channel layer, half low, NCHW: 179 -> 112 us, 39 us of MFMA
+// issue; a 64x64 layer of 16 channels 31 -> 11 us), small and ragged 16-bit
+// calls by the latency of the chain mask -> descriptors -> inputs -> MFMAs (two
+// 96x180 maps, 48 -> 72 channels, 12-pixel blocks: 22 -> 20 us; one 128x256
+// map of 96 channels, 16-pixel blocks: 37 -> 26 us).
 //
 // The tile loader is where the block modules live:
 //   SRC_PADDED : reads padded stacks (plain conv of segblocks_conv3x3)
@@ -31,6 +49,9 @@
 //
 // Weights: channels-last calls take OHWI memory ([C_out][3][3][C_in], the
 // memory of a channels_last [C_out, C_in, 3, 3] tensor), NCHW calls OIHW.
+#include <algorithm>
+#include <type_traits>
+
 #include "sb_common.h"
 #include "sb_kernels.h"
 #include "sb_pixel.h"
@@ -43,40 +64,39 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
+// One 16-byte operand of every lane covers 32 (fp16 / bf16) or 16 (fp32)
+// channels: STEPS MFMAs, of which step i takes.  The caller runs a step over
+// all of its accumulators before the next: an fp32 MFMA that follows another
+// on the same accumulator waits for it (measured: the MFMA phase of a lone
+// workgroup took 2.4 times its issue time with the four steps of an
+// accumulator back to back).
 template <typename T> struct MF;
 template <> struct MF<f16> {
-    static constexpr int KS = 32, EL = 8;  // K per instruction, K values per lane
-    typedef halfx8 frag;
-    static __device__ __forceinline__ floatx4 mma(frag a, frag b, floatx4 c) {
-        return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
+    static constexpr int STEPS = 1;
+    static __device__ __forceinline__ floatx4 mma(uint4 a, uint4 b, int, floatx4 c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(halfx8, a), __builtin_bit_cast(halfx8, b), c,
+                                                      0, 0, 0);
     }
 };
 template <> struct MF<bf16> {
-    static constexpr int KS = 32, EL = 8;
-    typedef bf16x8 frag;
-    static __device__ __forceinline__ floatx4 mma(frag a, frag b, floatx4 c) {
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+    static constexpr int STEPS = 1;
+    static __device__ __forceinline__ floatx4 mma(uint4 a, uint4 b, int, floatx4 c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c,
+                                                       0, 0, 0);
     }
 };
 template <> struct MF<float> {
-    static constexpr int KS = 4, EL = 1;
-    typedef float frag;
-    static __device__ __forceinline__ floatx4 mma(frag a, frag b, floatx4 c) {
-        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    static constexpr int STEPS = 4;
+    static __device__ __forceinline__ floatx4 mma(uint4 a, uint4 b, int i, floatx4 c) {
+        const floatx4 fa = __builtin_bit_cast(floatx4, a), fb = __builtin_bit_cast(floatx4, b);
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i], fb[i], c, 0, 0, 0);
     }
 };
 
-constexpr int NT = 64;     // output channels per workgroup
+constexpr int NT = 64;     // most output channels per workgroup
 constexpr int ROWB = 64;   // LDS bytes per tile pixel / weight row (one K chunk)
-constexpr int MT = 256;    // target output pixels per workgroup
-constexpr int W_BYTES = 9 * NT * ROWB;
-// Input-tile vectors per thread per batch (UI), and prefetched during the
-// MFMAs (UP).  A fused-pad source may need four loads per vector (2x2
-// average), so its batches are smaller and only its weights are prefetched,
-// to stay within 256 VGPRs (the next chunk's input pixels share cache lines
-// with the current chunk's and come from L2).
-template <int SRC> struct Batches { static constexpr int UI = 2, UP = 0; };
-template <> struct Batches<SRC_PADDED> { static constexpr int UI = 4, UP = 2; };
+constexpr int UI = 4;      // 16-byte input vectors per thread and batch
+constexpr int UA = 2;      // of them, averages in flight together
 constexpr int UW = 9 * NT * (ROWB / 16) / WG;  // weight vectors per thread per chunk
 static_assert(UW * WG == 9 * NT * (ROWB / 16), "weight staging covers the chunk exactly");
 
@@ -91,51 +111,128 @@ struct Tile {
 };
 
 // Source of the tile pixel p (padded-tile coordinates, row-major over
-// (rows + 2) x pe) for channels starting at c.
+// (rows + 2) x pe), channel 0.
 template <typename T, int L, int SRC>
-__device__ __forceinline__ Src<T> tile_src(const Geo& g, const ConvArgs& a, const Neigh& nb, const Tile& t, int p,
-                                           int c) {
+__device__ __forceinline__ Src<T> tile_src(const Geo& g, const ConvArgs& a, const Neigh& nb, const Tile& t, int p) {
     const int pu = p / t.pe, pv = p - pu * t.pe;
     const int u = t.r0 + pu;
     if constexpr (SRC == SRC_PADDED) {
-        return src_copy<T>(stack_at<T, L>((const T*)(t.high ? a.in_hi : a.in_lo), t.slot, a.C_in, t.pe, u, pv, c));
+        return src_copy<T>(stack_at<T, L>((const T*)(t.high ? a.in_hi : a.in_lo), t.slot, a.C_in, t.pe, u, pv, 0),
+                           !t.high);
     } else if constexpr (SRC == SRC_PACKED) {
         return packed_src<T, L>((const T*)a.in_hi, (const T*)a.in_lo, a.C_in, g.bs, nb, a.hi_cap, a.lo_cap, u - 1,
-                                pv - 1, c, pad_mode(a.flags));
+                                pv - 1, 0, pad_mode(a.flags));
     } else {
-        return dense_src<T, L>((const T*)a.in_hi, t.n, a.C_in, g.H, g.W, g.bs, t.gy, t.gx, nb, u - 1, pv - 1, c,
+        return dense_src<T, L>((const T*)a.in_hi, t.n, a.C_in, g.H, g.W, g.bs, t.gy, t.gx, nb, u - 1, pv - 1, 0,
                                pad_mode(a.flags));
     }
 }
 
-// One batch of UI 16-byte input vectors (channels-last, C_in % 8 (fp16) or
-// % 4 (fp32) == 0): item it -> pixel it/4, sub-chunk it%4.
-template <typename T, int L, int SRC, int U>
-struct InBatch {
-    static constexpr int KC = ROWB / (int)sizeof(T);
-    static constexpr int VQ = 16 / (int)sizeof(T);
-    SrcBatch<T, VQ, U> b;
+// Descriptor of a tile pixel: the byte offset of its source's channel 0 from the
+// high stack's (or the map's) base, also where it lies in the low stack, and
+// what it is; 0: a zero.  (Offsets from a kernel argument and not addresses,
+// nor a choice between two bases: the compiler loses the address space of
+// either, loads through the flat path, and the LDS reads of the MFMA loop
+// then wait for those loads.)
+constexpr unsigned long long SD_AVG = 1ull << 63, SD_LOW = 1ull << 62, SD_SOME = 1ull << 61;
+constexpr unsigned long long SD_OFF = SD_SOME - 1;
 
-    __device__ __forceinline__ void issue(const Geo& g, const ConvArgs& a, const Neigh& nb, const Tile& t,
+// What every descriptor of a workgroup shares.
+template <typename T>
+struct Strides {
+    const T* hi;            // the high stack or the map
+    long long ch_hi, ch_d;  // elements from a channel to the next (high stack or map); low stack: ch_hi + ch_d
+    long long d1, d2;       // to the right and to the lower pixel of an averaged cell
+    __device__ __forceinline__ long long ch(unsigned long long d) const { return ch_hi + ((d & SD_LOW) ? ch_d : 0); }
+    __device__ __forceinline__ const T* at(unsigned long long d) const {
+        return reinterpret_cast<const T*>(reinterpret_cast<const char*>(hi) + ((long long)(d << 3) >> 3));
+    }
+};
+template <typename T, int L, int SRC>
+__device__ __forceinline__ Strides<T> make_strides(const Geo& g, const ConvArgs& a, const Tile& t) {
+    const long long lb = g.bs >> 1, row = SRC == SRC_DENSE ? g.W : g.bs, px = L == NHWC ? a.C_in : 1;
+    Strides<T> s;
+    s.hi = (const T*)a.in_hi;
+    s.ch_hi = L == NHWC ? 1 : (SRC == SRC_DENSE ? (long long)g.H * g.W
+                                                : SRC == SRC_PADDED ? (long long)t.pe * t.pe : (long long)g.bs * g.bs);
+    s.ch_d = L == NHWC || SRC == SRC_PADDED ? 0 : lb * lb - s.ch_hi;
+    s.d1 = px;
+    s.d2 = px * row;
+    return s;
+}
+
+// The thread index, opaque to the optimiser at each use: the addresses made
+// from it are recomputed for every chunk instead of all being kept in
+// registers across the MFMAs.
+__device__ __forceinline__ int tid_here() {
+    int t = (int)threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
+// ---- channels-last staging in 16-byte vectors: item it is sub-chunk it % 4 of
+// pixel it / 4.  issue() requests every item's (first) vector, commit() the
+// three others of the averages, then writes LDS: what is in flight across
+// the MFMAs is one vector an item.
+template <typename T>
+struct VecIn {
+    static constexpr int KC = ROWB / (int)sizeof(T), VQ = 16 / (int)sizeof(T);
+    Vec<T, VQ> v[UI];
+
+    static __device__ __forceinline__ unsigned long long desc(const unsigned long long* s_desc, int C_in, int in_px,
+                                                              int it, int kc) {
+        return it < in_px * 4 && kc * KC + (it & 3) * VQ < C_in ? s_desc[it >> 2] : 0ull;
+    }
+    __device__ __forceinline__ void issue(const unsigned long long* s_desc, const Strides<T>& st, int C_in, int in_px,
                                           int base, int kc) {
-        const int items = t.in_px * 4;
+        const int tid = tid_here();
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int it = base + u * WG + (int)threadIdx.x;
-            Src<T> s = src_zero<T>();
-            if (it < items) {
-                const int c0 = kc * KC + (it & 3) * VQ;
-                if (c0 < a.C_in) s = tile_src<T, L, SRC>(g, a, nb, t, it >> 2, c0);
-            }
-            b.issue(u, s);
+        for (int u = 0; u < UI; ++u) {
+            const int it = base + u * WG + tid;
+            const unsigned long long d = desc(s_desc, C_in, in_px, it, kc);
+            v[u] = vzero<T, VQ>();
+            if (d) v[u] = vload<T, VQ>(st.at(d) + kc * KC + (it & 3) * VQ);
         }
     }
-    __device__ __forceinline__ void commit(unsigned char* s_in, const Tile& t, int base) const {
-        const int items = t.in_px * 4;
+    // the other three vectors of the averages among items u0 .. u0 + UA - 1, and those items to LDS
+    struct Rest {
+        Vec<T, VQ> r[UA][3];
+        bool avg[UA];
+    };
+    __device__ __forceinline__ void rest(Rest& q, int u0, const unsigned long long* s_desc, const Strides<T>& st,
+                                         int C_in, int in_px, int base, int kc) const {
+        const int tid = tid_here();
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int it = base + u * WG + (int)threadIdx.x;
-            if (it < items) *reinterpret_cast<uint4*>(s_in + swz(it >> 2, it & 3)) = b.value(u).raw;
+        for (int u = 0; u < UA; ++u) {
+            const int it = base + (u0 + u) * WG + tid;
+            const unsigned long long d = desc(s_desc, C_in, in_px, it, kc);
+            q.avg[u] = (d & SD_AVG) != 0;
+            if (q.avg[u]) {
+                const T* p = st.at(d) + kc * KC + (it & 3) * VQ;
+                q.r[u][0] = vload<T, VQ>(p + st.d1);
+                q.r[u][1] = vload<T, VQ>(p + st.d2);
+                q.r[u][2] = vload<T, VQ>(p + st.d2 + st.d1);
+            }
+        }
+    }
+    __device__ __forceinline__ void finish(const Rest& q, int u0, int in_px, int base, unsigned char* s_in) {
+        const int tid = tid_here();
+#pragma unroll
+        for (int u = 0; u < UA; ++u) {
+            const int it = base + (u0 + u) * WG + tid;
+            if (q.avg[u]) v[u0 + u] = vavg4<T, VQ>(v[u0 + u], q.r[u][0], q.r[u][1], q.r[u][2]);
+            if (it < in_px * 4) *reinterpret_cast<uint4*>(s_in + swz(it >> 2, it & 3)) = v[u0 + u].raw;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    __device__ __forceinline__ void commit(int u0, const unsigned long long* s_desc, const Strides<T>& st, int C_in,
+                                           int in_px, int base, int kc, unsigned char* s_in) {
+#pragma unroll
+        for (int u = 0; u < UI; u += UA) {
+            if (u < u0) continue;
+            Rest q;
+            rest(q, u, s_desc, st, C_in, in_px, base, kc);
+            finish(q, u, in_px, base, s_in);
         }
     }
 };
@@ -143,60 +240,173 @@ struct InBatch {
 // The weights of one K chunk as 16-byte vectors of OHWI memory, stored in LDS
 // as rows [tap][co] of 64 bytes (the chunk's input channels).
 template <typename T>
-struct WBatch {
-    static constexpr int KC = ROWB / (int)sizeof(T);
-    static constexpr int VQ = 16 / (int)sizeof(T);
+struct VecW {
+    static constexpr int KC = ROWB / (int)sizeof(T), VQ = 16 / (int)sizeof(T);
     Vec<T, VQ> w[UW];
 
-    __device__ __forceinline__ void issue(const ConvArgs& a, int co0, int kc) {
+    __device__ __forceinline__ void issue(const ConvArgs& a, int co0, int nt, int kc) {
         const T* __restrict__ wgt = (const T*)a.weight;
+        const int tid = tid_here();
 #pragma unroll
         for (int u = 0; u < UW; ++u) {
-            const int v = u * WG + (int)threadIdx.x;
+            const int v = u * WG + tid;
             const int col = v / 36, rem = v - col * 36;
             const int tap = rem >> 2, q = rem & 3;
             const int co = co0 + col, ci = kc * KC + q * VQ;
-            if (co < a.C_out && ci < a.C_in) w[u] = vload<T, VQ>(wgt + ((size_t)co * 9 + tap) * a.C_in + ci);
-            else                             w[u] = vzero<T, VQ>();
+            if (col < nt && co < a.C_out && ci < a.C_in) w[u] = vload<T, VQ>(wgt + ((size_t)co * 9 + tap) * a.C_in + ci);
+            else                                         w[u] = vzero<T, VQ>();
         }
     }
-    __device__ __forceinline__ void commit(unsigned char* s_w) const {
+    __device__ __forceinline__ void commit(unsigned char* s_w, int nt) const {
+        const int tid = tid_here();
 #pragma unroll
         for (int u = 0; u < UW; ++u) {
-            const int v = u * WG + (int)threadIdx.x;
+            const int v = u * WG + tid;
             const int col = v / 36, rem = v - col * 36;
             const int tap = rem >> 2, q = rem & 3;
-            *reinterpret_cast<uint4*>(s_w + swz(tap * NT + col, q)) = w[u].raw;
+            if (col < nt) *reinterpret_cast<uint4*>(s_w + swz(tap * nt + col, q)) = w[u].raw;
         }
     }
 };
 
-// Element-wise staging of one K chunk (any layout and channel count): the
-// input tile and the weights (OIHW for NCHW calls, OHWI for NHWC calls).
-template <typename T, int L, int SRC>
-__device__ __forceinline__ void stage_scalar(const Geo& g, const ConvArgs& a, const Neigh& nb, const Tile& t,
-                                             int co0, int kc, unsigned char* s_in, unsigned char* s_w) {
-    constexpr int KC = ROWB / (int)sizeof(T);
-    constexpr int VQ = 16 / (int)sizeof(T);
-    const int tid = threadIdx.x;
-    for (int it = tid; it < t.in_px * 4; it += WG) {
-        const int p = it >> 2, q = it & 3;
-        const int c0 = kc * KC + q * VQ;
+// ---- NCHW staging along x: a thread takes whole pixels (every channel of the
+// chunk), so neighbouring lanes read neighbouring elements of a plane.  The
+// first pixel's copies are requested a chunk ahead.
+template <typename T>
+struct PlaneIn {
+    static constexpr int KC = ROWB / (int)sizeof(T), VQ = 16 / (int)sizeof(T);
+    T v[KC];
+
+    static __device__ __forceinline__ unsigned long long desc(const unsigned long long* s_desc, int in_px, int p) {
+        return p < in_px ? s_desc[p] : 0ull;
+    }
+    __device__ __forceinline__ void issue(const unsigned long long* s_desc, const Strides<T>& st, int C_in, int in_px,
+                                          int base, int kc) {
+        const unsigned long long d = desc(s_desc, in_px, base + (int)threadIdx.x);
+        if (C_in - kc * KC < KC) return;  // a partial chunk is staged channel by channel in commit()
+#pragma unroll
+        for (int c = 0; c < KC; ++c) v[c] = from_f32<T>(0.0f);
+        if (d && !(d & SD_AVG)) {
+            const long long cs = st.ch(d);
+            const T* p = st.at(d) + kc * KC * cs;
+#pragma unroll
+            for (int c = 0; c < KC; ++c, p += cs) v[c] = *p;
+        }
+    }
+    // to LDS; an average is loaded here, two pixels a load, eight channels in flight
+    __device__ __forceinline__ void commit(const unsigned long long* s_desc, const Strides<T>& st, int C_in, int in_px,
+                                           int base, int kc, unsigned char* s_in) {
+        const int pix = base + (int)threadIdx.x;
+        const unsigned long long d = desc(s_desc, in_px, pix);
+        if (C_in - kc * KC < KC) {
+            if (pix >= in_px) return;
+            const long long cs = st.ch(d);
+            const T* p = st.at(d) + kc * KC * cs;
+#pragma unroll 4
+            for (int c = 0; c < KC; ++c, p += cs) {
+                T x = from_f32<T>(0.0f);
+                if (d && kc * KC + c < C_in) {
+                    x = p[0];
+                    if (d & SD_AVG) x = avg4(x, p[1], p[st.d2], p[st.d2 + 1]);
+                }
+                const int byte = c * (int)sizeof(T);
+                *reinterpret_cast<T*>(s_in + swz(pix, byte >> 4) + (byte & 15)) = x;
+            }
+            return;
+        }
+        if (d & SD_AVG) {
+            constexpr int HC = 8;
+            const T* p = st.at(d) + kc * KC * st.ch_hi;
+#pragma unroll
+            for (int h = 0; h < KC / HC; ++h) {
+                T top[HC][2], bot[HC][2];
+#pragma unroll
+                for (int c = 0; c < HC; ++c, p += st.ch_hi) {
+                    __builtin_memcpy(top[c], p, 2 * sizeof(T));
+                    __builtin_memcpy(bot[c], p + st.d2, 2 * sizeof(T));
+                }
+#pragma unroll
+                for (int c = 0; c < HC; ++c) v[h * HC + c] = avg4(top[c][0], top[c][1], bot[c][0], bot[c][1]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (pix < in_px) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                Vec<T, VQ> o;
+#pragma unroll
+                for (int e = 0; e < VQ; ++e) o.e[e] = v[q * VQ + e];
+                *reinterpret_cast<uint4*>(s_in + swz(pix, q)) = o.raw;
+            }
+        }
+    }
+};
+
+// The weights of one K chunk of OIHW memory: thread (co, q) takes the nine taps
+// of the VQ channels of sub-chunk q, one run of 144 bytes, and turns them into
+// nine 16-byte vectors of one tap each.
+template <typename T>
+struct PlaneW {
+    static constexpr int KC = ROWB / (int)sizeof(T), VQ = 16 / (int)sizeof(T);
+    static_assert(NT * 4 == WG, "one filter sub-chunk per thread");
+    T w[VQ * 9];
+
+    __device__ __forceinline__ void issue(const ConvArgs& a, int co0, int nt, int kc) {
+        const int col = (int)threadIdx.x >> 2, c0 = kc * KC + ((int)threadIdx.x & 3) * VQ;
+        const int nc = col < nt && co0 + col < a.C_out ? min(VQ, a.C_in - c0) : 0;  // channels of this thread's run
+        const T* p = (const T*)a.weight + ((size_t)(nc > 0 ? co0 + col : 0) * a.C_in + (nc > 0 ? c0 : 0)) * 9;
+        if (nc == VQ) {
+#pragma unroll
+            for (int v = 0; v < 9; ++v) __builtin_memcpy(w + v * VQ, p + v * VQ, 16);
+        } else {
+#pragma unroll
+            for (int e = 0; e < VQ * 9; ++e) {
+                w[e] = from_f32<T>(0.0f);
+                if (e < nc * 9) w[e] = p[e];
+            }
+        }
+    }
+    __device__ __forceinline__ void commit(unsigned char* s_w, int nt) const {
+        const int col = (int)threadIdx.x >> 2, q = (int)threadIdx.x & 3;
+        if (col >= nt) return;
+#pragma unroll
+        for (int tap = 0; tap < 9; ++tap) {
+            Vec<T, VQ> o;
+#pragma unroll
+            for (int e = 0; e < VQ; ++e) o.e[e] = w[e * 9 + tap];
+            *reinterpret_cast<uint4*>(s_w + swz(tap * nt + col, q)) = o.raw;
+        }
+    }
+};
+
+// ---- element-wise staging (channels-last tensors that are not whole vectors)
+template <typename T>
+__device__ __forceinline__ void stage_in_scalar(const unsigned long long* s_desc, const Strides<T>& st, int C_in,
+                                                int in_px, int kc, unsigned char* s_in) {
+    constexpr int KC = ROWB / (int)sizeof(T), VQ = 16 / (int)sizeof(T);
+    for (int it = (int)threadIdx.x; it < in_px * 4; it += WG) {
+        const int p = it >> 2, q = it & 3, c0 = kc * KC + q * VQ;
+        const unsigned long long d = s_desc[p];
+        const long long cs = st.ch(d);
+        const T* s = st.at(d) + c0 * cs;
         Vec<T, VQ> val;
 #pragma unroll
         for (int e = 0; e < VQ; ++e) {
-            const int c = c0 + e;
             T v = from_f32<T>(0.0f);
-            if (c < a.C_in) {
-                const Src<T> s = tile_src<T, L, SRC>(g, a, nb, t, p, c);
-                if (s.p) v = s.avg ? avg4(s.p[0], s.p[s.d1], s.p[s.d2], s.p[s.d2 + s.d1]) : s.p[0];
+            if (d && c0 + e < C_in) {
+                const T* x = s + e * cs;
+                v = (d & SD_AVG) ? avg4(x[0], x[st.d1], x[st.d2], x[st.d2 + st.d1]) : x[0];
             }
             val.e[e] = v;
         }
         *reinterpret_cast<uint4*>(s_in + swz(p, q)) = val.raw;
     }
+}
+template <typename T>
+__device__ __forceinline__ void stage_w_scalar(const ConvArgs& a, int co0, int nt, int kc, unsigned char* s_w) {
+    constexpr int KC = ROWB / (int)sizeof(T);
     const T* __restrict__ wgt = (const T*)a.weight;
-    for (int it = tid; it < NT * KC; it += WG) {
+    for (int it = (int)threadIdx.x; it < nt * KC; it += WG) {
         const int col = it / KC, cil = it - col * KC;
         const int co = co0 + col, ci = kc * KC + cil;
         const bool ok = co < a.C_out && ci < a.C_in;
@@ -204,26 +414,119 @@ __device__ __forceinline__ void stage_scalar(const Geo& g, const ConvArgs& a, co
 #pragma unroll
         for (int tap = 0; tap < 9; ++tap) {
             T wv = from_f32<T>(0.0f);
-            if (ok) {
-                if constexpr (L == NHWC) wv = wgt[((size_t)co * 9 + tap) * a.C_in + ci];
-                else                     wv = wgt[((size_t)co * a.C_in + ci) * 9 + tap];
-            }
-            *reinterpret_cast<T*>(s_w + swz(tap * NT + col, byte >> 4) + (byte & 15)) = wv;
+            if (ok) wv = wgt[((size_t)co * 9 + tap) * a.C_in + ci];
+            *reinterpret_cast<T*>(s_w + swz(tap * nt + col, byte >> 4) + (byte & 15)) = wv;
         }
     }
 }
 
-template <typename T, int L, int SRC, int DST, bool VEC>
+// How a call's tensors are staged: 16-byte vectors (channels-last), element by
+// element (channels-last), along x (NCHW).  What goes through registers a
+// chunk ahead: request() asks for chunk kc's weights and first inputs,
+// stage() writes them to LDS and stages the other inputs.
+enum Stage { ST_VEC = 0, ST_SCALAR = 1, ST_PLANE = 2 };
+
+template <typename T, int STG>
+struct Stager;
+template <typename T>
+struct Stager<T, ST_VEC> {
+    VecW<T> w;
+    VecIn<T> in;
+    __device__ __forceinline__ void weights(const ConvArgs& a, int co0, int nt, int kc) { w.issue(a, co0, nt, kc); }
+    __device__ __forceinline__ void inputs(const unsigned long long* s_desc, const Strides<T>& st, int C_in, int in_px,
+                                           int kc) {
+        in.issue(s_desc, st, C_in, in_px, 0, kc);
+    }
+    template <bool FIRST>
+    __device__ __forceinline__ void stage(const ConvArgs& a, int, int nt, int kc, const unsigned long long* s_desc,
+                                          const Strides<T>& st, int in_px, unsigned char* s_in, unsigned char* s_w) {
+        if constexpr (FIRST) {  // nothing has run yet: the first averages' loads join the others in flight
+            typename VecIn<T>::Rest q;
+            in.rest(q, 0, s_desc, st, a.C_in, in_px, 0, kc);
+            w.commit(s_w, nt);
+            in.finish(q, 0, in_px, 0, s_in);
+        } else {
+            w.commit(s_w, nt);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        in.commit(FIRST ? UA : 0, s_desc, st, a.C_in, in_px, 0, kc, s_in);
+        for (int base = WG * UI; base < in_px * 4; base += WG * UI) {
+            in.issue(s_desc, st, a.C_in, in_px, base, kc);
+            in.commit(0, s_desc, st, a.C_in, in_px, base, kc, s_in);
+        }
+    }
+};
+template <typename T>
+struct Stager<T, ST_PLANE> {
+    PlaneW<T> w;
+    PlaneIn<T> in;
+    __device__ __forceinline__ void weights(const ConvArgs& a, int co0, int nt, int kc) { w.issue(a, co0, nt, kc); }
+    __device__ __forceinline__ void inputs(const unsigned long long* s_desc, const Strides<T>& st, int C_in, int in_px,
+                                           int kc) {
+        in.issue(s_desc, st, C_in, in_px, 0, kc);
+    }
+    template <bool FIRST>
+    __device__ __forceinline__ void stage(const ConvArgs& a, int, int nt, int kc, const unsigned long long* s_desc,
+                                          const Strides<T>& st, int in_px, unsigned char* s_in, unsigned char* s_w) {
+        w.commit(s_w, nt);
+        __builtin_amdgcn_sched_barrier(0);
+        in.commit(s_desc, st, a.C_in, in_px, 0, kc, s_in);
+        for (int base = WG; base < in_px; base += WG) {
+            in.issue(s_desc, st, a.C_in, in_px, base, kc);
+            in.commit(s_desc, st, a.C_in, in_px, base, kc, s_in);
+        }
+    }
+};
+template <typename T>
+struct Stager<T, ST_SCALAR> {
+    __device__ __forceinline__ void weights(const ConvArgs&, int, int, int) {}
+    __device__ __forceinline__ void inputs(const unsigned long long*, const Strides<T>&, int, int, int) {}
+    template <bool FIRST>
+    __device__ __forceinline__ void stage(const ConvArgs& a, int co0, int nt, int kc, const unsigned long long* s_desc,
+                                          const Strides<T>& st, int in_px, unsigned char* s_in, unsigned char* s_w) {
+        stage_w_scalar<T>(a, co0, nt, kc, s_w);
+        stage_in_scalar<T>(s_desc, st, a.C_in, in_px, kc, s_in);
+    }
+};
+
+// The nine taps of one staged chunk, NS channel sub-tiles by nms <= MS pixel sub-tiles.
+template <typename T, int NS, int MS>
+__device__ __forceinline__ void chunk_mfma(floatx4 (&acc)[MS][4], const unsigned char* wlane, const unsigned char* s_in,
+                                           const int (&pbase)[MS], int pe, int kg, int nt, int nms) {
+#pragma unroll 1
+    for (int tap = 0; tap < 9; ++tap) {
+        const int toff = (tap / 3) * pe + (tap % 3);
+        uint4 wf[NS], pf[MS];
+#pragma unroll
+        for (int ns = 0; ns < NS; ++ns) wf[ns] = *reinterpret_cast<const uint4*>(wlane + (tap * nt + ns * 16) * ROWB);
+#pragma unroll
+        for (int ms = 0; ms < MS; ++ms)
+            if (ms < nms) pf[ms] = *reinterpret_cast<const uint4*>(s_in + swz(pbase[ms] + toff, kg));
+#pragma unroll
+        for (int ms = 0; ms < MS; ++ms)
+            if (ms < nms) {
+#pragma unroll
+                for (int i = 0; i < MF<T>::STEPS; ++i)
+#pragma unroll
+                    for (int ns = 0; ns < NS; ++ns) acc[ms][ns] = MF<T>::mma(wf[ns], pf[ms], i, acc[ms][ns]);
+            }
+    }
+}
+
+template <typename T, int L, int SRC, int DST, int STG, int MS>
 __global__ __launch_bounds__(WG, 2) void k_conv(Geo g, const uint8_t* __restrict__ mask, ConvArgs a, int Rh,
-                                                int Rl, int G, int w_off, int vec_out) {
+                                                int Rl, int G, int w_off, int d_off, int nt, int vec_out) {
     extern __shared__ __align__(16) unsigned char smem[];
-    typedef MF<T> mf;
     constexpr int KC = ROWB / (int)sizeof(T);  // channels per K chunk
     constexpr bool NEED_SLOTS = !(SRC == SRC_DENSE && DST == DST_DENSE);
 
+    unsigned char* s_in = smem;
+    unsigned char* s_w = smem + w_off;
+    unsigned long long* s_desc = reinterpret_cast<unsigned long long*>(smem + d_off);
     const int k = (int)blockIdx.x / G;
     const int grp = (int)blockIdx.x - k * G;
-    const int co0 = blockIdx.y * NT;
+    const int co0 = blockIdx.y * nt;
+    const int nsn = (min(nt, a.C_out - co0) + 15) >> 4;  // 16-channel sub-tiles that hold channels
     Tile t;
     {
         const int per = g.GH * g.GW;
@@ -246,99 +549,62 @@ __global__ __launch_bounds__(WG, 2) void k_conv(Geo g, const uint8_t* __restrict
     t.M = t.rows * t.e;
     t.pe = t.e + 2;
     t.in_px = (t.rows + 2) * t.pe;
-
-    unsigned char* s_in = smem;
-    unsigned char* s_w = smem + w_off;
+    const Strides<T> st = make_strides<T, L, SRC>(g, a, t);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, kg = lane >> 4;
 
+    // -- chunk 0's weights, and the tile's source descriptors
+    Stager<T, STG> sg;
+    sg.weights(a, co0, nt, 0);
+    for (int p = tid; p < t.in_px; p += WG) {
+        const Src<T> s = tile_src<T, L, SRC>(g, a, nb, t, p);
+        unsigned long long d = 0;
+        if (s.p)
+            d = ((reinterpret_cast<unsigned long long>(s.p) - reinterpret_cast<unsigned long long>(st.hi)) & SD_OFF) |
+                SD_SOME | (s.avg ? SD_AVG : 0ull) | (s.low ? SD_LOW : 0ull);
+        s_desc[p] = d;
+    }
+    __syncthreads();
+
     const int nst = (t.M + 15) >> 4;  // 16-pixel sub-tiles
-    int pbase[4];
+    const int nms = __builtin_amdgcn_readfirstlane((nst - wave + 3) >> 2);  // this wave's (wave, wave + 4, ...)
+    int pbase[MS];
 #pragma unroll
-    for (int ms = 0; ms < 4; ++ms) {
+    for (int ms = 0; ms < MS; ++ms) {
         const int m = min((wave + 4 * ms) * 16 + l16, t.M - 1);
         const int i = m / t.e, j = m - i * t.e;
         pbase[ms] = i * t.pe + j;
     }
     const int nchunks = (a.C_in + KC - 1) / KC;
-    const int in_items = t.in_px * 4;
-    constexpr int UI = Batches<SRC>::UI, UP = Batches<SRC>::UP;
 
-    // -- chunk 0
-    if constexpr (VEC) {
-        {
-            WBatch<T> wb;
-            InBatch<T, L, SRC, UI> ib;
-            wb.issue(a, co0, 0);
-            ib.issue(g, a, nb, t, 0, 0);
-            wb.commit(s_w);
-            ib.commit(s_in, t, 0);
-        }
-        for (int base = WG * UI; base < in_items; base += WG * UI) {
-            InBatch<T, L, SRC, UI> ib;
-            ib.issue(g, a, nb, t, base, 0);
-            ib.commit(s_in, t, base);
-        }
-    } else {
-        stage_scalar<T, L, SRC>(g, a, nb, t, co0, 0, s_in, s_w);
-    }
+    sg.inputs(s_desc, st, a.C_in, t.in_px, 0);
+    sg.template stage<true>(a, co0, nt, 0, s_desc, st, t.in_px, s_in, s_w);
     __syncthreads();
 
-    floatx4 acc[4][4];
+    floatx4 acc[MS][4];
 #pragma unroll
-    for (int ms = 0; ms < 4; ++ms)
+    for (int ms = 0; ms < MS; ++ms)
 #pragma unroll
         for (int ns = 0; ns < 4; ++ns) acc[ms][ns] = floatx4{0.f, 0.f, 0.f, 0.f};
+    const unsigned char* wlane = s_w + swz(l16, kg);  // (nt is a multiple of 16: the swizzle of a row is its l16's)
 
     for (int kc = 0; kc < nchunks; ++kc) {
         const bool more = kc + 1 < nchunks;
         // -- prefetch the next chunk's weights and first input batch
-        WBatch<T> wb;
-        InBatch<T, L, SRC, (UP > 0 ? UP : 1)> ib;
-        if constexpr (VEC) {
-            if (more) {
-                wb.issue(a, co0, kc + 1);
-                if constexpr (UP > 0) ib.issue(g, a, nb, t, 0, kc + 1);
-            }
+        if (more) {
+            sg.weights(a, co0, nt, kc + 1);
+            sg.inputs(s_desc, st, a.C_in, t.in_px, kc + 1);
         }
         // -- MFMA over the 9 taps of this chunk
-#pragma unroll 1
-        for (int tap = 0; tap < 9; ++tap) {
-            const int toff = (tap / 3) * t.pe + (tap % 3);
-#pragma unroll
-            for (int ks = 0; ks < KC / mf::KS; ++ks) {
-                const int byte = (ks * mf::KS + kg * mf::EL) * (int)sizeof(T);
-                typename mf::frag wf[4];
-#pragma unroll
-                for (int ns = 0; ns < 4; ++ns) {
-                    const int row = tap * NT + ns * 16 + l16;
-                    wf[ns] = *reinterpret_cast<const typename mf::frag*>(s_w + swz(row, byte >> 4) + (byte & 15));
-                }
-#pragma unroll
-                for (int ms = 0; ms < 4; ++ms) {
-                    if (wave + 4 * ms < nst) {
-                        const int p = pbase[ms] + toff;
-                        const typename mf::frag pf =
-                            *reinterpret_cast<const typename mf::frag*>(s_in + swz(p, byte >> 4) + (byte & 15));
-#pragma unroll
-                        for (int ns = 0; ns < 4; ++ns) acc[ms][ns] = mf::mma(wf[ns], pf, acc[ms][ns]);
-                    }
-                }
-            }
+        switch (nsn) {
+        case 1: chunk_mfma<T, 1, MS>(acc, wlane, s_in, pbase, t.pe, kg, nt, nms); break;
+        case 2: chunk_mfma<T, 2, MS>(acc, wlane, s_in, pbase, t.pe, kg, nt, nms); break;
+        case 3: chunk_mfma<T, 3, MS>(acc, wlane, s_in, pbase, t.pe, kg, nt, nms); break;
+        default: chunk_mfma<T, 4, MS>(acc, wlane, s_in, pbase, t.pe, kg, nt, nms); break;
         }
         __syncthreads();
         if (more) {
-            if constexpr (VEC) {
-                wb.commit(s_w);
-                if constexpr (UP > 0) ib.commit(s_in, t, 0);
-                for (int base = WG * UP; base < in_items; base += WG * UI) {
-                    InBatch<T, L, SRC, UI> ib2;
-                    ib2.issue(g, a, nb, t, base, kc + 1);
-                    ib2.commit(s_in, t, base);
-                }
-            } else {
-                stage_scalar<T, L, SRC>(g, a, nb, t, co0, kc + 1, s_in, s_w);
-            }
+            sg.template stage<false>(a, co0, nt, kc + 1, s_desc, st, t.in_px, s_in, s_w);
             __syncthreads();
         }
     }
@@ -346,18 +612,19 @@ __global__ __launch_bounds__(WG, 2) void k_conv(Geo g, const uint8_t* __restrict
     // -- epilogue: lane holds channels co0 + ns*16 + kg*4 + {0..3} of pixel (wave + 4*ms)*16 + l16
     const T* __restrict__ bias = (const T*)a.bias;
     const bool relu = (a.flags & 1) != 0;
+    const int co_end = min(co0 + nt, a.C_out);
     float bv[4][4];
 #pragma unroll
     for (int ns = 0; ns < 4; ++ns)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int co = co0 + ns * 16 + kg * 4 + r;
-            bv[ns][r] = (bias && co < a.C_out) ? to_f32(bias[co]) : 0.0f;
+            bv[ns][r] = (bias && co < co_end) ? to_f32(bias[co]) : 0.0f;
         }
     const T* res_base = (const T*)(t.high ? a.res_hi : a.res_lo);
     T* out_base = (T*)((DST == DST_DENSE || t.high) ? a.out_hi : a.out_lo);
 #pragma unroll
-    for (int ms = 0; ms < 4; ++ms) {
+    for (int ms = 0; ms < MS; ++ms) {
         if (wave + 4 * ms >= nst) continue;
         const int m = (wave + 4 * ms) * 16 + l16;
         if (m >= t.M) continue;
@@ -365,11 +632,11 @@ __global__ __launch_bounds__(WG, 2) void k_conv(Geo g, const uint8_t* __restrict
 #pragma unroll
         for (int ns = 0; ns < 4; ++ns) {
             const int co = co0 + ns * 16 + kg * 4;
-            if (co >= a.C_out) continue;
+            if (co >= co_end) continue;
             float f[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) f[r] = acc[ms][ns][r] + bv[ns][r];
-            const bool full = vec_out && co + 4 <= a.C_out;
+            const bool full = vec_out && co + 4 <= co_end;
             if constexpr (DST == DST_PACKED) {
                 // packed stack element (slot, co + r, i, j)
                 size_t off[4];
@@ -386,7 +653,7 @@ __global__ __launch_bounds__(WG, 2) void k_conv(Geo g, const uint8_t* __restrict
                     } else {
 #pragma unroll
                         for (int r = 0; r < 4; ++r)
-                            if (co + r < a.C_out) f[r] += to_f32(res_base[off[r]]);
+                            if (co + r < co_end) f[r] += to_f32(res_base[off[r]]);
                     }
                 }
                 Vec<T, 4> o;
@@ -397,33 +664,42 @@ __global__ __launch_bounds__(WG, 2) void k_conv(Geo g, const uint8_t* __restrict
                 } else {
 #pragma unroll
                     for (int r = 0; r < 4; ++r)
-                        if (co + r < a.C_out) out_base[off[r]] = o.e[r];
+                        if (co + r < co_end) out_base[off[r]] = o.e[r];
                 }
             } else {
                 Vec<T, 4> o;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) o.e[r] = from_f32<T>(relu ? fmaxf(f[r], 0.0f) : f[r]);
                 const int reps = t.high ? 1 : 2;
-                for (int dy = 0; dy < reps; ++dy)
-                    for (int dx = 0; dx < reps; ++dx) {
-                        const int Y = t.gy * g.bs + (t.high ? i : 2 * i + dy);
-                        const int X = t.gx * g.bs + (t.high ? j : 2 * j + dx);
-                        if constexpr (L == NHWC) {
+                for (int dy = 0; dy < reps; ++dy) {
+                    const int Y = t.gy * g.bs + (t.high ? i : 2 * i + dy);
+                    if constexpr (L == NHWC) {
+                        for (int dx = 0; dx < reps; ++dx) {
+                            const int X = t.gx * g.bs + (t.high ? j : 2 * j + dx);
                             T* p = out_base + (((size_t)t.n * g.H + Y) * g.W + X) * a.C_out + co;
                             if (full) {
                                 vstore<T, 4>(p, o);
                             } else {
 #pragma unroll
                                 for (int r = 0; r < 4; ++r)
-                                    if (co + r < a.C_out) p[r] = o.e[r];
+                                    if (co + r < co_end) p[r] = o.e[r];
                             }
-                        } else {
+                        }
+                    } else {
+                        const int X = t.gx * g.bs + (t.high ? j : 2 * j);
 #pragma unroll
-                            for (int r = 0; r < 4; ++r)
-                                if (co + r < a.C_out)
-                                    out_base[(((size_t)t.n * a.C_out + co + r) * g.H + Y) * g.W + X] = o.e[r];
+                        for (int r = 0; r < 4; ++r) {
+                            if (co + r >= co_end) continue;
+                            T* p = out_base + (((size_t)t.n * a.C_out + co + r) * g.H + Y) * g.W + X;
+                            if (t.high) {
+                                *p = o.e[r];
+                            } else {  // both pixels of the cell's row in one store
+                                const T two[2] = {o.e[r], o.e[r]};
+                                __builtin_memcpy(p, two, sizeof(two));
+                            }
                         }
                     }
+                }
             }
         }
     }
@@ -432,23 +708,61 @@ __global__ __launch_bounds__(WG, 2) void k_conv(Geo g, const uint8_t* __restrict
 inline int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 inline bool aligned(const void* p, int bytes) { return (reinterpret_cast<uintptr_t>(p) & (bytes - 1)) == 0; }
 
-template <typename T, int L, int SRC, int DST, bool VEC>
-hipError_t run_conv(const Geo& g, const uint8_t* mask, const ConvArgs& a, hipStream_t st) {
+// Rows per tile and output channels per workgroup.  About 256 pixels a tile
+// read the fewest halo pixels and weights; 128 or 64 where that many smaller
+// tiles still find a place at once (two workgroups a CU), so that more of the
+// chip works.  Measured, 256 / 128 / 64 pixels a tile: one 128x256 map of 96
+// channels, 16-pixel blocks, fp16 (256 / 512 / 1024 workgroups) 30 / 26 / 48
+// us; the 256x512 fp32 layer of 64 channels, 32-pixel blocks (512 / 1024 / 2048)
+// 112 / 141 / 144 us.  The channel tiles of a call are equal, so that 72
+// channels are 48 + 24 and not 64 + 8.
+struct ConvPlan {
+    int Rh, Rl, G, nt, ny, M;
+};
+inline ConvPlan conv_plan(const Geo& g, const ConvArgs& a, bool dense) {
+    ConvPlan p{};
     const int eh = g.bs, el = g.bs / 2;
-    const int Rh = clampi(MT / eh, 1, eh), Rl = clampi(MT / el, 1, el);
-    const int G = (((eh + Rh - 1) / Rh) > ((el + Rl - 1) / Rl)) ? (eh + Rh - 1) / Rh : (el + Rl - 1) / Rl;
-    const int in_px = ((Rh + 2) * (eh + 2) > (Rl + 2) * (el + 2)) ? (Rh + 2) * (eh + 2) : (Rl + 2) * (el + 2);
-    const int w_off = in_px * ROWB;
-    const int smem = w_off + W_BYTES;
+    p.ny = (a.C_out + NT - 1) / NT;
+    p.nt = ((a.C_out + p.ny - 1) / p.ny + 15) / 16 * 16;
+    p.ny = (a.C_out + p.nt - 1) / p.nt;
+    // (dense: the class counts are on the device; every block high is the most work)
+    const long long nh = dense ? g.B : std::min<long long>(a.hi_cap, g.B);
+    const long long nl = dense ? 0 : std::min<long long>(a.lo_cap, g.B);
+    for (int mt = 256; mt >= 64; mt /= 2) {
+        int Rh = clampi(mt / eh, 1, eh), Rl = clampi(mt / el, 1, el);
+        const int Gh = (eh + Rh - 1) / Rh, Gl = (el + Rl - 1) / Rl;
+        Rh = (eh + Gh - 1) / Gh;  // equal tiles
+        Rl = (el + Gl - 1) / Gl;
+        if (mt < 256 && (nh * Gh + nl * Gl) * p.ny > 2LL * device_cus()) break;
+        p.Rh = Rh;
+        p.Rl = Rl;
+        p.G = std::max(Gh, Gl);
+        p.M = std::max(Rh * eh, Rl * el);
+    }
+    return p;
+}
+
+template <typename T, int L, int SRC, int DST, int STG, int MS>
+hipError_t run_conv_ms(const Geo& g, const uint8_t* mask, const ConvArgs& a, const ConvPlan& p, hipStream_t st) {
+    const int eh = g.bs, el = g.bs / 2;
+    const int in_px = std::max((p.Rh + 2) * (eh + 2), (p.Rl + 2) * (el + 2));
+    const int w_off = in_px * ROWB, d_off = w_off + 9 * p.nt * ROWB, smem = d_off + in_px * 8;
     const int ob = 4 * (int)sizeof(T);  // one epilogue vector: 4 channels
     const int vec_out = (a.C_out % 4 == 0) && aligned(a.out_hi, ob) && aligned(a.out_lo, ob) &&
                         aligned(a.res_hi, ob) && aligned(a.res_lo, ob);
-    hipError_t e = ensure_dyn_lds((const void*)k_conv<T, L, SRC, DST, VEC>, smem);
+    hipError_t e = ensure_dyn_lds((const void*)k_conv<T, L, SRC, DST, STG, MS>, smem);
     if (e != hipSuccess) return e;
-    const dim3 grid((unsigned)(g.B * G), (unsigned)((a.C_out + NT - 1) / NT));
-    hipLaunchKernelGGL((k_conv<T, L, SRC, DST, VEC>), grid, dim3(WG), smem, st, g, mask, a, Rh, Rl, G, w_off,
-                       vec_out);
+    const dim3 grid((unsigned)(g.B * p.G), (unsigned)p.ny);
+    hipLaunchKernelGGL((k_conv<T, L, SRC, DST, STG, MS>), grid, dim3(WG), smem, st, g, mask, a, p.Rh, p.Rl, p.G, w_off,
+                       d_off, p.nt, vec_out);
     return hipGetLastError();
+}
+
+template <typename T, int L, int SRC, int DST, int STG>
+hipError_t run_conv(const Geo& g, const uint8_t* mask, const ConvArgs& a, hipStream_t st) {
+    const ConvPlan p = conv_plan(g, a, SRC == SRC_DENSE);
+    if (p.M <= 128) return run_conv_ms<T, L, SRC, DST, STG, 2>(g, mask, a, p, st);
+    return run_conv_ms<T, L, SRC, DST, STG, 4>(g, mask, a, p, st);
 }
 
 template <typename T, int SRC, int DST>
@@ -457,10 +771,10 @@ hipError_t conv_l(int layout, const Geo& g, const uint8_t* mask, const ConvArgs&
     if (layout == NHWC) {
         const bool vec = (a.C_in % VQ == 0) && aligned(a.in_hi, 16) && aligned(a.in_lo, 16) &&
                          aligned(a.weight, 16);
-        if (vec) return run_conv<T, NHWC, SRC, DST, true>(g, mask, a, st);
-        return run_conv<T, NHWC, SRC, DST, false>(g, mask, a, st);
+        if (vec) return run_conv<T, NHWC, SRC, DST, ST_VEC>(g, mask, a, st);
+        return run_conv<T, NHWC, SRC, DST, ST_SCALAR>(g, mask, a, st);
     }
-    return run_conv<T, NCHW, SRC, DST, false>(g, mask, a, st);
+    return run_conv<T, NCHW, SRC, DST, ST_PLANE>(g, mask, a, st);
 }
 
 template <typename T>

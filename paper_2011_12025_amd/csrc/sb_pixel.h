@@ -17,19 +17,20 @@ struct Src {
     const T* p;  // nullptr -> zero
     int avg;     // 1 -> average of the 2x2 cell at p
     int d1, d2;  // element offsets of the right and of the lower pixel of the cell
+    int low;     // 1 -> p lies in the low stack
 };
 
 template <typename T>
 __device__ __forceinline__ Src<T> src_zero() {
-    return Src<T>{nullptr, 0, 0, 0};
+    return Src<T>{nullptr, 0, 0, 0, 0};
 }
 template <typename T>
-__device__ __forceinline__ Src<T> src_copy(const T* p) {
-    return Src<T>{p, 0, 0, 0};
+__device__ __forceinline__ Src<T> src_copy(const T* p, int low = 0) {
+    return Src<T>{p, 0, 0, 0, low};
 }
 template <typename T>
 __device__ __forceinline__ Src<T> src_avg(const T* p, int d1, int d2) {
-    return Src<T>{p, 1, d1, d2};
+    return Src<T>{p, 1, d1, d2, 0};
 }
 
 // How BlockPad fills a halo (the `pm` argument below): PM_AVG is BlockPad
@@ -75,8 +76,8 @@ __device__ __forceinline__ Src<T> packed_src(const T* __restrict__ hi, const T* 
     const int ns = neigh_slot(nb, d);
     if (ns >= (nhigh ? hi_cap : lo_cap)) return src_zero<T>();
     const int u2 = uu - dy * e, v2 = vv - dx * e;
-    if (nhigh == own_high) return src_copy<T>(stack_at<T, L>(nhigh ? hi : lo, ns, C, e, u2, v2, c));
-    if (own_high) return src_copy<T>(stack_at<T, L>(lo, ns, C, lb, u2 >> 1, v2 >> 1, c));
+    if (nhigh == own_high) return src_copy<T>(stack_at<T, L>(nhigh ? hi : lo, ns, C, e, u2, v2, c), !nhigh);
+    if (own_high) return src_copy<T>(stack_at<T, L>(lo, ns, C, lb, u2 >> 1, v2 >> 1, c), 1);
     const int px = (L == NHWC) ? C : 1;
     if (pm == PM_STRIDED) return src_copy<T>(stack_at<T, L>(hi, ns, C, bs, 2 * u2, 2 * v2, c));
     return src_avg<T>(stack_at<T, L>(hi, ns, C, bs, 2 * u2, 2 * v2, c), px, px * bs);
