@@ -364,10 +364,16 @@ __global__ __launch_bounds__(WG) void k_wgrad(const T* __restrict__ hp, const T*
 // thread (i, group) adds chunks 16 group .. 16 group + 15 of element i in
 // order and leaves the sum in chunk 16 group (read by no other thread).
 constexpr int WR_GROUP = 16;
-__global__ __launch_bounds__(WG) void k_wgrad_group(float* __restrict__ part, int chunks, int total) {
-    const long long gid = (long long)blockIdx.x * WG + threadIdx.x;
+__global__ __launch_bounds__(WG) void k_wgrad_group(float* __restrict__ part, float* __restrict__ part_b, int chunks,
+                                                    int total, int total_b) {
+    long long gid = (long long)blockIdx.x * WG + threadIdx.x;
     const int groups = (chunks + WR_GROUP - 1) / WR_GROUP;
-    if (gid >= (long long)total * groups) return;
+    if (gid >= (long long)total * groups) {  // the bias sums (total_b of them, after the weights')
+        gid -= (long long)total * groups;
+        if (!part_b || gid >= (long long)total_b * groups) return;
+        part = part_b;
+        total = total_b;
+    }
     const int grp = (int)(gid / total), i = (int)(gid - (long long)grp * total);
     const int q0 = grp * WR_GROUP, q1 = min(chunks, q0 + WR_GROUP);
     float v[WR_GROUP];
@@ -389,29 +395,30 @@ __global__ __launch_bounds__(WG) void k_wgrad_reduce(const float* __restrict__ p
                                                      T* __restrict__ db) {
     const int total = C_out * 9 * C_in;
     const int i = (int)(blockIdx.x * WG + threadIdx.x);
-    if (i < total) {
+    // in order, sixteen loads in flight at a time
+    auto sum = [&](const float* p, int n, int k) {
         float s = 0.0f;
-        for (int q = 0; q < chunks; q += gstride) s += part[(size_t)q * total + i];
+        for (int q = 0; q < chunks; q += 16 * gstride) {
+            float v[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) v[u] = q + u * gstride < chunks ? p[(size_t)(q + u * gstride) * n + k] : 0.0f;
+#pragma unroll
+            for (int u = 0; u < 16; ++u)
+                if (q + u * gstride < chunks) s += v[u];
+        }
+        return s;
+    };
+    if (i < total) {
+        const float s = sum(part, total, i);
         const int ci = i % C_in, t = (i / C_in) % 9, co = i / (9 * C_in);
         size_t o;
         if constexpr (L == NHWC) o = i;  // [Cout][3][3][Cin]
         else                     o = ((size_t)co * C_in + ci) * 9 + t;
         dw[o] = from_f32<T>(s);
     }
-    if (db && i < C_out) {
-        // in chunk order, sixteen loads in flight at a time
-        float s = 0.0f;
-        int q = 0;
-        for (; q + 16 <= chunks; q += 16) {
-            float v[16];
-#pragma unroll
-            for (int u = 0; u < 16; ++u) v[u] = part_b[(size_t)(q + u) * C_out + i];
-#pragma unroll
-            for (int u = 0; u < 16; ++u) s += v[u];
-        }
-        for (; q < chunks; ++q) s += part_b[(size_t)q * C_out + i];
-        db[i] = from_f32<T>(s);
-    }
+    // the bias sums in the last workgroup's place, so that no thread does both
+    const int b = i - (total + WG - 1) / WG * WG;
+    if (db && b >= 0 && b < C_out) db[b] = from_f32<T>(sum(part_b, C_out, b));
 }
 
 typedef float floatx4_t __attribute__((ext_vector_type(4)));
@@ -658,37 +665,14 @@ __global__ __launch_bounds__(WM_THREADS, 1) void k_wgrad_mfma(const T* __restric
 inline size_t r256(size_t b) { return (b + 255) / 256 * 256; }
 inline int esz(int dtype) { return dtype == 0 ? 4 : 2; }
 
-// The data gradient of each stack as a convolution of its own (the classes
-// do not mix: the padded blocks are independent).  On the implicit GEMM:
-// the output gradient padded by one zero (extent e + 2) taken as a stack of
-// blocks of that extent, every block high, zero-padded on its own
-// (SB_FLAG_PAD_ZERO), transposed-rotated weights: a "same" convolution whose
-// output is the padded block's gradient.  Otherwise the general kernel runs
-// a valid convolution over the gradient padded by two.
-struct DgradCall {
-    Geo g;
-    ConvArgs a;
-};
-DgradCall dgrad_call(const Geo& g, int e, int cap, int C_in, int C_out) {
-    DgradCall d;
-    d.g = g;
-    d.g.N = 1;
-    d.g.C = C_out;
-    d.g.bs = e + 2;
-    d.g.GH = 1;
-    d.g.GW = cap;
-    d.g.B = cap;
-    d.g.H = e + 2;
-    d.g.W = cap * (e + 2);
-    d.a = ConvArgs{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, C_out, C_in,
-                   PM_ZERO << 1, cap, 0};  // zero padding of each block on its own
-    return d;
-}
-bool dgrad_igemm_shape(int dtype, int layout, const Geo& g, int C_in, int C_out, int hi_cap, int lo_cap) {
-    if (g.bs % 4) return false;  // even extents e + 2 for both classes
-    const DgradCall h = dgrad_call(g, g.bs, hi_cap, C_in, C_out), l = dgrad_call(g, g.bs / 2, lo_cap, C_in, C_out);
-    return (hi_cap == 0 || igemm_fits_shape(dtype, layout, h.g, h.a)) &&
-           (lo_cap == 0 || igemm_fits_shape(dtype, layout, l.g, l.a));
+// The data gradient is the full convolution of each block's output gradient
+// with the transposed, rotated filters (the classes do not mix: the padded
+// blocks are independent).  On the implicit GEMM it is one launch over both
+// stacks as they are; otherwise the general kernel runs a valid convolution
+// over the gradients padded by two zeros.
+ConvArgs dgrad_args(int C_in, int C_out, int hi_cap, int lo_cap) {
+    return ConvArgs{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, C_out, C_in,
+                    PM_ZERO << 1, hi_cap, lo_cap};
 }
 
 struct DgradLayout {
@@ -703,13 +687,12 @@ DgradLayout dgrad_layout(int dtype, int layout, const Geo& g, int C_in, int C_ou
     D.ql = r256((size_t)lo_cap * C_out * (lb + 4) * (lb + 4) * es);
     D.wt = r256((size_t)C_in * C_out * 9 * es);
     D.masks = r256((size_t)std::max<long long>({g.B, (long long)hi_cap, (long long)lo_cap}) * 2);
-    D.ig = 0;
-    D.ig_shape = dgrad_igemm_shape(dtype, layout, g, C_in, C_out, hi_cap, lo_cap);
-    if (D.ig_shape) {
-        const DgradCall h = dgrad_call(g, g.bs, hi_cap, C_in, C_out), l = dgrad_call(g, (int)lb, lo_cap, C_in, C_out);
-        D.ig = r256(std::max(hi_cap ? igemm_ws_bytes(h.g, h.a, 3, 1) : 0, lo_cap ? igemm_ws_bytes(l.g, l.a, 3, 1) : 0));
-    }
-    D.total = D.qh + D.ql + D.wt + D.masks + D.ig;
+    const ConvArgs a = dgrad_args(C_in, C_out, hi_cap, lo_cap);
+    D.ig_shape = igemm_full_fits_shape(dtype, layout, g, a);
+    D.ig = D.ig_shape ? r256(igemm_full_ws_bytes(g, a)) : 0;
+    // either route in one workspace: [filters][GEMM], or [padded gradients][filters][masks] where
+    // less aligned buffers take the general kernel
+    D.total = std::max(D.wt + D.ig, D.qh + D.ql + D.wt + D.masks);
     return D;
 }
 
@@ -783,41 +766,35 @@ hipError_t pad_bwd_t(int layout, const Geo& g, const void* dhp, const void* dlp,
 template <typename T, int L>
 hipError_t dgrad_t(const Geo& g, const void* dho, const void* dlo, const uint8_t* mask, const void* w, int C_in,
                    int C_out, void* dhp, void* dlp, int hi_cap, int lo_cap, Ws ws, hipStream_t st) {
-    (void)mask;
     constexpr int dt = sizeof(T) == 4 ? 0 : (std::is_same<T, f16>::value ? 1 : 2);
     const DgradLayout D = dgrad_layout(dt, L, g, C_in, C_out, hi_cap, lo_cap);
     if (ws.bytes < D.total || !ws.p) return hipErrorInvalidValue;
     char* base = (char*)ws.p;
+    const int grid = device_cus() * 4;
+    hipError_t e;
+    ConvArgs ga = dgrad_args(C_in, C_out, hi_cap, lo_cap);
+    ga.in_hi = dho;
+    ga.in_lo = dlo;
+    ga.weight = base;
+    ga.out_hi = dhp;
+    ga.out_lo = dlp;
+    if (D.ig_shape && igemm_fits(dt, L, g, ga)) {
+        const int total = C_in * C_out * 9;
+        hipLaunchKernelGGL((k_dgrad_prep<T, L>), dim3((unsigned)std::min<long long>(grid, (total + WG - 1) / WG)), dim3(WG),
+                           0, st, (const T*)w, C_out, C_in, (T*)base, nullptr, nullptr, 0LL, (const T*)nullptr, 0,
+                           (T*)nullptr, (const T*)nullptr, 0, (T*)nullptr, g.bs, 0);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        return launch_igemm_full(dt, g, mask, ga, Ws{base + D.wt, D.ig}, st);
+    }
     T* qh = (T*)base;
     T* ql = (T*)(base + D.qh);
     T* wt = (T*)(base + D.qh + D.ql);
     uint8_t* ones = (uint8_t*)(base + D.qh + D.ql + D.wt);
     const long long nm = std::max<long long>({g.B, (long long)hi_cap, (long long)lo_cap});
     uint8_t* zeros = ones + nm;
-    void* igws = base + D.qh + D.ql + D.wt + D.masks;
-    const int lb = g.bs / 2;
-    const int grid = device_cus() * 4;
-    hipError_t e;
-    // the implicit GEMM when both calls take it (shapes and alignment)
-    DgradCall h = dgrad_call(g, g.bs, hi_cap, C_in, C_out), l = dgrad_call(g, lb, lo_cap, C_in, C_out);
-    h.a.in_hi = qh;
-    h.a.weight = wt;
-    h.a.out_hi = dhp;
-    l.a.in_hi = ql;
-    l.a.weight = wt;
-    l.a.out_hi = dlp;
-    const bool ig = D.ig_shape && (hi_cap == 0 || igemm_fits(dt, L, h.g, h.a)) &&
-                    (lo_cap == 0 || igemm_fits(dt, L, l.g, l.a));
-    const int pad = ig ? 1 : 2;
     hipLaunchKernelGGL((k_dgrad_prep<T, L>), dim3(grid), dim3(WG), 0, st, (const T*)w, C_out, C_in, wt, ones, zeros,
-                       nm, (const T*)dho, hi_cap, qh, (const T*)dlo, lo_cap, ql, g.bs, pad);
+                       nm, (const T*)dho, hi_cap, qh, (const T*)dlo, lo_cap, ql, g.bs, 2);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (ig) {
-        const Ws w2{igws, D.ig};
-        if (hi_cap > 0 && (e = launch_igemm(dt, h.g, ones, h.a, 3, 1, w2, st)) != hipSuccess) return e;
-        if (lo_cap > 0 && (e = launch_igemm(dt, l.g, ones, l.a, 3, 1, w2, st)) != hipSuccess) return e;
-        return hipSuccess;
-    }
     // the high stack: every block of the grid taken as high, extent bs + 2 (the padded gradient)
     if (hi_cap > 0) {
         Geo gh = g;
@@ -869,12 +846,12 @@ hipError_t wgrad_t(const Geo& g, const void* hp, const void* lp, const void* dho
     const int total = C_out * 9 * C_in;
     int gstride = 1;
     if (p.chunks > 2 * WR_GROUP) {
-        const long long threads = (long long)total * ((p.chunks + WR_GROUP - 1) / WR_GROUP);
-        hipLaunchKernelGGL(k_wgrad_group, dim3((unsigned)((threads + WG - 1) / WG)), dim3(WG), 0, st, part, p.chunks,
-                           total);
+        const long long threads = (long long)(total + C_out) * ((p.chunks + WR_GROUP - 1) / WR_GROUP);
+        hipLaunchKernelGGL(k_wgrad_group, dim3((unsigned)((threads + WG - 1) / WG)), dim3(WG), 0, st, part, part_b,
+                           p.chunks, total, C_out);
         gstride = WR_GROUP;
     }
-    hipLaunchKernelGGL((k_wgrad_reduce<T, L>), dim3((unsigned)((total + WG - 1) / WG)), dim3(WG), 0, st,
+    hipLaunchKernelGGL((k_wgrad_reduce<T, L>), dim3((unsigned)((total + WG - 1) / WG + (C_out + WG - 1) / WG)), dim3(WG), 0, st,
                        (const float*)part, (const float*)part_b, p.chunks, gstride, C_in, C_out, (T*)dw, (T*)db);
     return hipGetLastError();
 }

@@ -194,6 +194,8 @@ struct GParams {
     int W;          // dense mode: width of the map
     int* dout;      // per M tile, TM dense output pixels (-1: none), written when splits > 1
     int hs_lg;      // log2 of the high output extent when the epilogue writes a.out_hs, else -1
+    int org;        // tap (ky, kx) of output pixel (i, j) is input pixel (ST i + ky - org, ST j + kx - org): the
+                    // filter's radius, or KS - 1 for the full convolution of blocks padded with zeros on their own
 };
 
 // The store of 8 finished channels of one output pixel: row m of the class's
@@ -556,7 +558,7 @@ __global__ __launch_bounds__(GWG, 1) void k_igemm(Geo g, const uint8_t* __restri
         const int idx = tid + it * GWG, t = idx - (idx / KT) * KT;
         const int pij = pijv[it];
         const int b = pij >> 22, i = (pij >> 11) & 2047, j = pij & 2047;
-        const int uu = ST * i + t / KS - KS / 2, vv = ST * j + (t - (t / KS) * KS) - KS / 2;
+        const int uu = ST * i + t / KS - gp.org, vv = ST * j + (t - (t / KS) * KS) - gp.org;
         const int dy = uu < 0 ? -1 : (uu >= e_in ? 1 : 0);
         const int dx = vv < 0 ? -1 : (vv >= e_in ? 1 : 0);
         nbv[it] = (pij >= 0 && !lpad) ? s_nb[b * 9 + (dy + 1) * 3 + dx + 1] : gdesc(GK_ZERO, 0);
@@ -571,7 +573,7 @@ __global__ __launch_bounds__(GWG, 1) void k_igemm(Geo g, const uint8_t* __restri
         if (pij >= 0) {
             const int b = pij >> 22, i = (pij >> 11) & 2047, j = pij & 2047;
             const int ky = t / KS, kx = t - (t / KS) * KS;
-            const int uu = ST * i + ky - KS / 2, vv = ST * j + kx - KS / 2;
+            const int uu = ST * i + ky - gp.org, vv = ST * j + kx - gp.org;
             if (lpad) {  // a low tile over the padded low stack: every source is a copy
                 ds = gdesc(GK_LO, ((slot0 + b) * (lb + 2) + uu + 1) * (lb + 2) + vv + 1);
             } else {
@@ -846,9 +848,11 @@ struct IgPlan {
     size_t part_bytes, pad_bytes;
 };
 
-IgPlan igemm_plan(const Geo& g, const ConvArgs& a, int ks, int stride, bool dense = false) {
+// full: the full convolution of every block on its own (outputs ks - 1 pixels wider).
+IgPlan igemm_plan(const Geo& g, const ConvArgs& a, int ks, int stride, bool dense = false, bool full = false) {
     IgPlan p;
-    const int eo_h = g.bs / stride, eo_l = (g.bs / 2) / stride;
+    const int wider = full ? ks - 1 : 0;
+    const int eo_h = g.bs / stride + wider, eo_l = (g.bs / 2) / stride + wider;
     auto tiles_of = [&](int TM, long long nh, long long nl) {
         return (nh * eo_h * eo_h + TM - 1) / TM + (nl * eo_l * eo_l + TM - 1) / TM;
     };
@@ -929,17 +933,19 @@ IgPlan igemm_plan(const Geo& g, const ConvArgs& a, int ks, int stride, bool dens
 }
 
 template <typename T, int KS, int ST, int WM, int MS, int NS>
-hipError_t igemm_run(const Geo& g, const uint8_t* mask, const ConvArgs& a, Ws ws, hipStream_t st, bool dense) {
+hipError_t igemm_run(const Geo& g, const uint8_t* mask, const ConvArgs& a, Ws ws, hipStream_t st, bool dense,
+                     bool full) {
     constexpr int TM = WM * MS * 16, TN = (GWAVES / WM) * NS * 16;
-    const IgPlan pl = igemm_plan(g, a, KS, ST, dense);
+    const IgPlan pl = igemm_plan(g, a, KS, ST, dense, full);
     if (pl.TM != TM || pl.TN != TN) return hipErrorInvalidValue;
     const int tiles = pl.tiles_h + pl.tiles_l;
     if (tiles == 0) return hipSuccess;
     if (ws.bytes < pl.part_bytes + pl.pad_bytes || (pl.part_bytes + pl.pad_bytes > 0 && !ws.p))
         return hipErrorInvalidValue;  // the entry points check the workspace before anything is launched
     GParams gp;
-    gp.eo_h = g.bs / ST;
-    gp.eo_l = (g.bs / 2) / ST;
+    gp.org = full ? KS - 1 : KS / 2;
+    gp.eo_h = g.bs / ST + (full ? KS - 1 : 0);
+    gp.eo_l = (g.bs / 2) / ST + (full ? KS - 1 : 0);
     gp.cpt = a.C_in / GKC;
     const int smem = igemm_smem_fixed<TM, TN, KS * KS>() + igemm_hb_bytes(g);
     hipError_t e = ensure_dyn_lds((const void*)k_igemm<T, KS, ST, WM, MS, NS>, smem);
@@ -996,13 +1002,13 @@ hipError_t igemm_run(const Geo& g, const uint8_t* mask, const ConvArgs& a, Ws ws
 
 template <typename T, int KS, int ST>
 hipError_t igemm_tile(const Geo& g, const uint8_t* mask, const ConvArgs& a, Ws ws, hipStream_t st,
-                      bool dense = false) {
-    const IgPlan pl = igemm_plan(g, a, KS, ST, dense);
+                      bool dense = false, bool full = false) {
+    const IgPlan pl = igemm_plan(g, a, KS, ST, dense, full);
     const int tn = pl.TN;
-    if (pl.TM == 256) return igemm_run<T, KS, ST, 4, 4, 4>(g, mask, a, ws, st, dense);
-    if (tn == 64) return igemm_run<T, KS, ST, 4, 2, 2>(g, mask, a, ws, st, dense);
-    if (tn == 256) return igemm_run<T, KS, ST, 2, 4, 4>(g, mask, a, ws, st, dense);
-    return igemm_run<T, KS, ST, 2, 4, 2>(g, mask, a, ws, st, dense);
+    if (pl.TM == 256) return igemm_run<T, KS, ST, 4, 4, 4>(g, mask, a, ws, st, dense, full);
+    if (tn == 64) return igemm_run<T, KS, ST, 4, 2, 2>(g, mask, a, ws, st, dense, full);
+    if (tn == 256) return igemm_run<T, KS, ST, 2, 4, 4>(g, mask, a, ws, st, dense, full);
+    return igemm_run<T, KS, ST, 2, 4, 2>(g, mask, a, ws, st, dense, full);
 }
 
 template <typename T>
@@ -1070,6 +1076,24 @@ hipError_t launch_igemm_dense(int dtype, const Geo& g, const uint8_t* mask, cons
     p.hi_cap = p.lo_cap = (int)g.B;
     if (dtype == 1) return igemm_tile<f16, 3, 1>(g, mask, p, ws, st, true);
     return igemm_tile<bf16, 3, 1>(g, mask, p, ws, st, true);
+}
+
+bool igemm_full_fits_shape(int dtype, int layout, const Geo& g, const ConvArgs& a) {
+    // the outputs (two pixels wider) are indexed like stacks of larger blocks
+    Geo w = g;
+    w.bs = g.bs + 2;
+    return pad_mode(a.flags) == PM_ZERO && igemm_fits_shape(dtype, layout, g, a) && igemm_fits_shape(dtype, layout, w, a) &&
+           (long long)a.lo_cap * (g.bs / 2 + 2) * (g.bs / 2 + 2) < (1LL << 30);
+}
+
+size_t igemm_full_ws_bytes(const Geo& g, const ConvArgs& a) {
+    const IgPlan p = igemm_plan(g, a, 3, 1, false, true);
+    return p.part_bytes + p.pad_bytes;
+}
+
+hipError_t launch_igemm_full(int dtype, const Geo& g, const uint8_t* mask, const ConvArgs& a, Ws ws, hipStream_t st) {
+    if (dtype == 1) return igemm_tile<f16, 3, 1>(g, mask, a, ws, st, false, true);
+    return igemm_tile<bf16, 3, 1>(g, mask, a, ws, st, false, true);
 }
 
 }  // namespace sb

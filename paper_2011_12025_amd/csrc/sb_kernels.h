@@ -110,6 +110,12 @@ hipError_t launch_bconv(int dtype, const Geo& g, const uint8_t* mask, const Conv
 bool igemm_dense_fits(int dtype, int layout, const Geo& g, const ConvArgs& a);
 size_t igemm_dense_ws_bytes(const Geo& g, const ConvArgs& a);
 hipError_t launch_igemm_dense(int dtype, const Geo& g, const uint8_t* mask, const ConvArgs& a, Ws ws, hipStream_t st);
+// The full 3x3 convolution of every block on its own (a.flags holds PM_ZERO):
+// stacks of extents bs and bs/2 in, bs + 2 and bs/2 + 2 out, the block padded
+// by two zeros.  igemm_fits checks the pointers as well.
+bool igemm_full_fits_shape(int dtype, int layout, const Geo& g, const ConvArgs& a);
+size_t igemm_full_ws_bytes(const Geo& g, const ConvArgs& a);
+hipError_t launch_igemm_full(int dtype, const Geo& g, const uint8_t* mask, const ConvArgs& a, Ws ws, hipStream_t st);
 int conv2d_lds_bytes(int dtype, int C_in, int K, int S);
 int stem_lds_bytes(int K, int S);
 hipError_t launch_conv2d(int dtype, const void* x, int N, int C_in, int H, int W, const void* w, const void* bias,
