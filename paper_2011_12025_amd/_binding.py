@@ -111,5 +111,14 @@ def check(fn: str, code: int) -> None:
         raise SegBlocksError(fn, code, lib().segblocks_last_error().decode())
 
 
+_fns = {}
+
+
 def call(fn: str, *args) -> None:
-    check(fn, getattr(lib(), fn)(*args))
+    """One library call; pointers are plain integers (or None)."""
+    f = _fns.get(fn)
+    if f is None:
+        f = _fns[fn] = getattr(lib(), fn)
+    code = f(*args)
+    if code:
+        check(fn, code)

@@ -16,6 +16,8 @@ as segblocks_block_conv_ex does; the results are the same bit for bit).
 """
 from __future__ import annotations
 
+import functools
+
 import torch
 
 from . import (block_conv3x3, block_conv3x3_workspace_size, block_conv_chain, block_conv_chain_reads_half,
@@ -25,6 +27,26 @@ from ._binding import SB_NHWC
 
 WIDTHS = (64, 128, 256, 512)
 STRIDES = (1, 2, 2, 2)
+
+
+@functools.lru_cache(maxsize=1024)
+def _stage_workspace(device: int, bs: int, N: int, H: int, W: int, dtype: torch.dtype, nh: int, nl: int) -> int:
+    """BlockEncoder.workspace_bytes for stage-1 blocks of side bs on one device
+    (some thirty queries of shapes alone, asked again only for new counts)."""
+    need, cin = 0, WIDTHS[0]
+    for si, (width, stride) in enumerate(zip(WIDTHS, STRIDES)):
+        for bi in range(2):
+            st = stride if bi == 0 else 1
+            if st == 1:
+                need = max(need, block_conv3x3_workspace_size(dtype, SB_NHWC, N, cin, H, W, bs, width, nh, nl))
+            else:
+                need = max(need, block_conv_ex_workspace_size(dtype, N, cin, H, W, bs, width, 3, st, nh, nl))
+            if st != 1 or cin != width:
+                need = max(need, block_conv_ex_workspace_size(dtype, N, cin, H, W, bs, width, 1, st, nh, nl))
+            bs, H, W = bs // st, H // st, W // st
+            need = max(need, block_conv3x3_workspace_size(dtype, SB_NHWC, N, width, H, W, bs, width, nh, nl))
+            cin = width
+    return need
 
 
 class BlockEncoder:
@@ -55,22 +77,8 @@ class BlockEncoder:
         """Largest workspace any stage convolution needs for an N x 64 x H x W
         stage-1 map with block counts (n_high, n_low); the convolutions run
         one after the other on one stream, so they share one buffer."""
-        nh, nl = counts
-        bs, need = self.image_block // 4, 0
-        cin = WIDTHS[0]
-        for si, (width, stride) in enumerate(zip(WIDTHS, STRIDES)):
-            for bi in range(2):
-                st = stride if bi == 0 else 1
-                if st == 1:
-                    need = max(need, block_conv3x3_workspace_size(dtype, SB_NHWC, N, cin, H, W, bs, width, nh, nl))
-                else:
-                    need = max(need, block_conv_ex_workspace_size(dtype, N, cin, H, W, bs, width, 3, st, nh, nl))
-                if st != 1 or cin != width:
-                    need = max(need, block_conv_ex_workspace_size(dtype, N, cin, H, W, bs, width, 1, st, nh, nl))
-                bs, H, W = bs // st, H // st, W // st
-                need = max(need, block_conv3x3_workspace_size(dtype, SB_NHWC, N, width, H, W, bs, width, nh, nl))
-                cin = width
-        return need
+        device = torch.cuda.current_device() if torch.cuda.is_initialized() else -1
+        return _stage_workspace(device, self.image_block // 4, N, H, W, dtype, *counts)
 
     def stem_blocks(self, x: torch.Tensor, mask: torch.Tensor, counts):
         """The blockwise stem: image blocks -> stacks at stride 4."""
