@@ -75,12 +75,15 @@ __device__ __forceinline__ void stage_filters(const T* __restrict__ w, const T* 
         const int co = co0 + sperm(r);
         v[u] = vzero<T, 8>();
         if (i < CH && co < C_out) {
+            // (both taps' channels are one run: one load each, at any alignment)
             const T* p = w + (((size_t)co * SK + ky) * SK + 2 * kq) * C;
+            T e[2 * C] = {};
+            if (kq < 3) __builtin_memcpy(e, p, 2 * C * sizeof(T));
+            else __builtin_memcpy(e, p, C * sizeof(T));
 #pragma unroll
-            for (int ci = 0; ci < C; ++ci) v[u].e[ci] = p[ci];
-            if (kq < 3) {
-#pragma unroll
-                for (int ci = 0; ci < C; ++ci) v[u].e[4 + ci] = p[C + ci];
+            for (int ci = 0; ci < C; ++ci) {
+                v[u].e[ci] = e[ci];
+                v[u].e[4 + ci] = e[C + ci];
             }
         }
     }
@@ -170,8 +173,8 @@ __device__ __forceinline__ uint4 finish8(const floatx4& a, const floatx4& b, con
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const float f0 = a[i] + bv[i], f1 = b[i] + bv[4 + i];
-        o.e[i] = from_f32<T>(relu ? (f0 > 0.0f ? f0 : 0.0f) : f0);
-        o.e[4 + i] = from_f32<T>(relu ? (f1 > 0.0f ? f1 : 0.0f) : f1);
+        o.e[i] = from_f32<T>(relu ? fmaxf(f0, 0.0f) : f0);
+        o.e[4 + i] = from_f32<T>(relu ? fmaxf(f1, 0.0f) : f1);
     }
     return o.raw;
 }
@@ -203,16 +206,16 @@ __device__ __forceinline__ uint32_t max2(uint32_t a, uint32_t b) {
 
 // One workgroup: 16 x 32 pooled pixels, 64 channels.  Wave (rg, ch) makes
 // pooled rows 4 rg .. 4 rg + 3, columns 16 ch .. 16 ch + 15, from nine stem
-// rows of 32 pixels one after the other; a row's horizontal maxima are taken
-// across lanes (an operand's 16 pixels are one row), the vertical ones as the
-// rows come.  The stem column left of the wave's 32 is one more operand whose
+// rows of 32 pixels one after the other: the vertical maxima are taken as the
+// rows come, then the horizontal ones across lanes (an operand's 16 pixels are
+// one row).  The stem column left of the wave's 32 is one more operand whose
 // 16 "pixels" are that column in the wave's nine rows (28 MFMAs beside 504).
 // Recomputed at tile borders: one row in nine.
 //
 // Bound by MFMA issue (K padded from 147 to 224) and, at one image, by the
 // single round of workgroups, whose start (image tile and filters from
-// memory) nothing overlaps.  1024x2048, 64 channels: 26 us for one image and
-// 96 us for four, where the stem and the pool as two kernels take 51 and 199.
+// memory) nothing overlaps.  1024x2048, 64 channels: 24.5 us for one image and
+// 88 us for four, where the stem and the pool as two kernels take 51 and 199.
 template <typename T, int C>
 __global__ __launch_bounds__(SP_WG, 1) void k_stem_pool(const T* __restrict__ x, int H, int W, const T* __restrict__ w,
                                                         const T* __restrict__ bias, int C_out, T* __restrict__ y,
@@ -275,7 +278,8 @@ __global__ __launch_bounds__(SP_WG, 1) void k_stem_pool(const T* __restrict__ x,
 #pragma unroll
             for (int ns = 0; ns < 4; ++ns) acc[ns] = SMF<T>::mma(wf[ky][ns], bf, acc[ns]);
         }
-        const bool in = oxc0 + 32 * ch > 0 && oxc0 + 32 * ch - 1 < Wo;
+        const int cy = cr0 + lr0 + r;
+        const bool in = oxc0 + 32 * ch > 0 && oxc0 + 32 * ch - 1 < Wo && cy >= 0 && cy < Ho;
 #pragma unroll
         for (int jj = 0; jj < 2; ++jj) {
             edge[jj] = finish8<T>(acc[2 * jj], acc[2 * jj + 1], s_bias + jj * 32 + kg * 8, true);
@@ -283,8 +287,21 @@ __global__ __launch_bounds__(SP_WG, 1) void k_stem_pool(const T* __restrict__ x,
         }
     }
 
-    // horizontal maxima of stem row lr0 + r (even lanes: pooled column l16 / 2 of fragment t), zero outside the map
-    auto row_max = [&](int r, uint4 (&h)[2][2]) {
+    // its maxima over three rows, in the lane of the first
+    uint4 edge3[2];
+#pragma unroll
+    for (int jj = 0; jj < 2; ++jj) {
+        uint32_t e[4] = {edge[jj].x, edge[jj].y, edge[jj].z, edge[jj].w};
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            const uint32_t n1 = row_next(e[d]);
+            e[d] = max2(max2(e[d], n1), row_next(n1));
+        }
+        edge3[jj] = uint4{e[0], e[1], e[2], e[3]};
+    }
+
+    // stem row lr0 + r after bias and ReLU, rounded; zero outside the map
+    auto stem_row = [&](int r, uint4 (&h)[2][2]) {
         const int cy = cr0 + lr0 + r;
         if (cy < 0 || cy >= Ho) {  // uniform
 #pragma unroll
@@ -309,54 +326,55 @@ __global__ __launch_bounds__(SP_WG, 1) void k_stem_pool(const T* __restrict__ x,
 #pragma unroll
                 for (int ns = 0; ns < 4; ++ns) acc[t][ns] = SMF<T>::mma(wf[ky][ns], bf[t], acc[t][ns]);
         }
-        const int src = ((lane & 48) + r) * 4;
 #pragma unroll
-        for (int jj = 0; jj < 2; ++jj) {
-            const uint32_t ed[4] = {edge[jj].x, edge[jj].y, edge[jj].z, edge[jj].w};
-            uint32_t q[2][4];
+        for (int jj = 0; jj < 2; ++jj)
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                uint4 o = finish8<T>(acc[t][2 * jj], acc[t][2 * jj + 1], s_bias + jj * 32 + kg * 8, true);
-                const bool in = oxc0 + 32 * ch + 16 * t + l16 < Wo;
-                q[t][0] = in ? o.x : 0u;
-                q[t][1] = in ? o.y : 0u;
-                q[t][2] = in ? o.z : 0u;
-                q[t][3] = in ? o.w : 0u;
-            }
-            uint32_t m[2][4];
+            for (int t = 0; t < 2; ++t)
+                h[t][jj] = finish8<T>(acc[t][2 * jj], acc[t][2 * jj + 1], s_bias + jj * 32 + kg * 8, true);
+        if (oxc0 + 64 > Wo) {  // (uniform) the tile passes the map's right edge
 #pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                const uint32_t e0 = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)ed[d]);
-                m[0][d] = max2(max2(row_prev(e0, q[0][d]), q[0][d]), row_next(q[0][d]));
-                m[1][d] = max2(max2(row_prev(row_rot1(q[0][d]), q[1][d]), q[1][d]), row_next(q[1][d]));
-            }
+            for (int t = 0; t < 2; ++t)
+                if (oxc0 + 32 * ch + 16 * t + l16 >= Wo) {
 #pragma unroll
-            for (int t = 0; t < 2; ++t) h[t][jj] = uint4{m[t][0], m[t][1], m[t][2], m[t][3]};
+                    for (int jj = 0; jj < 2; ++jj) h[t][jj] = uint4{0u, 0u, 0u, 0u};
+                }
         }
     };
     auto vmax = [](uint4 a, uint4 b) { return uint4{max2(a.x, b.x), max2(a.y, b.y), max2(a.z, b.z), max2(a.w, b.w)}; };
 
+    // three rows to one, then three columns to one (even lanes: pooled column l16 / 2 of fragment t)
     uint4 cur[2][2];
-    row_max(0, cur);
+    stem_row(0, cur);
     for (int q = 0; q < 4; ++q) {
         const int pi = pi0 + (lr0 >> 1) + q;
         if (pi >= Hp) return;  // uniform; no barrier follows
         uint4 h[2][2];
-        row_max(2 * q + 1, h);
+        stem_row(2 * q + 1, h);
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
             for (int jj = 0; jj < 2; ++jj) cur[t][jj] = vmax(cur[t][jj], h[t][jj]);
-        row_max(2 * q + 2, h);
+        stem_row(2 * q + 2, h);
         T* yrow = y + ((size_t)n * Hp + pi) * Wp * C_out;
+        const int src = ((lane & 48) + 2 * q) * 4;
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const int pj = pj0 + 16 * ch + 8 * t + (l16 >> 1);
+        for (int jj = 0; jj < 2; ++jj) {
+            const uint32_t ed[4] = {edge3[jj].x, edge3[jj].y, edge3[jj].z, edge3[jj].w};
+            const uint4 c0 = vmax(cur[0][jj], h[0][jj]), c1 = vmax(cur[1][jj], h[1][jj]);
+            const uint32_t v0[4] = {c0.x, c0.y, c0.z, c0.w}, v1[4] = {c1.x, c1.y, c1.z, c1.w};
+            uint32_t m[2][4];
 #pragma unroll
-            for (int jj = 0; jj < 2; ++jj) {
-                const int co = co0 + jj * 32 + kg * 8;
+            for (int d = 0; d < 4; ++d) {
+                const uint32_t e0 = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)ed[d]);
+                m[0][d] = max2(max2(row_prev(e0, v0[d]), v0[d]), row_next(v0[d]));
+                m[1][d] = max2(max2(row_prev(row_rot1(v0[d]), v1[d]), v1[d]), row_next(v1[d]));
+            }
+            const int co = co0 + jj * 32 + kg * 8;
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const int pj = pj0 + 16 * ch + 8 * t + (l16 >> 1);
                 if ((l16 & 1) == 0 && pj < Wp && co < C_out)
-                    *reinterpret_cast<uint4*>(yrow + (size_t)pj * C_out + co) = vmax(cur[t][jj], h[t][jj]);
+                    *reinterpret_cast<uint4*>(yrow + (size_t)pj * C_out + co) = uint4{m[t][0], m[t][1], m[t][2], m[t][3]};
                 cur[t][jj] = h[t][jj];
             }
         }
@@ -378,7 +396,7 @@ __device__ __forceinline__ int side(int u, int e) { return u < 0 ? 0 : (u >= e ?
 // padded input tile comes from the image in 2x2 cells: a cell is four pixels,
 // or (in a low block, on either side of a block border) its average.  Bound
 // by the latency of that load and by the output's stores.  1024x2048, 8x16
-// blocks, half low: 28 us; split, pad and the direct convolution take 3780 us.
+// blocks, half low: 27 us; split, pad and the direct convolution take 3780 us.
 template <typename T, int C>
 __global__ __launch_bounds__(SB_WG, 2) void k_stem_blocks(Geo g, const uint8_t* __restrict__ mask,
                                                           const T* __restrict__ x, const T* __restrict__ w,
@@ -507,11 +525,14 @@ __global__ __launch_bounds__(SB_WG, 2) void k_stem_blocks(Geo g, const uint8_t* 
 // max-pool on packed stacks
 // ---------------------------------------------------------------------------
 
-// One workgroup: 256 (output pixel, 8 channels) items of one block; a thread
-// takes the nine window pixels through BlockPad's sources (all in flight
-// together).  Bound by the input's read from HBM or the Infinity Cache, each
-// pixel once there and 2.25 times from L1 / L2.  The stem's output at
-// 1024x2048, half low: 38 us; pad and max-pool as two kernels take 87 us.
+// One workgroup: 256 items of one block, an item eight channels of PB_ROWS
+// output pixels below one another, whose windows share rows: 27 loads for four
+// outputs instead of 36, three rows (nine loads) in flight.  A pixel of the
+// halo (the row above or the column left of the block) comes through
+// BlockPad's source.  Bound by the input's read from HBM or the Infinity
+// Cache.  The stem's output at 1024x2048, half low: 21 us (38 with a
+// thread for every output); pad and max-pool as two kernels take 87 us.
+constexpr int PB_ROWS = 4;
 template <typename T>
 __global__ __launch_bounds__(WG) void k_pool_blocks(Geo g, const uint8_t* __restrict__ mask, const T* __restrict__ hi,
                                                     const T* __restrict__ lo, T* __restrict__ ho, T* __restrict__ lo_o,
@@ -529,40 +550,72 @@ __global__ __launch_bounds__(WG) void k_pool_blocks(Geo g, const uint8_t* __rest
     const Neigh nb = wave_neighbourhood<true>(wm, g.GH, g.GW, n, gy, gx);
     const int e = high ? g.bs : g.bs >> 1, eo = e >> 1, cv = g.C / 8;
     const int it = piece * WG + (int)threadIdx.x;
-    if (it >= eo * eo * cv) return;
-    const int pix = it / cv, c = (it - pix * cv) * 8, i = pix / eo, j = pix - i * eo;
-    float m[8];
-#pragma unroll
-    for (int b = 0; b < 8; ++b) m[b] = -INFINITY;
-    // interior windows read the block itself: nine plain loads
-    if (i > 0 && j > 0) {
-        const T* p = (high ? hi : lo) + (((size_t)slot * e + 2 * i - 1) * e + 2 * j - 1) * g.C + c;
-        Vec<T, 8> v[9];
-#pragma unroll
-        for (int d = 0; d < 9; ++d)
-            v[d].raw = *reinterpret_cast<const uint4*>(p + ((size_t)(d / 3) * e + d % 3) * g.C);
-#pragma unroll
-        for (int d = 0; d < 9; ++d)
-#pragma unroll
-            for (int b = 0; b < 8; ++b) m[b] = fmaxf(m[b], to_f32(v[d].e[b]));
-    } else {
-        for (int r = 0; r < 3; ++r) {
-            SrcBatch<T, 8, 3> sb;
-#pragma unroll
-            for (int s = 0; s < 3; ++s)
-                sb.issue(s, packed_src<T, NHWC>(hi, lo, g.C, g.bs, nb, hi_cap, lo_cap, 2 * i - 1 + r, 2 * j - 1 + s, c));
-#pragma unroll
+    const int strips = (eo + PB_ROWS - 1) / PB_ROWS;
+    if (it >= strips * eo * cv) return;
+    const int pix = it / cv, c = (it - pix * cv) * 8, strip = pix / eo, j = pix - strip * eo;
+    const int i0 = strip * PB_ROWS, rows = min(PB_ROWS, eo - i0);
+    const T* own = (high ? hi : lo) + ((size_t)slot * e * e + 2 * j) * g.C + c;
+    T* out = (high ? ho : lo_o) + (((size_t)slot * eo + i0) * eo + j) * g.C + c;
+
+    // window row u: its three pixels, requested, then their maximum
+    struct Row {
+        Vec<T, 8> v[3];
+    };
+    auto halo = [&](int u, int v) {
+        const Src<T> s = packed_src<T, NHWC>(hi, lo, g.C, g.bs, nb, hi_cap, lo_cap, u, v, c);
+        if (!s.p) return vzero<T, 8>();
+        const Vec<T, 8> a = vload<T, 8>(s.p);
+        if (!s.avg) return a;
+        return vavg4<T, 8>(a, vload<T, 8>(s.p + s.d1), vload<T, 8>(s.p + s.d2), vload<T, 8>(s.p + s.d2 + s.d1));
+    };
+    auto load = [&](int u, Row& r) {
+        if (u < 0) {
             for (int s = 0; s < 3; ++s) {
-                const Vec<T, 8> v = sb.value(s);
-#pragma unroll
-                for (int b = 0; b < 8; ++b) m[b] = fmaxf(m[b], to_f32(v.e[b]));
+                const Vec<T, 8> x = halo(u, 2 * j - 1 + s);
+                if (s == 0) r.v[0] = x;
+                else if (s == 1) r.v[1] = x;
+                else r.v[2] = x;
             }
+            return;
         }
-    }
-    Vec<T, 8> o;
+        const T* p = own + (size_t)u * e * g.C;
+        r.v[1] = vload<T, 8>(p);
+        r.v[2] = vload<T, 8>(p + g.C);
+        if (j > 0) r.v[0] = vload<T, 8>(p - g.C);
+        else r.v[0] = halo(u, -1);
+    };
+    auto row_max = [](const Row& r, float (&m)[8]) {
 #pragma unroll
-    for (int b = 0; b < 8; ++b) o.e[b] = from_f32<T>(m[b]);
-    *reinterpret_cast<uint4*>((high ? ho : lo_o) + (((size_t)slot * eo + i) * eo + j) * g.C + c) = o.raw;
+        for (int b = 0; b < 8; ++b)
+            m[b] = fmaxf(fmaxf(to_f32(r.v[0].e[b]), to_f32(r.v[1].e[b])), to_f32(r.v[2].e[b]));
+    };
+    float prev[8];
+    Row a, b;
+    {
+        Row r;
+        load(2 * i0 - 1, r);
+        load(2 * i0, a);
+        load(2 * i0 + 1, b);
+        row_max(r, prev);
+    }
+    for (int i = 0; i < rows; ++i) {
+        Row a2, b2;
+        if (i + 1 < rows) {  // the next output's rows, while this one is finished
+            load(2 * (i0 + i) + 2, a2);
+            load(2 * (i0 + i) + 3, b2);
+        }
+        float m[8];
+        row_max(a, m);
+#pragma unroll
+        for (int x = 0; x < 8; ++x) m[x] = fmaxf(prev[x], m[x]);
+        row_max(b, prev);
+        Vec<T, 8> o;
+#pragma unroll
+        for (int x = 0; x < 8; ++x) o.e[x] = from_f32<T>(fmaxf(m[x], prev[x]));
+        vstore<T, 8>(out + (size_t)i * eo * g.C, o);
+        a = a2;
+        b = b2;
+    }
 }
 
 inline bool al(const void* p, uintptr_t n) { return (reinterpret_cast<uintptr_t>(p) & (n - 1)) == 0; }
@@ -620,7 +673,9 @@ hipError_t stem_blocks_t(const Geo& g, const uint8_t* mask, const void* x, const
 template <typename T>
 hipError_t pool_blocks_t(const Geo& g, const uint8_t* mask, const void* hi, const void* lo, void* ho, void* lo_o,
                          int hi_cap, int lo_cap, hipStream_t st) {
-    auto pieces = [&](int eo) { return (int)(((long long)eo * eo * (g.C / 8) + WG - 1) / WG); };
+    auto pieces = [&](int eo) {
+        return (int)(((long long)((eo + PB_ROWS - 1) / PB_ROWS) * eo * (g.C / 8) + WG - 1) / WG);
+    };
     const int th = pieces(g.bs / 2), tl = pieces(g.bs / 4);
     const long long blocks = (long long)hi_cap * th + (long long)lo_cap * tl;
     if (blocks == 0) return hipSuccess;
