@@ -8,6 +8,7 @@
 #include <stdarg.h>
 #include <stdio.h>
 
+#include <algorithm>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -95,6 +96,11 @@ int check_ws(const char* fn, size_t need, const void* ws, size_t ws_bytes) {
         return fail(SB_ENOMEM, fn, "needs a workspace of %zu bytes (got %zu at %p)", need, ws ? ws_bytes : (size_t)0, ws);
     if (reinterpret_cast<uintptr_t>(ws) % 256) return fail(SB_EINVAL, fn, "workspace must be 256-byte aligned");
     return SB_OK;
+}
+
+// The bytes a call may use of a workspace it does not insist on.
+size_t usable_ws(const void* ws, size_t ws_bytes) {
+    return ws && reinterpret_cast<uintptr_t>(ws) % 256 == 0 ? ws_bytes : 0;
 }
 
 bool any_overlap(const std::vector<Range>& outs, const std::vector<Range>& ins) {
@@ -257,8 +263,11 @@ int segblocks_block_conv3x3(const void* hi, const void* lo, int dtype, int layou
         (s = check_stack(fn, "lo_out", lo_out, lo_cap)))
         return s;
     sb::ConvArgs a{hi, lo, weight, bias, residual_hi, residual_lo, hi_out, lo_out, C_in, C_out, flags, hi_cap, lo_cap};
-    const size_t need = sb::conv_ws_bytes(dtype, layout, sb::SRC_PACKED, sb::DST_PACKED, g, a);
-    if ((s = check_ws(fn, need, workspace, ws_bytes))) return s;
+    // (a workspace that is enough only without splitting a remainder runs that plan)
+    const size_t least = sb::conv_ws_bytes(dtype, layout, sb::SRC_PACKED, sb::DST_PACKED, g, a, true);
+    if ((s = check_ws(fn, least, workspace, ws_bytes))) return s;
+    ws_bytes = usable_ws(workspace, ws_bytes);
+    const size_t need = std::min(ws_bytes, sb::conv_ws_bytes(dtype, layout, sb::SRC_PACKED, sb::DST_PACKED, g, a));
     const long long es = esize(dtype), lb = bs / 2;
     const Range rh{hi, hi_cap * (long long)C_in * bs * bs * es}, rl{lo, lo_cap * (long long)C_in * lb * lb * es};
     const Range rw{weight, (long long)C_out * C_in * 9 * es}, rb{bias, bias ? C_out * es : 0};
@@ -359,16 +368,21 @@ int block_conv_ex_impl(const char* fn, bool fixed_scratch, const void* hi, const
         (s = check_stack(fn, "lo_out", lo_out, lo_cap)))
         return s;
     sb::ConvArgs a{hi, lo, weight, bias, residual_hi, residual_lo, hi_out, lo_out, C_in, C_out, flags, hi_cap, lo_cap};
-    const size_t need = sb::igemm_fits_shape(dtype, layout, g, a) ? sb::igemm_ws_bytes(g, a, ksize, stride) : 0;
+    // (scratch that is enough only without splitting a remainder runs that plan)
+    const bool ig = sb::igemm_fits_shape(dtype, layout, g, a);
+    const size_t least = ig ? sb::igemm_ws_bytes(g, a, ksize, stride, true) : 0;
+    const size_t most = ig ? sb::igemm_ws_bytes(g, a, ksize, stride) : 0;
     if (fixed_scratch) {
-        if (need > SCRATCH_BYTES)
-            return fail(SB_ENOMEM, fn, "needs %zu bytes of scratch, more than the fixed %zu bytes", need,
+        if (least > SCRATCH_BYTES)
+            return fail(SB_ENOMEM, fn, "needs %zu bytes of scratch, more than the fixed %zu bytes", least,
                         SCRATCH_BYTES);
         workspace = nullptr;
         ws_bytes = 0;
-    } else if ((s = check_ws(fn, need, workspace, ws_bytes))) {
+    } else if ((s = check_ws(fn, least, workspace, ws_bytes))) {
         return s;
     }
+    ws_bytes = usable_ws(workspace, ws_bytes);
+    const size_t need = std::min(fixed_scratch ? (size_t)SCRATCH_BYTES : ws_bytes, most);
     const long long es = esize(dtype), lb = bs / 2, bo = bs / stride, lo_e = lb / stride;
     const Range rh{hi, hi_cap * (long long)C_in * bs * bs * es}, rl{lo, lo_cap * (long long)C_in * lb * lb * es};
     const Range rw{weight, (long long)C_out * C_in * ksize * ksize * es}, rb{bias, bias ? C_out * es : 0};
@@ -445,9 +459,13 @@ int segblocks_block_conv_chain(const void* hi, const void* lo, const void* hi_ha
     // and writes hi_out_half itself (in the resident kernel the extra
     // registers cost more than the launch after it)
     const bool k33 = ksize == 3 && stride == 1;
-    const size_t need = k33 ? sb::conv_ws_bytes(dtype, layout, sb::SRC_PACKED, sb::DST_PACKED, g, a)
-                            : (sb::igemm_fits_shape(dtype, layout, g, a) ? sb::igemm_ws_bytes(g, a, ksize, stride) : 0);
-    if ((s = check_ws(fn, need, workspace, ws_bytes))) return s;
+    auto bytes_for = [&](bool frugal) -> size_t {
+        if (k33) return sb::conv_ws_bytes(dtype, layout, sb::SRC_PACKED, sb::DST_PACKED, g, a, frugal);
+        return sb::igemm_fits_shape(dtype, layout, g, a) ? sb::igemm_ws_bytes(g, a, ksize, stride, frugal) : 0;
+    };
+    if ((s = check_ws(fn, bytes_for(true), workspace, ws_bytes))) return s;
+    ws_bytes = usable_ws(workspace, ws_bytes);
+    const size_t need = std::min(ws_bytes, bytes_for(false));
     const Range rh{hi, hi_cap * (long long)C_in * bs * bs * es}, rl{lo, lo_cap * (long long)C_in * lb * lb * es};
     const Range rhh{hi_half, hi_half ? hi_cap * (long long)C_in * (lb * lb) * es : 0};
     const Range rw{weight, (long long)C_out * C_in * ksize * ksize * es}, rb{bias, bias ? C_out * es : 0};

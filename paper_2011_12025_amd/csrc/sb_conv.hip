@@ -860,10 +860,10 @@ hipError_t layer_via_packed(int dtype, const Geo& g, const uint8_t* mask, const 
 
 }  // namespace
 
-size_t conv_ws_bytes(int dtype, int layout, ConvSrc src, ConvDst dst, const Geo& g, const ConvArgs& a) {
+size_t conv_ws_bytes(int dtype, int layout, ConvSrc src, ConvDst dst, const Geo& g, const ConvArgs& a, bool frugal) {
     if (conv_res_fits_shape(dtype, layout, g, a)) return 0;
     if (src == SRC_PACKED && dst == DST_PACKED && igemm_fits_shape(dtype, layout, g, a))
-        return igemm_ws_bytes(g, a, 3, 1);
+        return igemm_ws_bytes(g, a, 3, 1, frugal);
     if (src == SRC_DENSE && dst == DST_DENSE && layer_packed_route(dtype, layout, g, a))
         return igemm_dense_fits(dtype, layout, g, a) ? igemm_dense_ws_bytes(g, a) : packed_layout(g, a).total;
     return 0;

@@ -30,7 +30,9 @@
 // Split K: when the tiles alone do not fill the chip, the K steps of a tile
 // are divided among several workgroups that write fp32 partial tiles to the
 // caller's workspace; a second kernel sums them in split order
-// (deterministic) and runs the epilogue.
+// (deterministic) and runs the epilogue.  When they fill it and leave a
+// remainder (281 tiles on 256 CUs), only the remainder's tiles are split, so
+// that the last round is short instead of nearly empty.
 //
 // The grid has room for every slot below the stacks' capacities; the class
 // counts are only known in the kernel, so each workgroup numbers the tiles
@@ -181,9 +183,10 @@ struct GParams {
     int tiles;      // M tiles of the grid (both classes)
     int tiles_n;    // output-channel tiles
     int tile_major; // grid order: 1 = M tile slowest, 0 = M tile fastest
-    int splits;     // workgroups sharing the K steps of a tile
-    float* part;    // fp32 partial tiles [tile][n tile][split][TM * TN] when splits > 1
-    int* rows;      // per M tile, written when splits > 1: valid output rows of its class's stack and its
+    int whole;      // units (M tile x channel tile, in grid order) below this one are not split
+    int splits;     // workgroups sharing the K steps of each other unit
+    float* part;    // fp32 partial tiles [unit - whole][split][TM * TN] when splits > 1
+    int* rows;      // per M tile with split units: valid output rows of its class's stack and its
                     // tile number in that class (-1 - number for the low class)
     const void* lo_pad;  // the low stack with its 1-pixel halo [lo_cap][lb+2][lb+2][C_in], or nullptr
     // Dense mode (a whole layer): the high blocks' pixels come from the dense
@@ -192,7 +195,7 @@ struct GParams {
     // [N][H][W][C_out], a low pixel to its 2 x 2 cell (BlockCombine).
     int dense;
     int W;          // dense mode: width of the map
-    int* dout;      // per M tile, TM dense output pixels (-1: none), written when splits > 1
+    int* dout;      // per M tile with split units, TM dense output pixels (-1: none)
     int hs_lg;      // log2 of the high output extent when the epilogue writes a.out_hs, else -1
     int org;        // tap (ky, kx) of output pixel (i, j) is input pixel (ST i + ky - org, ST j + kx - org): the
                     // filter's radius, or KS - 1 for the full convolution of blocks padded with zeros on their own
@@ -375,29 +378,28 @@ __global__ __launch_bounds__(GWG, 1) void k_igemm(Geo g, const uint8_t* __restri
     const int tid = (int)threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: LDS windows are scalar addresses
     const int B = (int)g.B;
-    // Workgroup lin = (M tile, channel tile, split).  When the stacks have
+    // Workgroup = (M tile, channel tile, split).  When the stacks have
     // room for more blocks than the mask can fill, the M tile is the slowest
     // index, so that the surplus workgroups are dispatched last; otherwise
     // the fastest, so that the channel tiles and splits of a tile, which
     // share its pixels, run on one XCD when the tile count is a multiple of 8
     // (workgroups go to the XCDs round-robin).
-    const int lin = (int)blockIdx.x, per_tile = gp.tiles_n * gp.splits;
-    int tx, rq;
-    if (gp.tile_major) {
-        tx = lin / per_tile;
-        rq = lin - tx * per_tile;
-    } else {
-        rq = lin / gp.tiles;
-        tx = lin - rq * gp.tiles;
+    const int units = gp.tiles * gp.tiles_n;
+    int unit = (int)blockIdx.x, z = 0, splits = 1;
+    if (unit >= gp.whole) {
+        const int l = unit - gp.whole, r = units - gp.whole;
+        splits = gp.splits;
+        z = gp.tile_major ? l % splits : l / r;
+        unit = gp.whole + (gp.tile_major ? l / splits : l - z * r);
     }
-    const int ny = gp.tile_major ? rq / gp.splits : rq - (rq / gp.tiles_n) * gp.tiles_n;
+    const int ny = gp.tile_major ? unit % gp.tiles_n : unit / gp.tiles;
+    const int tx = gp.tile_major ? unit / gp.tiles_n : unit - ny * gp.tiles;
     const int co0 = ny * TN;
     const int C_in = a.C_in, C_out = a.C_out;
     const int cpt = gp.cpt;
     const int nsteps = KT * cpt;
-    const int z = gp.tile_major ? rq - ny * gp.splits : rq / gp.tiles_n;
-    const int s_first = z * nsteps / gp.splits;
-    const int n = (z + 1) * nsteps / gp.splits - s_first;  // steps of this workgroup (>= 1)
+    const int s_first = z * nsteps / splits;
+    const int n = (z + 1) * nsteps / splits - s_first;  // steps of this workgroup (>= 1)
     const T* zrow = reinterpret_cast<const T*>(g_zero_row);
 
     // the mask byte of the thread's first block
@@ -471,7 +473,7 @@ __global__ __launch_bounds__(GWG, 1) void k_igemm(Geo g, const uint8_t* __restri
     const int eo2 = eo * eo;
     const int rows_valid = surplus ? 0 : (high ? nh_eff : nl_eff) * eo2;
     const int m0 = mt * TM;
-    if (gp.splits > 1 && ny == 0 && z == 0 && tid == 0) {
+    if (splits > 1 && z == 0 && tid == 0) {  // (the channel tiles of an M tile write the same)
         gp.rows[2 * tx] = rows_valid;
         gp.rows[2 * tx + 1] = high ? mt : -1 - mt;
     }
@@ -608,7 +610,7 @@ __global__ __launch_bounds__(GWG, 1) void k_igemm(Geo g, const uint8_t* __restri
             o = s_nbase[b] + (high ? i * g.W + j : 2 * i * g.W + 2 * j);
         }
         s_dout[tid] = o;
-        if (gp.splits > 1 && ny == 0 && z == 0) gp.dout[tx * TM + tid] = o;
+        if (splits > 1 && z == 0) gp.dout[tx * TM + tid] = o;
     }
     gbarrier();
 
@@ -689,16 +691,15 @@ __global__ __launch_bounds__(GWG, 1) void k_igemm(Geo g, const uint8_t* __restri
     }
     __builtin_amdgcn_s_waitcnt(0);  // the padding DMAs
 
-    if (gp.splits == 1) {
+    if (splits == 1) {
         gepilogue<T, WM, MS, NS>(acc, a, high, m0, rows_valid, co0, dense ? s_dout : nullptr, g.W,
                                  high && gp.hs_lg >= 0 ? (T*)a.out_hs : nullptr, gp.hs_lg);
     } else {
-        const int tile_lin = tx * gp.tiles_n + ny;
 #pragma unroll
         for (int ms = 0; ms < MS; ++ms)
 #pragma unroll
             for (int ns = 0; ns < NS; ++ns)
-                *reinterpret_cast<floatx4*>(gp.part + gpart_off<TM * TN, MS, NS>(tile_lin, z, gp.splits, wave, ms, ns,
+                *reinterpret_cast<floatx4*>(gp.part + gpart_off<TM * TN, MS, NS>(unit - gp.whole, z, splits, wave, ms, ns,
                                                                                 lane)) = acc[ms][ns];
     }
 }
@@ -715,14 +716,14 @@ __global__ __launch_bounds__(GWG, 1) void k_igemm(Geo g, const uint8_t* __restri
 // (thread ^ 64) for eo = 16 and the one after (thread ^ 128) for eo = 32
 // (MS = 4).
 template <typename T, int WM, int MS, int NS>
-__global__ __launch_bounds__(256) void k_igemm_reduce(ConvArgs a, GParams gp, int tiles, int tiles_n) {
+__global__ __launch_bounds__(256) void k_igemm_reduce(ConvArgs a, GParams gp) {
     constexpr int WN = GWAVES / WM;
     constexpr int TM = WM * MS * 16, TN = WN * NS * 16;
     constexpr int PER_TILE = GWAVES * MS * (NS / 2) * 64;
     static_assert(PER_TILE % 256 == 0, "a workgroup stays in one tile");
     __shared__ uint4 s_o[256];
     const long long gid = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (gid >= (long long)tiles * tiles_n * PER_TILE) return;  // whole workgroups
+    if (gid >= (long long)(gp.tiles * gp.tiles_n - gp.whole) * PER_TILE) return;  // whole workgroups
     const int tile_lin = (int)(gid / PER_TILE);
     int r = (int)(gid - (long long)tile_lin * PER_TILE);
     const int lane = r & 63;
@@ -740,7 +741,9 @@ __global__ __launch_bounds__(256) void k_igemm_reduce(ConvArgs a, GParams gp, in
         r /= MS;
     }
     const int wave = r;
-    const int tx = tile_lin / tiles_n, ty = tile_lin - tx * tiles_n;
+    const int unit = gp.whole + tile_lin;
+    const int ty = gp.tile_major ? unit % gp.tiles_n : unit / gp.tiles;
+    const int tx = gp.tile_major ? unit / gp.tiles_n : unit - ty * gp.tiles;
     const int rows_valid = gp.rows[2 * tx];
     const int code = gp.rows[2 * tx + 1];
     const int high = code >= 0;
@@ -812,6 +815,7 @@ namespace {
 // partial tiles.
 constexpr int GSTART_COST = 10;
 constexpr int GSPLIT_COST = 12;  // plus one per split
+constexpr int GTAIL_COST = 7;    // the same pass over a remainder's tiles only: mostly its launch
 
 inline bool galigned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 inline size_t ground256(size_t b) { return (b + 255) / 256 * 256; }
@@ -844,12 +848,18 @@ inline bool igemm_tm256_fits(const Geo& g, int ks) {
 // and the caller's workspace that they take.
 struct IgPlan {
     int TM, TN, tiles_h, tiles_l, tiles_n, splits;
+    int whole;    // units that are not split (a multiple of the CUs, or 0)
     bool pad_low;
+    bool own_hs;  // ... as the high stack's border cells at half resolution instead
     size_t part_bytes, pad_bytes;
 };
 
 // full: the full convolution of every block on its own (outputs ks - 1 pixels wider).
-IgPlan igemm_plan(const Geo& g, const ConvArgs& a, int ks, int stride, bool dense = false, bool full = false) {
+// frugal: without splitting a remainder (its partial tiles may need more
+// workspace than a plan without it: a call whose workspace is only enough for
+// the frugal plan runs that).
+IgPlan igemm_plan(const Geo& g, const ConvArgs& a, int ks, int stride, bool dense = false, bool full = false,
+                  bool frugal = false) {
     IgPlan p;
     const int wider = full ? ks - 1 : 0;
     const int eo_h = g.bs / stride + wider, eo_l = (g.bs / 2) / stride + wider;
@@ -884,6 +894,8 @@ IgPlan igemm_plan(const Geo& g, const ConvArgs& a, int ks, int stride, bool dens
     p.TM = 128;
     p.TN = tn_max;
     p.splits = 1;
+    p.whole = 0;
+    const bool room = (long long)a.hi_cap + a.lo_cap > g.B;  // surplus tiles
     for (int cand = 0; cand < 4; ++cand) {
         int TM = 128, tn;
         if (cand < 3) {
@@ -907,6 +919,23 @@ IgPlan igemm_plan(const Geo& g, const ConvArgs& a, int ks, int stride, bool dens
                 p.TM = TM;
                 p.TN = tn;
                 p.splits = c;
+                p.whole = 0;
+            }
+            // whole rounds of unsplit tiles, then the remainder split c ways: a
+            // 128-channel convolution of four images, 60 % low (281 tiles of
+            // 256 x 128), 56 -> 45 us with its pass; it pays while the remainder
+            // is small (320 tiles: 59 -> 57)
+            const long long whole = wgs / cus * cus, rest = wgs - whole;
+            if (c == 1 || frugal || dense || room || whole == 0 || rest == 0) continue;
+            const double tail = (double)(whole / cus) * (nsteps * w + GSTART_COST) +
+                                (double)((rest * c + cus - 1) / cus) * ((nsteps + c - 1) / c * w + GSTART_COST) +
+                                GTAIL_COST + c * wr * rest / cus;
+            if (tail < best) {
+                best = tail;
+                p.TM = TM;
+                p.TN = tn;
+                p.splits = c;
+                p.whole = (int)whole;
             }
         }
     }
@@ -915,6 +944,7 @@ IgPlan igemm_plan(const Geo& g, const ConvArgs& a, int ks, int stride, bool dens
     const int tiles = p.tiles_h + p.tiles_l;
     p.tiles_n = (a.C_out + p.TN - 1) / p.TN;
     if (tiles == 0) p.splits = 1;
+    if (p.splits == 1) p.whole = 0;
     // A low block's halo across a resolution change, with average sampling, is
     // the 2x2 average of a high neighbour's cell: a 3 x 3 convolution with
     // both classes pads the low stack once beforehand (BlockPad of the low
@@ -925,18 +955,24 @@ IgPlan igemm_plan(const Geo& g, const ConvArgs& a, int ks, int stride, bool dens
     // In dense mode the padded low stack comes straight from the dense map and
     // the high tiles read their low neighbours from it as well.
     p.pad_low = dense || (ks == 3 && p.tiles_l > 0 && a.hi_cap > 0 && pad_mode(a.flags) == PM_AVG && !a.in_hs);
-    p.part_bytes = p.splits > 1 ? ground256((size_t)tiles * p.tiles_n * p.splits * p.TM * p.TN * 4 + (size_t)tiles * 8 +
-                                            (dense ? (size_t)tiles * p.TM * 4 : 0))
+    p.part_bytes = p.splits > 1 ? ground256(((size_t)tiles * p.tiles_n - p.whole) * p.splits * p.TM * p.TN * 4 +
+                                            (size_t)tiles * 8 + (dense ? (size_t)tiles * p.TM * 4 : 0))
                                 : 0;
-    p.pad_bytes = p.pad_low ? ground256((size_t)a.lo_cap * (g.bs / 2 + 2) * (g.bs / 2 + 2) * a.C_in * 2) : 0;
+    // What a low block needs of its high neighbours is only the border cells of
+    // their half-resolution stack, which the K loop reads like a stack given as
+    // in_hs: that is less to write than the padded low stack unless low blocks
+    // are few (the rule is the two sizes; so the workspace is never larger).
+    const size_t lb = g.bs / 2;
+    const size_t pad = (size_t)a.lo_cap * (lb + 2) * (lb + 2), hs = (size_t)a.hi_cap * lb * lb;
+    p.own_hs = p.pad_low && !dense && hs <= pad && a.C_in % 8 == 0;
+    p.pad_bytes = p.pad_low ? ground256((p.own_hs ? hs : pad) * a.C_in * 2) : 0;
     return p;
 }
 
 template <typename T, int KS, int ST, int WM, int MS, int NS>
-hipError_t igemm_run(const Geo& g, const uint8_t* mask, const ConvArgs& a, Ws ws, hipStream_t st, bool dense,
-                     bool full) {
+hipError_t igemm_run(const Geo& g, const uint8_t* mask, ConvArgs a, Ws ws, hipStream_t st, bool dense, bool full,
+                     const IgPlan& pl) {
     constexpr int TM = WM * MS * 16, TN = (GWAVES / WM) * NS * 16;
-    const IgPlan pl = igemm_plan(g, a, KS, ST, dense, full);
     if (pl.TM != TM || pl.TN != TN) return hipErrorInvalidValue;
     const int tiles = pl.tiles_h + pl.tiles_l;
     if (tiles == 0) return hipSuccess;
@@ -953,6 +989,8 @@ hipError_t igemm_run(const Geo& g, const uint8_t* mask, const ConvArgs& a, Ws ws
     const int tiles_n = pl.tiles_n;
     const int S = pl.splits;
     gp.splits = S;
+    gp.whole = S > 1 ? pl.whole : tiles * tiles_n;
+    const long long split_units = (long long)tiles * tiles_n - gp.whole;
     gp.tiles = tiles;
     gp.tiles_n = tiles_n;
     gp.tile_major = (long long)a.hi_cap + a.lo_cap > g.B;  // room for surplus tiles
@@ -970,7 +1008,7 @@ hipError_t igemm_run(const Geo& g, const uint8_t* mask, const ConvArgs& a, Ws ws
     gp.hs_lg = hs_epi ? __builtin_ctz((unsigned)eo_h) : -1;
     if (S > 1) {
         gp.part = (float*)ws.p;
-        gp.rows = (int*)((char*)ws.p + (size_t)tiles * tiles_n * S * TM * TN * 4);  // 2 ints per tile
+        gp.rows = (int*)((char*)ws.p + (size_t)split_units * S * TM * TN * 4);  // 2 ints per tile
         gp.dout = gp.rows + 2 * tiles;                                              // dense mode: TM per tile
     }
     if (pl.pad_low) {
@@ -978,19 +1016,21 @@ hipError_t igemm_run(const Geo& g, const uint8_t* mask, const ConvArgs& a, Ws ws
         Geo pg = g;
         pg.C = a.C_in;
         const int dt = std::is_same<T, f16>::value ? 1 : 2;
-        e = dense ? launch_pad_low_dense(dt, pg, a.in_hi, mask, lp, a.lo_cap, st)
-                  : launch_pad_rows(dt, pg, a.in_hi, a.in_lo, mask, nullptr, lp, a.hi_cap, a.lo_cap, PM_AVG, st);
+        e = pl.own_hs ? launch_sample_hs(dt, a.in_hi, a.hi_cap, g.bs, a.C_in, lp, st, true)
+            : dense   ? launch_pad_low_dense(dt, pg, a.in_hi, mask, lp, a.lo_cap, st)
+                      : launch_pad_rows(dt, pg, a.in_hi, a.in_lo, mask, nullptr, lp, a.hi_cap, a.lo_cap, PM_AVG, st);
         if (e != hipSuccess) return e;
-        gp.lo_pad = lp;
+        if (pl.own_hs) a.in_hs = lp;
+        else gp.lo_pad = lp;
     }
-    const dim3 grid((unsigned)((long long)tiles * tiles_n * S));
+    const dim3 grid((unsigned)(gp.whole + split_units * S));
     hipLaunchKernelGGL((k_igemm<T, KS, ST, WM, MS, NS>), grid, dim3(GWG), smem, st, g, mask, a, gp);
     if (S > 1) {
         e = hipGetLastError();
         if (e != hipSuccess) return e;
-        const long long threads = (long long)tiles * tiles_n * GWAVES * MS * (NS / 2) * 64;
+        const long long threads = split_units * GWAVES * MS * (NS / 2) * 64;
         hipLaunchKernelGGL((k_igemm_reduce<T, WM, MS, NS>), dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, a,
-                           gp, tiles, tiles_n);
+                           gp);
     }
     if (a.out_hs && !hs_epi && !dense) {
         e = hipGetLastError();
@@ -1003,12 +1043,13 @@ hipError_t igemm_run(const Geo& g, const uint8_t* mask, const ConvArgs& a, Ws ws
 template <typename T, int KS, int ST>
 hipError_t igemm_tile(const Geo& g, const uint8_t* mask, const ConvArgs& a, Ws ws, hipStream_t st,
                       bool dense = false, bool full = false) {
-    const IgPlan pl = igemm_plan(g, a, KS, ST, dense, full);
+    IgPlan pl = igemm_plan(g, a, KS, ST, dense, full);
+    if (ws.bytes < pl.part_bytes + pl.pad_bytes) pl = igemm_plan(g, a, KS, ST, dense, full, true);
     const int tn = pl.TN;
-    if (pl.TM == 256) return igemm_run<T, KS, ST, 4, 4, 4>(g, mask, a, ws, st, dense, full);
-    if (tn == 64) return igemm_run<T, KS, ST, 4, 2, 2>(g, mask, a, ws, st, dense, full);
-    if (tn == 256) return igemm_run<T, KS, ST, 2, 4, 4>(g, mask, a, ws, st, dense, full);
-    return igemm_run<T, KS, ST, 2, 4, 2>(g, mask, a, ws, st, dense, full);
+    if (pl.TM == 256) return igemm_run<T, KS, ST, 4, 4, 4>(g, mask, a, ws, st, dense, full, pl);
+    if (tn == 64) return igemm_run<T, KS, ST, 4, 2, 2>(g, mask, a, ws, st, dense, full, pl);
+    if (tn == 256) return igemm_run<T, KS, ST, 2, 4, 4>(g, mask, a, ws, st, dense, full, pl);
+    return igemm_run<T, KS, ST, 2, 4, 2>(g, mask, a, ws, st, dense, full, pl);
 }
 
 template <typename T>
@@ -1040,8 +1081,8 @@ bool igemm_fits(int dtype, int layout, const Geo& g, const ConvArgs& a) {
     return igemm_fits_shape(dtype, layout, g, a);
 }
 
-size_t igemm_ws_bytes(const Geo& g, const ConvArgs& a, int ksize, int stride) {
-    const IgPlan p = igemm_plan(g, a, ksize, stride);
+size_t igemm_ws_bytes(const Geo& g, const ConvArgs& a, int ksize, int stride, bool frugal) {
+    const IgPlan p = igemm_plan(g, a, ksize, stride, false, false, frugal);
     return p.part_bytes + p.pad_bytes;
 }
 
@@ -1087,7 +1128,7 @@ bool igemm_full_fits_shape(int dtype, int layout, const Geo& g, const ConvArgs& 
 }
 
 size_t igemm_full_ws_bytes(const Geo& g, const ConvArgs& a) {
-    const IgPlan p = igemm_plan(g, a, 3, 1, false, true);
+    const IgPlan p = igemm_plan(g, a, 3, 1, false, true, true);
     return p.part_bytes + p.pad_bytes;
 }
 

@@ -67,7 +67,9 @@ hipError_t launch_conv(int dtype, int layout, ConvSrc src, ConvDst dst, const Ge
                        const uint8_t* mask, const ConvArgs& a, Ws ws, hipStream_t st);
 // Workspace of launch_conv for these shapes and capacities, assuming every
 // buffer is 16-byte aligned (a call with less aligned buffers needs no more).
-size_t conv_ws_bytes(int dtype, int layout, ConvSrc src, ConvDst dst, const Geo& g, const ConvArgs& a);
+// frugal: the least the call runs with.
+size_t conv_ws_bytes(int dtype, int layout, ConvSrc src, ConvDst dst, const Geo& g, const ConvArgs& a,
+                     bool frugal = false);
 
 // Row-job split / pad / combine for channels-last tensors of whole 16-byte
 // pixels with 16-byte aligned buffers; rows_fit tells whether they apply.
@@ -86,7 +88,9 @@ hipError_t launch_pad_low_dense(int dtype, const Geo& g, const void* x, const ui
 // The high stack at half resolution: hs[s][u][v] = the 2x2 average of cell
 // (2u, 2v) of block s of hi [hi_cap][e][e][C] (e even), for every slot below
 // hi_cap (fp16 / bf16, channels-last, 16-byte aligned, C % 8 == 0).
-hipError_t launch_sample_hs(int dtype, const void* hi, int hi_cap, int e, int C, void* hs, hipStream_t st);
+// border: only the cells on the blocks' borders (the others are left as they are).
+hipError_t launch_sample_hs(int dtype, const void* hi, int hi_cap, int e, int C, void* hs, hipStream_t st,
+                            bool border = false);
 
 // Encoder kernels (channels-last fp16/bf16): block convolution K x K
 // (K = 1, 3) at stride 1 or 2 on packed stacks, dense convolution, and
@@ -96,7 +100,8 @@ hipError_t launch_sample_hs(int dtype, const void* hi, int hi_cap, int e, int C,
 // igemm_fits_shape leaves out the pointer alignment that igemm_fits checks.
 bool igemm_fits_shape(int dtype, int layout, const Geo& g, const ConvArgs& a);
 bool igemm_fits(int dtype, int layout, const Geo& g, const ConvArgs& a);
-size_t igemm_ws_bytes(const Geo& g, const ConvArgs& a, int ksize, int stride);
+// frugal: the least the call runs with (igemm_ws_bytes: what its best plan takes)
+size_t igemm_ws_bytes(const Geo& g, const ConvArgs& a, int ksize, int stride, bool frugal = false);
 // launch_igemm writes a.out_hs (when given) from its epilogue where the tile
 // layout keeps every 2x2 cell within a wave, else with launch_sample_hs after.
 hipError_t launch_igemm(int dtype, const Geo& g, const uint8_t* mask, const ConvArgs& a, int ksize, int stride,
