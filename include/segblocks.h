@@ -375,6 +375,17 @@ int segblocks_pad_backward(const void* dhp, const void* dlp, int dtype, int layo
                            int H, int W, const uint8_t* mask, int bs, int sampling, void* dhi,
                            void* dlo, int hi_cap, int lo_cap, hipStream_t stream);
 
+/* segblocks_split then segblocks_pad_ex in one kernel (x [N,C,H,W] ->
+ * hi_pad, lo_pad), and segblocks_pad_backward then segblocks_split_backward
+ * (dhp, dlp -> dx [N,C,H,W]): the same values, without the packed stacks in
+ * memory. */
+int segblocks_split_pad(const void* x, int dtype, int layout, int N, int C, int H, int W, const uint8_t* mask,
+                        int bs, int sampling, void* hi_pad, void* lo_pad, int hi_cap, int lo_cap,
+                        hipStream_t stream);
+int segblocks_pad_split_backward(const void* dhp, const void* dlp, int dtype, int layout, int N, int C, int H,
+                                 int W, const uint8_t* mask, int bs, int sampling, void* dx, int hi_cap,
+                                 int lo_cap, hipStream_t stream);
+
 /* Gradient of segblocks_conv3x3 with respect to its padded input:
  *   dP[s,ci,u,v] = sum_{co,ky,kx} w[co,ci,ky,kx] * dO[s,co,u-ky,v-kx]
  * dho [nh,C_out,bs,bs], dlo [nl,C_out,lb,lb] -> dhp [nh,C_in,bs+2,bs+2],

@@ -24,7 +24,7 @@ __all__ = ["count", "split", "pad", "conv3x3", "combine", "block_conv3x3", "bloc
            "layer_workspace_size", "policy_heuristic", "combine_backward", "split_backward", "pad_backward",
            "conv3x3_backward_data", "conv3x3_backward_weight", "layer_backward", "pad_halo", "conv_halo",
            "maxpool_halo", "block_conv_chain", "block_conv_chain_workspace_size", "block_conv_chain_reads_half",
-           "stem_pool", "stem_blocks", "maxpool_blocks", "stem_fits"]
+           "split_pad", "pad_split_backward", "stem_pool", "stem_blocks", "maxpool_blocks", "stem_fits"]
 
 _DT = {torch.float32: _b.SB_F32, torch.float16: _b.SB_F16, torch.bfloat16: _b.SB_BF16}
 
@@ -581,21 +581,47 @@ def conv3x3_backward_weight(hp: torch.Tensor, lp: torch.Tensor, dho: torch.Tenso
     return dw, db
 
 
+def split_pad(x: torch.Tensor, mask: torch.Tensor, bs: int, counts=None, layout=None, sampling: str = "avg"):
+    """pad(*split(x)) in one kernel: (hi_pad, lo_pad)."""
+    mask = _mask(mask)
+    layout = layout_of(x) if layout is None else layout
+    _check_layout(layout, x)
+    N, C, H, W = x.shape
+    nh, nl = counts if counts is not None else count(mask)
+    hp = _empty((nh, C, bs + 2, bs + 2), x, layout)
+    lp = _empty((nl, C, bs // 2 + 2, bs // 2 + 2), x, layout)
+    _b.call("segblocks_split_pad", _ptr(x), _dt(x), layout, N, C, H, W, _ptr(mask), bs, _SAMPLING[sampling], _ptr(hp),
+            _ptr(lp), nh, nl, _stream(x))
+    return hp, lp
+
+
+def pad_split_backward(dhp: torch.Tensor, dlp: torch.Tensor, mask: torch.Tensor, bs: int, H: int, W: int, layout=None,
+                       sampling: str = "avg"):
+    """split_backward(*pad_backward(dhp, dlp)) in one kernel: dx [N,C,H,W]."""
+    mask = _mask(mask)
+    ref = dhp if dhp.shape[0] else dlp
+    layout = layout_of(ref) if layout is None else layout
+    _check_layout(layout, dhp, dlp)
+    N, C = mask.shape[0], ref.shape[1]
+    dx = _empty((N, C, H, W), ref, layout)
+    _b.call("segblocks_pad_split_backward", _ptr(dhp), _ptr(dlp), _dt(ref), layout, N, C, H, W, _ptr(mask), bs,
+            _SAMPLING[sampling], _ptr(dx), dhp.shape[0], dlp.shape[0], _stream(ref))
+    return dx
+
+
 def layer_backward(x: torch.Tensor, mask: torch.Tensor, bs: int, weight: torch.Tensor, dy: torch.Tensor,
                    bias: bool = True, sampling: str = "avg"):
     """Gradients (dx, dw, db) of y = layer(x) for an output gradient dy: the
-    forward stacks are recomputed (split, pad), then combine, convolution,
-    pad and split are run transposed.  Every step is a library call."""
+    padded stacks are recomputed (split and pad), then combine, convolution,
+    and pad with split are run transposed.  Every step is a library call."""
     layout = layout_of(x)
     N, C, H, W = x.shape
     nh, nl = count(mask)
-    hi, lo = split(x, mask, bs, counts=(nh, nl))
-    hp, lp = pad(hi, lo, mask, bs, H, W, sampling=sampling)
+    hp, lp = split_pad(x, mask, bs, counts=(nh, nl), layout=layout, sampling=sampling)
     dho, dlo_o = combine_backward(dy, mask, bs, counts=(nh, nl), layout=layout)
     dw, db = conv3x3_backward_weight(hp, lp, dho, dlo_o, mask, bs, H, W, bias=bias, layout=layout)
     dhp, dlp = conv3x3_backward_data(dho, dlo_o, mask, bs, H, W, weight, layout=layout)
-    dhi, dlo = pad_backward(dhp, dlp, mask, bs, H, W, layout=layout, sampling=sampling)
-    return split_backward(dhi, dlo, mask, bs, H, W, layout=layout), dw, db
+    return pad_split_backward(dhp, dlp, mask, bs, H, W, layout=layout, sampling=sampling), dw, db
 
 
 # ---------------------------------------------------------------------------

@@ -754,6 +754,47 @@ int segblocks_pad_backward(const void* dhp, const void* dlp, int dtype, int layo
                                              stream));
 }
 
+int segblocks_split_pad(const void* x, int dtype, int layout, int N, int C, int H, int W, const uint8_t* mask, int bs,
+                        int sampling, void* hi_pad, void* lo_pad, int hi_cap, int lo_cap, hipStream_t stream) {
+    const char* fn = "segblocks_split_pad";
+    sb::Geo g;
+    int s;
+    if ((s = check_geo(fn, dtype, layout, N, C, H, W, mask, bs, g))) return s;
+    if (!x) return fail(SB_EINVAL, fn, "x is NULL");
+    if (sampling != SB_PAD_AVG && sampling != SB_PAD_STRIDED && sampling != SB_PAD_ZERO)
+        return fail(SB_EINVAL, fn, "bad sampling %d", sampling);
+    if ((s = check_caps(fn, hi_cap, lo_cap)) || (s = check_stack(fn, "hi_pad", hi_pad, hi_cap)) ||
+        (s = check_stack(fn, "lo_pad", lo_pad, lo_cap)))
+        return s;
+    const long long es = esize(dtype), ph = bs + 2, pl = bs / 2 + 2;
+    if (ph * ph * C >= (1LL << 31)) return fail(SB_ESHAPE, fn, "block too large");
+    const Range rhp{hi_pad, hi_cap * (long long)C * ph * ph * es}, rlp{lo_pad, lo_cap * (long long)C * pl * pl * es};
+    if (any_overlap({rhp, rlp}, {Range{x, (long long)N * C * H * W * es}, Range{mask, g.B}}))
+        return fail(SB_EINVAL, fn, "output buffers overlap inputs or each other");
+    return hip_status(fn, sb::launch_split_pad(dtype, layout, g, x, mask, hi_pad, lo_pad, hi_cap, lo_cap, sampling, stream));
+}
+
+int segblocks_pad_split_backward(const void* dhp, const void* dlp, int dtype, int layout, int N, int C, int H, int W,
+                                 const uint8_t* mask, int bs, int sampling, void* dx, int hi_cap, int lo_cap,
+                                 hipStream_t stream) {
+    const char* fn = "segblocks_pad_split_backward";
+    sb::Geo g;
+    int s;
+    if ((s = check_geo(fn, dtype, layout, N, C, H, W, mask, bs, g))) return s;
+    if (!dx) return fail(SB_EINVAL, fn, "dx is NULL");
+    if (sampling != SB_PAD_AVG && sampling != SB_PAD_STRIDED && sampling != SB_PAD_ZERO)
+        return fail(SB_EINVAL, fn, "bad sampling %d", sampling);
+    if ((s = check_caps(fn, hi_cap, lo_cap)) || (s = check_stack(fn, "dhp", dhp, hi_cap)) ||
+        (s = check_stack(fn, "dlp", dlp, lo_cap)))
+        return s;
+    const long long es = esize(dtype), ph = bs + 2, pl = bs / 2 + 2;
+    if (ph * ph * C >= (1LL << 31)) return fail(SB_ESHAPE, fn, "block too large");
+    const Range rhp{dhp, hi_cap * (long long)C * ph * ph * es}, rlp{dlp, lo_cap * (long long)C * pl * pl * es};
+    if (any_overlap({Range{dx, (long long)N * C * H * W * es}}, {rhp, rlp, Range{mask, g.B}}))
+        return fail(SB_EINVAL, fn, "dx overlaps an input");
+    return hip_status(fn, sb::launch_pad_split_bwd(dtype, layout, g, dhp, dlp, mask, dx, hi_cap, lo_cap, sampling, stream));
+}
+
 int segblocks_conv3x3_backward_data_workspace_size(int dtype, int layout, int N, int C_in, int H, int W, int bs,
                                                    int C_out, int hi_cap, int lo_cap, size_t* bytes) {
     const char* fn = "segblocks_conv3x3_backward_data_workspace_size";

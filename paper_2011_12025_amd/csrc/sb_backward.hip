@@ -45,6 +45,7 @@
 //   sums groups of 16 ranges, k_wgrad_reduce the groups in order), so
 //   results do not depend on timing.
 #include <algorithm>
+#include <initializer_list>
 #include <type_traits>
 
 #include "sb_common.h"
@@ -167,6 +168,154 @@ __global__ __launch_bounds__(WG) void k_pad_bwd(const T* __restrict__ dhp, const
     if constexpr (L == NHWC) dst = (high ? dhi : dlo) + ((((size_t)slot * e + r) * e + j) * C + c);
     else                     dst = (high ? dhi : dlo) + ((((size_t)slot * C + c) * e + r) * e + j);
     vstore<T, V>(dst, o);
+}
+
+// ---------------------------------------------------------------------------
+// the layer's first and last step: BlockSample + BlockPad, and both transposed
+// ---------------------------------------------------------------------------
+constexpr int FU = 4;  // vectors per thread, their loads in flight together
+
+// Row, column and first channel of item it of a block of extent e, in the
+// memory order of the call's layout.
+template <int L, int V>
+__device__ __forceinline__ void item_at(int it, int e, int C, int& r, int& j, int& c) {
+    if constexpr (L == NHWC) {
+        const int cv = C / V, pix = it / cv;
+        c = (it - pix * cv) * V;
+        r = pix / e;
+        j = pix - r * e;
+    } else {
+        static_assert(L == NHWC || V == 1, "NCHW moves single elements");
+        const int row = it / e;
+        j = it - row * e;
+        c = row / e;
+        r = row - c * e;
+    }
+}
+
+// The padded stacks straight from the map (segblocks_split then
+// segblocks_pad_ex): the packed stacks, read once by each of its blocks and
+// its neighbours, never reach memory.  Bound by the map's read and the
+// stacks' write: 256x512, 64 channels, half low, fp16 @@FIG_SP.
+template <typename T, int L, int V>
+__global__ __launch_bounds__(WG) void k_split_pad(Geo g, const uint8_t* __restrict__ mask, const T* __restrict__ x,
+                                                  T* __restrict__ hp, T* __restrict__ lp, int hi_cap, int lo_cap,
+                                                  int pm, int Gh, int Gl) {
+    const int bid = (int)blockIdx.x;
+    const bool high = bid < hi_cap * Gh;
+    const int q = high ? bid : bid - hi_cap * Gh, per = high ? Gh : Gl;
+    const int slot = q / per, piece = q - slot * per;
+    WaveMask wm;
+    wm.init(mask, (int)g.B);
+    const int k = wm.find_nth(slot, high);
+    if (k < 0) return;
+    int n, gy, gx;
+    bcoords(k, g.GH, g.GW, n, gy, gx);
+    const Neigh nb = wave_neighbourhood<true>(wm, g.GH, g.GW, n, gy, gx);
+    uint32_t have = 0;  // bit d: neighbour d exists and has a place in its stack
+#pragma unroll
+    for (int d = 0; d < 9; ++d)
+        have |= (uint32_t)(((nb.valid >> d) & 1u) && nb.slot[d] < (((nb.high >> d) & 1u) ? hi_cap : lo_cap)) << d;
+    const int e = high ? g.bs : g.bs >> 1, pe = e + 2;
+    const int items = pe * pe * (g.C / V);
+    T* out = (high ? hp : lp) + (size_t)slot * pe * pe * g.C;
+    SrcBatch<T, V, FU> b;
+#pragma unroll
+    for (int u = 0; u < FU; ++u) {
+        const int it = (piece * FU + u) * WG + (int)threadIdx.x;
+        Src<T> s = src_zero<T>();
+        if (it < items) {
+            int r, j, c;
+            item_at<L, V>(it, pe, g.C, r, j, c);
+            const int d = (r == 0 ? 0 : r == pe - 1 ? 6 : 3) + (j == 0 ? 0 : j == pe - 1 ? 2 : 1);
+            if ((have >> d) & 1u)
+                s = dense_src<T, L>(x, n, g.C, g.H, g.W, g.bs, gy, gx, nb, r - 1, j - 1, c, pm);
+        }
+        b.issue(u, s);
+    }
+#pragma unroll
+    for (int u = 0; u < FU; ++u) {
+        const int it = (piece * FU + u) * WG + (int)threadIdx.x;
+        if (it < items) vstore<T, V>(out + (size_t)it * V, b.value(u));
+    }
+}
+
+// The input gradient straight from the padded stacks' (segblocks_pad_backward
+// then segblocks_split_backward, with the same rounding in between): a high
+// pixel away from its block's border is a copy, the others gather every
+// window over them as k_pad_bwd does.  Same workload: @@FIG_PS.
+template <typename T, int L, int V>
+__global__ __launch_bounds__(WG) void k_pad_split_bwd(Geo g, const uint8_t* __restrict__ mask,
+                                                      const T* __restrict__ dhp, const T* __restrict__ dlp,
+                                                      T* __restrict__ dx, int hi_cap, int lo_cap, int pm, int G) {
+    const int k = (int)blockIdx.x / G, piece = (int)blockIdx.x - k * G;
+    WaveMask wm;
+    wm.init(mask, (int)g.B);
+    int n, gy, gx;
+    bcoords(k, g.GH, g.GW, n, gy, gx);
+    const Neigh nb = wave_neighbourhood<true>(wm, g.GH, g.GW, n, gy, gx);
+    const bool high = (nb.high >> 4) & 1;
+    const int slot = nb.slot[4], lb = g.bs >> 1, e = high ? g.bs : lb, pe = e + 2;
+    const bool have = slot < (high ? hi_cap : lo_cap);
+    const int items = e * e * (g.C / V);
+    const int px = L == NHWC ? g.C : 1;
+    const T* own = high ? dhp : dlp;
+    Vec<T, V> v[FU];
+    bool copy[FU];
+#pragma unroll
+    for (int u = 0; u < FU; ++u) {  // the block's own window, which every pixel takes
+        const int it = (piece * FU + u) * WG + (int)threadIdx.x;
+        v[u] = vzero<T, V>();
+        copy[u] = true;
+        if (it < items && have) {
+            int r, j, c;
+            item_at<L, V>(it, e, g.C, r, j, c);
+            const int m = high ? 2 : 1;  // (a low neighbour's window reaches two pixels into a high block)
+            copy[u] = pm == PM_ZERO || (r >= m && r < e - m && j >= m && j < e - m);
+            if (copy[u]) v[u] = vload<T, V>(stack_at<T, L>(own, slot, g.C, pe, r + 1, j + 1, c));
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < FU; ++u) {
+        const int it = (piece * FU + u) * WG + (int)threadIdx.x;
+        if (it >= items) continue;
+        int r, j, c;
+        item_at<L, V>(it, e, g.C, r, j, c);
+        if (!copy[u]) {
+            float acc[V];
+#pragma unroll
+            for (int i = 0; i < V; ++i) acc[i] = 0.0f;
+            if (high) {
+                window_sum<T, L, V>(dhp, g.C, g.bs, nb, hi_cap, true, r, j, c, acc);
+                if (pm == PM_AVG || ((r | j) & 1) == 0) {
+                    float h[V];
+#pragma unroll
+                    for (int i = 0; i < V; ++i) h[i] = 0.0f;
+                    window_sum<T, L, V>(dlp, g.C, lb, nb, lo_cap, false, r >> 1, j >> 1, c, h);
+                    const float f = pm == PM_AVG ? 0.25f : 1.0f;
+#pragma unroll
+                    for (int i = 0; i < V; ++i) acc[i] += f * h[i];
+                }
+            } else {
+                for (int q = 0; q < 4; ++q)
+                    window_sum<T, L, V>(dhp, g.C, g.bs, nb, hi_cap, true, 2 * r + (q >> 1), 2 * j + (q & 1), c, acc);
+                window_sum<T, L, V>(dlp, g.C, lb, nb, lo_cap, false, r, j, c, acc);
+            }
+#pragma unroll
+            for (int i = 0; i < V; ++i) v[u].e[i] = from_f32<T>(acc[i]);
+        }
+        if (high) {
+            T* p = dx + (map_at<T, L>(dx, n, g.C, g.H, g.W, gy * g.bs + r, gx * g.bs + j, c) - dx);
+            vstore<T, V>(p, v[u]);
+        } else {
+            const Vec<T, V> o = vquarter<T, V>(v[u]);
+            T* p = dx + (map_at<T, L>(dx, n, g.C, g.H, g.W, gy * g.bs + 2 * r, gx * g.bs + 2 * j, c) - dx);
+            vstore<T, V>(p, o);
+            vstore<T, V>(p + px, o);
+            vstore<T, V>(p + (size_t)px * g.W, o);
+            vstore<T, V>(p + (size_t)px * g.W + px, o);
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -763,6 +912,52 @@ hipError_t pad_bwd_t(int layout, const Geo& g, const void* dhp, const void* dlp,
     return run(k_pad_bwd<T, NCHW, 1>, 1);
 }
 
+template <typename T, int L, int V>
+hipError_t split_pad_v(const Geo& g, const void* x, const uint8_t* mask, void* hp, void* lp, int hi_cap, int lo_cap,
+                       int pm, hipStream_t st) {
+    auto pieces = [&](long long pe) { return (int)((pe * pe * (g.C / V) + WG * FU - 1) / (WG * FU)); };
+    const int Gh = pieces(g.bs + 2), Gl = pieces(g.bs / 2 + 2);
+    const long long blocks = (long long)hi_cap * Gh + (long long)lo_cap * Gl;
+    if (blocks == 0) return hipSuccess;
+    hipLaunchKernelGGL((k_split_pad<T, L, V>), dim3((unsigned)blocks), dim3(WG), 0, st, g, mask, (const T*)x, (T*)hp,
+                       (T*)lp, hi_cap, lo_cap, pm, Gh, Gl);
+    return hipGetLastError();
+}
+
+template <typename T, int L, int V>
+hipError_t pad_split_bwd_v(const Geo& g, const void* dhp, const void* dlp, const uint8_t* mask, void* dx, int hi_cap,
+                           int lo_cap, int pm, hipStream_t st) {
+    const int G = (int)(((long long)g.bs * g.bs * (g.C / V) + WG * FU - 1) / (WG * FU));
+    hipLaunchKernelGGL((k_pad_split_bwd<T, L, V>), dim3((unsigned)(g.B * G)), dim3(WG), 0, st, g, mask, (const T*)dhp,
+                       (const T*)dlp, (T*)dx, hi_cap, lo_cap, pm, G);
+    return hipGetLastError();
+}
+
+template <typename T>
+bool whole_vectors(int layout, const Geo& g, std::initializer_list<const void*> ps) {
+    uintptr_t any = 0;
+    for (const void* p : ps) any |= reinterpret_cast<uintptr_t>(p);
+    return layout == NHWC && g.C % (16 / (int)sizeof(T)) == 0 && (any & 15) == 0;
+}
+
+template <typename T>
+hipError_t split_pad_t(int layout, const Geo& g, const void* x, const uint8_t* mask, void* hp, void* lp, int hi_cap,
+                       int lo_cap, int pm, hipStream_t st) {
+    if (whole_vectors<T>(layout, g, {x, hp, lp}))
+        return split_pad_v<T, NHWC, 16 / (int)sizeof(T)>(g, x, mask, hp, lp, hi_cap, lo_cap, pm, st);
+    if (layout == NHWC) return split_pad_v<T, NHWC, 1>(g, x, mask, hp, lp, hi_cap, lo_cap, pm, st);
+    return split_pad_v<T, NCHW, 1>(g, x, mask, hp, lp, hi_cap, lo_cap, pm, st);
+}
+
+template <typename T>
+hipError_t pad_split_bwd_t(int layout, const Geo& g, const void* dhp, const void* dlp, const uint8_t* mask, void* dx,
+                           int hi_cap, int lo_cap, int pm, hipStream_t st) {
+    if (whole_vectors<T>(layout, g, {dhp, dlp, dx}))
+        return pad_split_bwd_v<T, NHWC, 16 / (int)sizeof(T)>(g, dhp, dlp, mask, dx, hi_cap, lo_cap, pm, st);
+    if (layout == NHWC) return pad_split_bwd_v<T, NHWC, 1>(g, dhp, dlp, mask, dx, hi_cap, lo_cap, pm, st);
+    return pad_split_bwd_v<T, NCHW, 1>(g, dhp, dlp, mask, dx, hi_cap, lo_cap, pm, st);
+}
+
 template <typename T, int L>
 hipError_t dgrad_t(const Geo& g, const void* dho, const void* dlo, const uint8_t* mask, const void* w, int C_in,
                    int C_out, void* dhp, void* dlp, int hi_cap, int lo_cap, Ws ws, hipStream_t st) {
@@ -864,6 +1059,24 @@ hipError_t launch_pad_bwd(int dtype, int layout, const Geo& g, const void* dhp, 
     case 0: return pad_bwd_t<float>(layout, g, dhp, dlp, mask, dhi, dlo, hi_cap, lo_cap, pm, st);
     case 1: return pad_bwd_t<f16>(layout, g, dhp, dlp, mask, dhi, dlo, hi_cap, lo_cap, pm, st);
     default: return pad_bwd_t<bf16>(layout, g, dhp, dlp, mask, dhi, dlo, hi_cap, lo_cap, pm, st);
+    }
+}
+
+hipError_t launch_split_pad(int dtype, int layout, const Geo& g, const void* x, const uint8_t* mask, void* hp, void* lp,
+                            int hi_cap, int lo_cap, int pm, hipStream_t st) {
+    switch (dtype) {
+    case 0: return split_pad_t<float>(layout, g, x, mask, hp, lp, hi_cap, lo_cap, pm, st);
+    case 1: return split_pad_t<f16>(layout, g, x, mask, hp, lp, hi_cap, lo_cap, pm, st);
+    default: return split_pad_t<bf16>(layout, g, x, mask, hp, lp, hi_cap, lo_cap, pm, st);
+    }
+}
+
+hipError_t launch_pad_split_bwd(int dtype, int layout, const Geo& g, const void* dhp, const void* dlp,
+                                const uint8_t* mask, void* dx, int hi_cap, int lo_cap, int pm, hipStream_t st) {
+    switch (dtype) {
+    case 0: return pad_split_bwd_t<float>(layout, g, dhp, dlp, mask, dx, hi_cap, lo_cap, pm, st);
+    case 1: return pad_split_bwd_t<f16>(layout, g, dhp, dlp, mask, dx, hi_cap, lo_cap, pm, st);
+    default: return pad_split_bwd_t<bf16>(layout, g, dhp, dlp, mask, dx, hi_cap, lo_cap, pm, st);
     }
 }
 

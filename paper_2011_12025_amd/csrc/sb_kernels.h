@@ -135,6 +135,12 @@ hipError_t launch_maxpool(int dtype, const void* x, int N, int C, int H, int W, 
 // are launch_split / launch_combine with bwd.
 hipError_t launch_pad_bwd(int dtype, int layout, const Geo& g, const void* dhp, const void* dlp, const uint8_t* mask,
                           void* dhi, void* dlo, int hi_cap, int lo_cap, int pm, hipStream_t st);
+// Both neighbours of the convolution's backward pass in one kernel each: split
+// and pad of the map, pad and split transposed into the map's gradient.
+hipError_t launch_split_pad(int dtype, int layout, const Geo& g, const void* x, const uint8_t* mask, void* hp, void* lp,
+                            int hi_cap, int lo_cap, int pm, hipStream_t st);
+hipError_t launch_pad_split_bwd(int dtype, int layout, const Geo& g, const void* dhp, const void* dlp,
+                                const uint8_t* mask, void* dx, int hi_cap, int lo_cap, int pm, hipStream_t st);
 size_t dgrad_ws_bytes(int dtype, int layout, const Geo& g, int C_in, int C_out, int hi_cap, int lo_cap);
 hipError_t launch_dgrad(int dtype, int layout, const Geo& g, const void* dho, const void* dlo, const uint8_t* mask,
                         const void* w, int C_in, int C_out, void* dhp, void* dlp, int hi_cap, int lo_cap, Ws ws,

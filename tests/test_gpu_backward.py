@@ -148,3 +148,32 @@ def test_layer_backward(c, sampling):
     npx = c.N * c.H * c.W
     assert_conv_close(dw, rdw, c.dtype, npx, "dw")
     assert_conv_close(db, rdb, c.dtype, npx, "db")
+
+
+@pytest.mark.parametrize("sampling", ["avg", "strided", "zero"])
+@pytest.mark.parametrize("layout", ["nchw", "nhwc"])
+@pytest.mark.parametrize("c,short", [(c, 0) for c in CASES] + [(CASES[0], 2), (CASES[2], 3)],
+                         ids=lambda v: v.name if isinstance(v, Case) else str(v))
+def test_fused_first_and_last_step(c, short, layout, sampling):
+    """split_pad and pad_split_backward against the two calls each stands for,
+    bit for bit, also with stacks that lack room for some blocks."""
+    import paper_2011_12025_amd as sb
+    mask, x, w, b = make_inputs(c)
+    md, xd = torch.from_numpy(mask).cuda(), to_dev(x, layout)
+    lay = 1 if layout == "nhwc" else 0
+    nh, nl = (max(0, int(n) - short) for n in (mask.sum(), mask.size - mask.sum()))
+    log(f"[fused split/pad] {c.name} {layout} {sampling} {nh}/{nl}")
+    got = sb.split_pad(xd, md, c.bs, counts=(nh, nl), layout=lay, sampling=sampling)
+    ref = sb.pad(*sb.split(xd, md, c.bs, counts=(nh, nl), layout=lay), md, c.bs, c.H, c.W, layout=lay,
+                 sampling=sampling)
+    torch.cuda.synchronize()
+    for g, r in zip(got, ref):
+        assert g.shape == r.shape and torch.equal(g, r)
+    lb = c.bs // 2
+    gh = up(_grad(c.seed + 5, (nh, c.C, c.bs + 2, c.bs + 2), c.dtype), c.dtype, layout)
+    gl = up(_grad(c.seed + 6, (nl, c.C, lb + 2, lb + 2), c.dtype), c.dtype, layout)
+    dx = sb.pad_split_backward(gh, gl, md, c.bs, c.H, c.W, layout=lay, sampling=sampling)
+    ref = sb.split_backward(*sb.pad_backward(gh, gl, md, c.bs, c.H, c.W, layout=lay, sampling=sampling), md, c.bs, c.H,
+                            c.W, layout=lay)
+    torch.cuda.synchronize()
+    assert torch.equal(dx, ref)
