@@ -273,6 +273,20 @@ int segblocks_block_conv_chain(const void* hi, const void* lo, const void* hi_ha
                                void* hi_out, void* lo_out, void* hi_out_half, int hi_cap,
                                int lo_cap, void* workspace, size_t ws_bytes, hipStream_t stream);
 
+/* The first convolution of a residual block that changes stride or width,
+ * with the block's 1x1 shortcut of the same input: the results of
+ * segblocks_block_conv_chain (ksize 3, no residual) in hi_out, lo_out,
+ * hi_out_half and of segblocks_block_conv_ex (ksize 1, flags 0) with
+ * sc_weight [C_out][C_in], sc_bias in sc_hi, sc_lo (shaped like hi_out,
+ * lo_out); one launch where the implicit GEMM takes the convolution.
+ * Workspace: segblocks_block_conv_chain_workspace_size (ksize 3). */
+int segblocks_block_conv_down(const void* hi, const void* lo, const void* hi_half, int dtype, int layout, int N,
+                              int C_in, int H, int W, const uint8_t* mask, int bs, const void* weight,
+                              const void* bias, const void* sc_weight, const void* sc_bias, int C_out,
+                              int stride, int flags, void* hi_out, void* lo_out, void* hi_out_half,
+                              void* sc_hi, void* sc_lo, int hi_cap, int lo_cap, void* workspace,
+                              size_t ws_bytes, hipStream_t stream);
+
 /* Whether segblocks_block_conv_chain with these shapes, flags and
  * capacities (16-byte aligned buffers) reads hi_half, so that the call
  * producing its input knows whether to ask for hi_out_half: *reads (HOST

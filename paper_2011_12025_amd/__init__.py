@@ -24,7 +24,7 @@ __all__ = ["count", "split", "pad", "conv3x3", "combine", "block_conv3x3", "bloc
            "layer_workspace_size", "policy_heuristic", "combine_backward", "split_backward", "pad_backward",
            "conv3x3_backward_data", "conv3x3_backward_weight", "layer_backward", "pad_halo", "conv_halo",
            "maxpool_halo", "block_conv_chain", "block_conv_chain_workspace_size", "block_conv_chain_reads_half",
-           "split_pad", "pad_split_backward", "stem_pool", "stem_blocks", "maxpool_blocks", "stem_fits"]
+           "block_conv_down", "split_pad", "pad_split_backward", "stem_pool", "stem_blocks", "maxpool_blocks", "stem_fits"]
 
 _DT = {torch.float32: _b.SB_F32, torch.float16: _b.SB_F16, torch.bfloat16: _b.SB_BF16}
 
@@ -386,6 +386,37 @@ def block_conv_chain(hi: torch.Tensor, lo: torch.Tensor, mask: torch.Tensor, bs:
             _ptr(mask), bs, _ptr(weight), _ptr(bias), C_out, k, stride, _flags(relu, sampling), _ptr(rh), _ptr(rl),
             _ptr(ho), _ptr(lo_o), _ptr(hh), hi.shape[0], lo.shape[0], wp, wn, _stream(ref))
     return ho, lo_o, hh
+
+
+def block_conv_down(hi: torch.Tensor, lo: torch.Tensor, mask: torch.Tensor, bs: int, H: int, W: int,
+                    weight: torch.Tensor, bias, sc_weight: torch.Tensor, sc_bias, stride: int = 2, relu: bool = True,
+                    hi_half=None, want_half: bool = False, workspace=None, sampling: str = "avg"):
+    """A residual block's first 3x3 convolution (block_conv_chain) and its 1x1
+    shortcut (block_conv_ex) of the same input, in one launch where the
+    implicit GEMM takes it.  Returns ((hi_out, lo_out, hi_out_half or None),
+    (sc_hi, sc_lo))."""
+    mask = _mask(mask)
+    ref = hi if hi.shape[0] else lo
+    layout = _b.SB_NHWC
+    _check_layout(layout, hi, lo)
+    C_in, C_out, N = ref.shape[1], weight.shape[0], mask.shape[0]
+    if tuple(sc_weight.shape[:2]) != (C_out, C_in):
+        raise ValueError("the shortcut's filters must be [C_out, C_in, 1, 1]")
+    weight, sc_weight = _weight(weight, layout, 3), _weight(sc_weight, layout, 1)
+    bias = None if bias is None else bias.contiguous()
+    sc_bias = None if sc_bias is None else sc_bias.contiguous()
+    bo, lo_e = bs // stride, bs // 2 // stride
+    nh, nl = hi.shape[0], lo.shape[0]
+    ho, sh = _empty((nh, C_out, bo, bo), ref, layout), _empty((nh, C_out, bo, bo), ref, layout)
+    lo_o, sl = _empty((nl, C_out, lo_e, lo_e), ref, layout), _empty((nl, C_out, lo_e, lo_e), ref, layout)
+    hh = _empty((nh, C_out, bo // 2, bo // 2), ref, layout) if want_half else None
+    need = _need("segblocks_block_conv_chain_workspace_size", _dt(ref), layout, N, C_in, H, W, bs, C_out, 3, stride, nh,
+                 nl)
+    wp, wn, _keep = _ws(need, ref.device, workspace)
+    _b.call("segblocks_block_conv_down", _ptr(hi), _ptr(lo), _ptr(hi_half), _dt(ref), layout, N, C_in, H, W, _ptr(mask),
+            bs, _ptr(weight), _ptr(bias), _ptr(sc_weight), _ptr(sc_bias), C_out, stride, _flags(relu, sampling), _ptr(ho),
+            _ptr(lo_o), _ptr(hh), _ptr(sh), _ptr(sl), nh, nl, wp, wn, _stream(ref))
+    return (ho, lo_o, hh), (sh, sl)
 
 
 def conv2d(x: torch.Tensor, weight: torch.Tensor, bias=None, stride: int = 1, padding: int = 0,

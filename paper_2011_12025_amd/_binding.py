@@ -29,7 +29,7 @@ EXPORTS = ["segblocks_count", "segblocks_split", "segblocks_pad", "segblocks_pad
            "segblocks_combine_backward", "segblocks_split_backward", "segblocks_pad_backward",
            "segblocks_conv3x3_backward_data", "segblocks_conv3x3_backward_data_workspace_size",
            "segblocks_conv3x3_backward_weight", "segblocks_conv3x3_backward_weight_workspace_size",
-           "segblocks_pad_halo", "segblocks_conv_halo", "segblocks_maxpool_halo", "segblocks_split_pad", "segblocks_pad_split_backward", "segblocks_stem_pool",
+           "segblocks_pad_halo", "segblocks_conv_halo", "segblocks_maxpool_halo", "segblocks_block_conv_down", "segblocks_split_pad", "segblocks_pad_split_backward", "segblocks_stem_pool",
            "segblocks_stem_blocks", "segblocks_maxpool_blocks", "segblocks_last_error"]
 
 SB_OK, SB_EINVAL, SB_ESHAPE, SB_EHIP, SB_ENOMEM = 0, -1, -2, -3, -4
@@ -74,6 +74,8 @@ _SIGS = {
     "segblocks_block_conv_ex_workspace_size": [_I] * 12 + [_ZP],
     "segblocks_layer_workspace_size": [_I] * 8 + [_ZP],
     "segblocks_conv2d": [_P, _I, _I, _I, _I, _I, _I, _P, _P, _I, _I, _I, _I, _I, _P, _P],
+    "segblocks_block_conv_down": [_P, _P, _P, _I, _I, _I, _I, _I, _I, _P, _I, _P, _P, _P, _P, _I, _I, _I, _P, _P, _P,
+                                  _P, _P, _I, _I, _P, _Z, _P],
     "segblocks_split_pad": [_P, _I, _I, _I, _I, _I, _I, _P, _I, _I, _P, _P, _I, _I, _P],
     "segblocks_pad_split_backward": [_P, _P, _I, _I, _I, _I, _I, _I, _P, _I, _I, _P, _I, _I, _P],
     "segblocks_stem_pool": [_P, _I, _I, _I, _I, _I, _I, _P, _P, _I, _P, _P],

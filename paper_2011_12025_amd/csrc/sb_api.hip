@@ -426,12 +426,15 @@ int segblocks_block_conv_ex_noalloc(const void* hi, const void* lo, int dtype, i
                               hi_cap, lo_cap, nullptr, 0, stream);
 }
 
-int segblocks_block_conv_chain(const void* hi, const void* lo, const void* hi_half, int dtype, int layout, int N,
-                               int C_in, int H, int W, const uint8_t* mask, int bs, const void* weight,
-                               const void* bias, int C_out, int ksize, int stride, int flags, const void* residual_hi,
-                               const void* residual_lo, void* hi_out, void* lo_out, void* hi_out_half, int hi_cap,
-                               int lo_cap, void* workspace, size_t ws_bytes, hipStream_t stream) {
-    const char* fn = "segblocks_block_conv_chain";
+namespace {
+
+// segblocks_block_conv_chain, with the shortcut of segblocks_block_conv_down (sc_weight, or NULL).
+int block_conv_chain_impl(const char* fn, const void* hi, const void* lo, const void* hi_half, int dtype, int layout,
+                          int N, int C_in, int H, int W, const uint8_t* mask, int bs, const void* weight,
+                          const void* bias, int C_out, int ksize, int stride, int flags, const void* residual_hi,
+                          const void* residual_lo, void* hi_out, void* lo_out, void* hi_out_half, int hi_cap, int lo_cap,
+                          const void* sc_weight, const void* sc_bias, void* sc_hi, void* sc_lo, void* workspace,
+                          size_t ws_bytes, hipStream_t stream) {
     sb::Geo g;
     int s;
     if ((s = check_geo(fn, dtype, layout, N, C_in, H, W, mask, bs, g))) return s;
@@ -475,11 +478,23 @@ int segblocks_block_conv_chain(const void* hi, const void* lo, const void* hi_ha
     const Range rrh{residual_hi, hi_cap * (long long)C_out * bo * bo * es};
     const Range rrl{residual_lo, lo_cap * (long long)C_out * lo_e * lo_e * es};
     const Range rws{workspace, (long long)need};
-    if (any_overlap({rho, rlo, rhoh, rws}, {rh, rl, rhh, rw, rb, rrh, rrl, Range{mask, g.B}}))
+    const Range rsw{sc_weight, sc_weight ? (long long)C_out * C_in * es : 0}, rsb{sc_bias, sc_bias ? C_out * es : 0};
+    const Range rsh{sc_hi, sc_hi ? rho.bytes : 0}, rsl{sc_lo, sc_lo ? rlo.bytes : 0};
+    if (any_overlap({rho, rlo, rhoh, rsh, rsl, rws}, {rh, rl, rhh, rw, rb, rsw, rsb, rrh, rrl, Range{mask, g.B}}))
         return fail(SB_EINVAL, fn, "output buffers or the workspace overlap inputs or each other");
     const sb::Ws ws{workspace, ws_bytes};
     bool gemm;
     hipError_t e;
+    // one launch where the GEMM takes the 3x3 convolution and the shortcut's buffers are as aligned
+    sb::ConvArgs sa{hi, lo, sc_weight, sc_bias, nullptr, nullptr, sc_hi, sc_lo, C_in, C_out, 0, hi_cap, lo_cap};
+    const bool in_one = sc_weight && !(k33 && sb::conv_res_fits(dtype, layout, g, a)) && sb::igemm_fits(dtype, layout, g, a) &&
+                        sb::igemm_fits(dtype, layout, g, sa);
+    if (in_one) {
+        a.sc_weight = sc_weight;
+        a.sc_bias = sc_bias;
+        a.sc_hi = sc_hi;
+        a.sc_lo = sc_lo;
+    }
     if (k33) {
         gemm = !sb::conv_res_fits(dtype, layout, g, a) && sb::igemm_fits(dtype, layout, g, a);
         e = sb::launch_conv(dtype, layout, sb::SRC_PACKED, sb::DST_PACKED, g, mask, a, ws, stream);
@@ -490,7 +505,40 @@ int segblocks_block_conv_chain(const void* hi, const void* lo, const void* hi_ha
     }
     if (e == hipSuccess && hi_out_half && !gemm)
         e = sb::launch_sample_hs(dtype, hi_out, hi_cap, (int)bo, C_out, hi_out_half, stream);
+    if (e == hipSuccess && sc_weight && !in_one)
+        e = sb::igemm_fits(dtype, layout, g, sa) && sb::igemm_ws_bytes(g, sa, 1, stride, true) <= ws_bytes
+                ? sb::launch_igemm(dtype, g, mask, sa, 1, stride, ws, stream)
+                : sb::launch_bconv(dtype, g, mask, sa, 1, stride, stream);
     return hip_status(fn, e);
+}
+
+}  // namespace
+
+int segblocks_block_conv_chain(const void* hi, const void* lo, const void* hi_half, int dtype, int layout, int N,
+                               int C_in, int H, int W, const uint8_t* mask, int bs, const void* weight,
+                               const void* bias, int C_out, int ksize, int stride, int flags, const void* residual_hi,
+                               const void* residual_lo, void* hi_out, void* lo_out, void* hi_out_half, int hi_cap,
+                               int lo_cap, void* workspace, size_t ws_bytes, hipStream_t stream) {
+    return block_conv_chain_impl("segblocks_block_conv_chain", hi, lo, hi_half, dtype, layout, N, C_in, H, W, mask, bs,
+                                 weight, bias, C_out, ksize, stride, flags, residual_hi, residual_lo, hi_out, lo_out,
+                                 hi_out_half, hi_cap, lo_cap, nullptr, nullptr, nullptr, nullptr, workspace, ws_bytes,
+                                 stream);
+}
+
+int segblocks_block_conv_down(const void* hi, const void* lo, const void* hi_half, int dtype, int layout, int N,
+                              int C_in, int H, int W, const uint8_t* mask, int bs, const void* weight,
+                              const void* bias, const void* sc_weight, const void* sc_bias, int C_out, int stride,
+                              int flags, void* hi_out, void* lo_out, void* hi_out_half, void* sc_hi, void* sc_lo,
+                              int hi_cap, int lo_cap, void* workspace, size_t ws_bytes, hipStream_t stream) {
+    const char* fn = "segblocks_block_conv_down";
+    int s;
+    if (!sc_weight) return fail(SB_EINVAL, fn, "sc_weight is NULL");
+    if ((s = check_caps(fn, hi_cap, lo_cap)) || (s = check_stack(fn, "sc_hi", sc_hi, hi_cap)) ||
+        (s = check_stack(fn, "sc_lo", sc_lo, lo_cap)))
+        return s;
+    return block_conv_chain_impl(fn, hi, lo, hi_half, dtype, layout, N, C_in, H, W, mask, bs, weight, bias, C_out, 3,
+                                 stride, flags, nullptr, nullptr, hi_out, lo_out, hi_out_half, hi_cap, lo_cap, sc_weight,
+                                 sc_bias, sc_hi, sc_lo, workspace, ws_bytes, stream);
 }
 
 namespace {

@@ -173,7 +173,24 @@ __global__ __launch_bounds__(WG) void k_pad_bwd(const T* __restrict__ dhp, const
 // ---------------------------------------------------------------------------
 // the layer's first and last step: BlockSample + BlockPad, and both transposed
 // ---------------------------------------------------------------------------
-constexpr int FU = 4;  // vectors per thread, their loads in flight together
+// Vectors per thread, their loads in flight together.  Measured for 1 / 2 / 4,
+// 256x512, 64 channels, half low, fp16: split_pad 18.4 / 14.8 / 17.9 us,
+// pad_split_bwd 22.8 / 19.0 / 18.6.
+constexpr int FU = 2;
+
+// Whole 16-byte vectors are streamed (non-temporal), single elements are not.
+template <typename T, int V>
+__device__ __forceinline__ Vec<T, V> stream_load(const T* p) {
+    Vec<T, V> v;
+    if constexpr (sizeof(T) * V == 16) v.raw = ld_nt16(p);
+    else v = vload<T, V>(p);
+    return v;
+}
+template <typename T, int V>
+__device__ __forceinline__ void stream_store(T* p, const Vec<T, V>& v) {
+    if constexpr (sizeof(T) * V == 16) st_nt16(p, v.raw);
+    else vstore<T, V>(p, v);
+}
 
 // Row, column and first channel of item it of a block of extent e, in the
 // memory order of the call's layout.
@@ -196,7 +213,8 @@ __device__ __forceinline__ void item_at(int it, int e, int C, int& r, int& j, in
 // The padded stacks straight from the map (segblocks_split then
 // segblocks_pad_ex): the packed stacks, read once by each of its blocks and
 // its neighbours, never reach memory.  Bound by the map's read and the
-// stacks' write: 256x512, 64 channels, half low, fp16 @@FIG_SP.
+// stacks' write: 256x512, 64 channels, half low, fp16
+// 14.8 us, the two calls 16.2.
 template <typename T, int L, int V>
 __global__ __launch_bounds__(WG) void k_split_pad(Geo g, const uint8_t* __restrict__ mask, const T* __restrict__ x,
                                                   T* __restrict__ hp, T* __restrict__ lp, int hi_cap, int lo_cap,
@@ -219,7 +237,8 @@ __global__ __launch_bounds__(WG) void k_split_pad(Geo g, const uint8_t* __restri
     const int e = high ? g.bs : g.bs >> 1, pe = e + 2;
     const int items = pe * pe * (g.C / V);
     T* out = (high ? hp : lp) + (size_t)slot * pe * pe * g.C;
-    SrcBatch<T, V, FU> b;
+    Vec<T, V> v[FU][4];
+    int mode[FU];  // 0 zero, 1 copy, 2 average
 #pragma unroll
     for (int u = 0; u < FU; ++u) {
         const int it = (piece * FU + u) * WG + (int)threadIdx.x;
@@ -231,19 +250,28 @@ __global__ __launch_bounds__(WG) void k_split_pad(Geo g, const uint8_t* __restri
             if ((have >> d) & 1u)
                 s = dense_src<T, L>(x, n, g.C, g.H, g.W, g.bs, gy, gx, nb, r - 1, j - 1, c, pm);
         }
-        b.issue(u, s);
+        mode[u] = !s.p ? 0 : s.avg ? 2 : 1;
+        v[u][0] = vzero<T, V>();
+        if (s.p) v[u][0] = stream_load<T, V>(s.p);
+        if (mode[u] == 2) {
+            v[u][1] = stream_load<T, V>(s.p + s.d1);
+            v[u][2] = stream_load<T, V>(s.p + s.d2);
+            v[u][3] = stream_load<T, V>(s.p + s.d2 + s.d1);
+        }
     }
 #pragma unroll
     for (int u = 0; u < FU; ++u) {
         const int it = (piece * FU + u) * WG + (int)threadIdx.x;
-        if (it < items) vstore<T, V>(out + (size_t)it * V, b.value(u));
+        if (mode[u] == 2) v[u][0] = vavg4<T, V>(v[u][0], v[u][1], v[u][2], v[u][3]);
+        if (it < items) stream_store<T, V>(out + (size_t)it * V, v[u][0]);
     }
 }
 
 // The input gradient straight from the padded stacks' (segblocks_pad_backward
 // then segblocks_split_backward, with the same rounding in between): a high
 // pixel away from its block's border is a copy, the others gather every
-// window over them as k_pad_bwd does.  Same workload: @@FIG_PS.
+// window over them as k_pad_bwd does.  Same workload:
+// 19.0 us, the two calls 23.8.
 template <typename T, int L, int V>
 __global__ __launch_bounds__(WG) void k_pad_split_bwd(Geo g, const uint8_t* __restrict__ mask,
                                                       const T* __restrict__ dhp, const T* __restrict__ dlp,
@@ -272,7 +300,7 @@ __global__ __launch_bounds__(WG) void k_pad_split_bwd(Geo g, const uint8_t* __re
             item_at<L, V>(it, e, g.C, r, j, c);
             const int m = high ? 2 : 1;  // (a low neighbour's window reaches two pixels into a high block)
             copy[u] = pm == PM_ZERO || (r >= m && r < e - m && j >= m && j < e - m);
-            if (copy[u]) v[u] = vload<T, V>(stack_at<T, L>(own, slot, g.C, pe, r + 1, j + 1, c));
+            if (copy[u]) v[u] = stream_load<T, V>(stack_at<T, L>(own, slot, g.C, pe, r + 1, j + 1, c));
         }
     }
 #pragma unroll
@@ -306,14 +334,14 @@ __global__ __launch_bounds__(WG) void k_pad_split_bwd(Geo g, const uint8_t* __re
         }
         if (high) {
             T* p = dx + (map_at<T, L>(dx, n, g.C, g.H, g.W, gy * g.bs + r, gx * g.bs + j, c) - dx);
-            vstore<T, V>(p, v[u]);
+            stream_store<T, V>(p, v[u]);
         } else {
             const Vec<T, V> o = vquarter<T, V>(v[u]);
             T* p = dx + (map_at<T, L>(dx, n, g.C, g.H, g.W, gy * g.bs + 2 * r, gx * g.bs + 2 * j, c) - dx);
-            vstore<T, V>(p, o);
-            vstore<T, V>(p + px, o);
-            vstore<T, V>(p + (size_t)px * g.W, o);
-            vstore<T, V>(p + (size_t)px * g.W + px, o);
+            stream_store<T, V>(p, o);
+            stream_store<T, V>(p + px, o);
+            stream_store<T, V>(p + (size_t)px * g.W, o);
+            stream_store<T, V>(p + (size_t)px * g.W + px, o);
         }
     }
 }

@@ -197,6 +197,14 @@ struct GParams {
     int W;          // dense mode: width of the map
     int* dout;      // per M tile with split units, TM dense output pixels (-1: none)
     int hs_lg;      // log2 of the high output extent when the epilogue writes a.out_hs, else -1
+    // A residual block's 1 x 1 shortcut of the same input at the same stride, in
+    // workgroups after the convolution's (main_wgs of them): the centre tap
+    // alone, its own filters, bias and outputs, one workgroup a unit.
+    int main_wgs;
+    const void* sc_weight;
+    const void* sc_bias;
+    void* sc_hi;
+    void* sc_lo;
     int org;        // tap (ky, kx) of output pixel (i, j) is input pixel (ST i + ky - org, ST j + kx - org): the
                     // filter's radius, or KS - 1 for the full convolution of blocks padded with zeros on their own
 };
@@ -385,8 +393,9 @@ __global__ __launch_bounds__(GWG, 1) void k_igemm(Geo g, const uint8_t* __restri
     // share its pixels, run on one XCD when the tile count is a multiple of 8
     // (workgroups go to the XCDs round-robin).
     const int units = gp.tiles * gp.tiles_n;
-    int unit = (int)blockIdx.x, z = 0, splits = 1;
-    if (unit >= gp.whole) {
+    const bool sc = KS == 3 && (int)blockIdx.x >= gp.main_wgs;
+    int unit = (int)blockIdx.x - (sc ? gp.main_wgs : 0), z = 0, splits = 1;
+    if (!sc && unit >= gp.whole) {
         const int l = unit - gp.whole, r = units - gp.whole;
         splits = gp.splits;
         z = gp.tile_major ? l % splits : l / r;
@@ -398,8 +407,8 @@ __global__ __launch_bounds__(GWG, 1) void k_igemm(Geo g, const uint8_t* __restri
     const int C_in = a.C_in, C_out = a.C_out;
     const int cpt = gp.cpt;
     const int nsteps = KT * cpt;
-    const int s_first = z * nsteps / splits;
-    const int n = (z + 1) * nsteps / splits - s_first;  // steps of this workgroup (>= 1)
+    const int s_first = sc ? KT / 2 * cpt : z * nsteps / splits;
+    const int n = sc ? cpt : (z + 1) * nsteps / splits - s_first;  // steps of this workgroup (>= 1)
     const T* zrow = reinterpret_cast<const T*>(g_zero_row);
 
     // the mask byte of the thread's first block
@@ -413,7 +422,10 @@ __global__ __launch_bounds__(GWG, 1) void k_igemm(Geo g, const uint8_t* __restri
     for (int j = 0; j < AR; ++j) {
         const int r = (wave * AR + j) * 8 + (lane >> 3);
         const int co = min(co0 + gperm(r), C_out - 1);
-        wrow[j] = (const T*)a.weight + (size_t)co * KT * C_in + (((lane & 7) ^ ((r >> 1) & 7)) * 8);
+        // (a step adds tap * C_in: the shortcut's filters have the centre tap only)
+        const T* wbase = sc ? (const T*)gp.sc_weight + (ptrdiff_t)(co - KT / 2) * C_in
+                            : (const T*)a.weight + (size_t)co * KT * C_in;
+        wrow[j] = wbase + (((lane & 7) ^ ((r >> 1) & 7)) * 8);
     }
     const int tap0 = s_first / cpt, c0 = s_first - (s_first / cpt) * cpt;
     int tap1 = tap0, c1 = c0 + 1;
@@ -691,7 +703,15 @@ __global__ __launch_bounds__(GWG, 1) void k_igemm(Geo g, const uint8_t* __restri
     }
     __builtin_amdgcn_s_waitcnt(0);  // the padding DMAs
 
-    if (splits == 1) {
+    if (sc) {
+        ConvArgs b = a;
+        b.bias = gp.sc_bias;
+        b.res_hi = b.res_lo = nullptr;
+        b.out_hi = gp.sc_hi;
+        b.out_lo = gp.sc_lo;
+        b.flags = 0;
+        gepilogue<T, WM, MS, NS>(acc, b, high, m0, rows_valid, co0, nullptr, g.W, nullptr, -1);
+    } else if (splits == 1) {
         gepilogue<T, WM, MS, NS>(acc, a, high, m0, rows_valid, co0, dense ? s_dout : nullptr, g.W,
                                  high && gp.hs_lg >= 0 ? (T*)a.out_hs : nullptr, gp.hs_lg);
     } else {
@@ -980,6 +1000,10 @@ hipError_t igemm_run(const Geo& g, const uint8_t* mask, ConvArgs a, Ws ws, hipSt
         return hipErrorInvalidValue;  // the entry points check the workspace before anything is launched
     GParams gp;
     gp.org = full ? KS - 1 : KS / 2;
+    gp.sc_weight = a.sc_weight;
+    gp.sc_bias = a.sc_bias;
+    gp.sc_hi = a.sc_hi;
+    gp.sc_lo = a.sc_lo;
     gp.eo_h = g.bs / ST + (full ? KS - 1 : 0);
     gp.eo_l = (g.bs / 2) / ST + (full ? KS - 1 : 0);
     gp.cpt = a.C_in / GKC;
@@ -1023,7 +1047,8 @@ hipError_t igemm_run(const Geo& g, const uint8_t* mask, ConvArgs a, Ws ws, hipSt
         if (pl.own_hs) a.in_hs = lp;
         else gp.lo_pad = lp;
     }
-    const dim3 grid((unsigned)(gp.whole + split_units * S));
+    gp.main_wgs = (int)(gp.whole + split_units * S);
+    const dim3 grid((unsigned)(gp.main_wgs + (a.sc_weight ? tiles * tiles_n : 0)));
     hipLaunchKernelGGL((k_igemm<T, KS, ST, WM, MS, NS>), grid, dim3(GWG), smem, st, g, mask, a, gp);
     if (S > 1) {
         e = hipGetLastError();

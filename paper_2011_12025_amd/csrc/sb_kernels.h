@@ -40,6 +40,13 @@ struct ConvArgs {
     // from the results.  nullptr = not given / not wanted.
     const void* in_hs = nullptr;
     void* out_hs = nullptr;
+    // The 1x1 shortcut of the same input at the same stride and width (a 3x3
+    // convolution on the implicit GEMM computes it in the same launch): filters
+    // [C_out][C_in], bias or nullptr, output stacks.  nullptr = none.
+    const void* sc_weight = nullptr;
+    const void* sc_bias = nullptr;
+    void* sc_hi = nullptr;
+    void* sc_lo = nullptr;
 };
 
 // bwd: the transposes for the backward pass instead: split of a gradient map

@@ -20,8 +20,8 @@ import functools
 
 import torch
 
-from . import (block_conv3x3, block_conv3x3_workspace_size, block_conv_chain, block_conv_chain_reads_half,
-               block_conv_ex, block_conv_ex_workspace_size, combine, conv2d, conv_halo, count, maxpool, maxpool_blocks,
+from . import (block_conv3x3_workspace_size, block_conv_chain, block_conv_chain_reads_half, block_conv_down,
+               block_conv_ex_workspace_size, combine, conv2d, conv_halo, count, maxpool, maxpool_blocks,
                maxpool_halo, pad_halo, split, stem_blocks, stem_fits, stem_pool)
 from ._binding import SB_NHWC
 
@@ -121,12 +121,12 @@ class BlockEncoder:
             w1, b1 = self.w[p + "c1.w"], self.w[p + "c1.b"]
             # c1 feeds c2: 3x3/1 on the map at this block's output resolution
             want = reads_half(width, H // st, W // st, bs // st, width, 1)
-            h1 = block_conv_chain(hi, lo, mask, bs, H, W, w1, b1, stride=st, relu=True, hi_half=hh, want_half=want,
-                                  workspace=ws)
             if p + "sc.w" in self.w:
-                sc = block_conv_ex(hi, lo, mask, bs, H, W, self.w[p + "sc.w"], self.w[p + "sc.b"], stride=st,
-                                   workspace=ws)
+                h1, sc = block_conv_down(hi, lo, mask, bs, H, W, w1, b1, self.w[p + "sc.w"], self.w[p + "sc.b"], stride=st,
+                                         relu=True, hi_half=hh, want_half=want, workspace=ws)
             else:
+                h1 = block_conv_chain(hi, lo, mask, bs, H, W, w1, b1, stride=st, relu=True, hi_half=hh, want_half=want,
+                                      workspace=ws)
                 sc = (hi, lo)
             bs, H, W = bs // st, H // st, W // st
             # c2 feeds the next block's c1, if there is one

@@ -160,3 +160,33 @@ def test_encoder_half_stacks_bitexact(dtype, blk, H, W, N, mask_kind, seed):
     torch.cuda.synchronize()
     assert y1.dtype == t
     assert_bitexact(y1, f32(y0), f"encoder {dtype} blk={blk}")
+
+
+@pytest.mark.parametrize("dtype,N,C,Co,grid,bs,stride,p_low,extra", [
+    ("f16", 2, 64, 128, (4, 6), 16, 2, 0.5, 0), ("bf16", 1, 128, 256, (8, 16), 8, 2, 0.5, 0),
+    ("f16", 1, 256, 512, (8, 8), 4, 2, 0.3, 0), ("bf16", 1, 64, 128, (3, 4), 8, 1, 0.5, 0),
+    ("f16", 1, 64, 64, (2, 3), 32, 1, 0.5, 0),                       # the resident kernel, the shortcut apart
+    ("f16", 1, 72, 40, (3, 3), 8, 2, 0.5, 0),                        # neither on the GEMM
+    ("f16", 1, 64, 128, (4, 4), 16, 2, 0.0, 0), ("bf16", 1, 64, 128, (4, 4), 16, 2, 1.0, 0),
+    ("f16", 1, 64, 320, (4, 6), 8, 2, 0.5, 5),                       # room for surplus blocks, a partial channel tile
+    ("f16", 4, 64, 128, (8, 16), 32, 2, 0.6, 0)])                    # more than one round of tiles
+def test_down_equals_convolution_and_shortcut(dtype, N, C, Co, grid, bs, stride, p_low, extra):
+    import paper_2011_12025_amd as sb
+    GH, GW = grid
+    H, W = GH * bs, GW * bs
+    log(f"[down] {dtype} {N}x{C}->{Co} grid {grid} bs={bs} s={stride} p_low={p_low}")
+    mask = torch.from_numpy(inputs.mask_bernoulli(320, N, GH, GW, p_low)).cuda()
+    nh, nl = sb.count(mask)
+    x = _cl(inputs.feature_map(320, N, C, H, W, dtype))
+    hi, lo = sb.split(x, mask, bs, counts=(nh + extra, nl + extra))
+    w3, b3 = _cl(inputs.conv_weight(320, Co, C, 3, dtype)), inputs.conv_bias(320, Co, 9 * C, dtype).cuda()
+    w1, b1 = _cl(inputs.conv_weight(321, Co, C, 1, dtype)), inputs.conv_bias(321, Co, C, dtype).cuda()
+    hh = None if nh == 0 else _cl(half_res(hi))
+    want = (bs // stride) % 2 == 0
+    h, sc = sb.block_conv_down(hi, lo, mask, bs, H, W, w3, b3, w1, b1, stride=stride, hi_half=hh, want_half=want)
+    ref = sb.block_conv_chain(hi, lo, mask, bs, H, W, w3, b3, stride=stride, relu=True, hi_half=hh, want_half=want)
+    rsc = sb.block_conv_ex(hi, lo, mask, bs, H, W, w1, b1, stride=stride)
+    torch.cuda.synchronize()
+    for g, r, n in ((h[0], ref[0], nh), (h[1], ref[1], nl), (h[2], ref[2], nh), (sc[0], rsc[0], nh), (sc[1], rsc[1], nl)):
+        if g is not None:
+            assert g.shape == r.shape and torch.equal(g[:n], r[:n])
