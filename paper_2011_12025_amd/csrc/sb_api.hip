@@ -994,7 +994,7 @@ int segblocks_stem_pool(const void* x, int dtype, int layout, int N, int C_in, i
         return fail(SB_EINVAL, fn, "supported: channels-last fp16 / bf16, C_in <= 4, C_out %% 8 == 0, even W, aligned");
     const long long Hp = ((H - 1) / 2) / 2 + 1, Wp = ((W - 1) / 2) / 2 + 1, es = 2;
     if ((long long)N * H * W * C_in > (1LL << 40) || (long long)N * Hp * Wp * C_out > (1LL << 38) ||
-        N * ((Hp + 15) / 16) * ((Wp + 31) / 32) >= (1LL << 31))
+        N * ((Hp + 7) / 8) * ((Wp + 31) / 32) >= (1LL << 31))
         return fail(SB_ESHAPE, fn, "problem too large");
     const Range rx{x, (long long)N * C_in * H * W * es}, ry{y, (long long)N * C_out * Hp * Wp * es};
     const Range rw{weight, (long long)C_out * C_in * 49 * es}, rb{bias, bias ? C_out * es : 0};

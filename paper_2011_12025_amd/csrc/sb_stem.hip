@@ -182,10 +182,12 @@ __device__ __forceinline__ uint4 finish8(const floatx4& a, const floatx4& b, con
 // ---------------------------------------------------------------------------
 // dense stem + max-pool
 // ---------------------------------------------------------------------------
-constexpr int SP_WG = 512;               // eight waves, one workgroup per CU
-constexpr int SP_PH = 16, SP_PW = 32;    // pooled tile
-constexpr int SP_IH = 4 * SP_PH + 7, SP_IW = 4 * SP_PW + 8, SP_PITCH = SP_IW * 8;
-constexpr int SP_LDS = SW_BYTES + SP_IH * SP_PITCH + 64 * 4;
+// Pooled tile: PH rows (16: eight waves, one workgroup a CU; 8: four waves, two)
+// x 32 columns.
+constexpr int SP_PW = 32, SP_IW = 4 * SP_PW + 8, SP_PITCH = SP_IW * 8;
+constexpr int sp_wg(int ph) { return ph * 32; }
+constexpr int sp_rows(int ph) { return 4 * ph + 7; }
+constexpr int sp_lds(int ph) { return SW_BYTES + sp_rows(ph) * SP_PITCH + 64 * 4; }
 
 // lane i of a row of 16 lanes takes lane i - 1 (lane 0: `edge`), lane i + 1
 // (lane 15: undefined), or lane 15 in lane 0
@@ -204,7 +206,7 @@ __device__ __forceinline__ uint32_t max2(uint32_t a, uint32_t b) {
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
 }
 
-// One workgroup: 16 x 32 pooled pixels, 64 channels.  Wave (rg, ch) makes
+// One workgroup: PH x 32 pooled pixels, 64 channels.  Wave (rg, ch) makes
 // pooled rows 4 rg .. 4 rg + 3, columns 16 ch .. 16 ch + 15, from nine stem
 // rows of 32 pixels one after the other: the vertical maxima are taken as the
 // rows come, then the horizontal ones across lanes (an operand's 16 pixels are
@@ -214,12 +216,16 @@ __device__ __forceinline__ uint32_t max2(uint32_t a, uint32_t b) {
 //
 // Bound by MFMA issue (K padded from 147 to 224) and, at one image, by the
 // single round of workgroups, whose start (image tile and filters from
-// memory) nothing overlaps.  1024x2048, 64 channels: 24.5 us for one image and
-// 88 us for four, where the stem and the pool as two kernels take 51 and 199.
-template <typename T, int C>
-__global__ __launch_bounds__(SP_WG, 1) void k_stem_pool(const T* __restrict__ x, int H, int W, const T* __restrict__ w,
+// memory) nothing overlaps.  1024x2048, 64 channels, tiles of
+// 16 / 8 rows: 24.5 / 26.2 us for one image (256 / 512 workgroups, one round
+// either way), 86.6 / 79.2 for four (several rounds: one workgroup's start beside
+// the other's MFMAs); so 16 rows up to one tile a CU, 8 beyond.  The stem and
+// the pool as two kernels take 51 and 199.
+template <typename T, int C, int PH>
+__global__ __launch_bounds__(sp_wg(PH), PH == 16 ? 1 : 2) void k_stem_pool(const T* __restrict__ x, int H, int W, const T* __restrict__ w,
                                                         const T* __restrict__ bias, int C_out, T* __restrict__ y,
                                                         int Ho, int Wo, int Hp, int Wp, int TY, int TX) {
+    constexpr int SP_WG = sp_wg(PH), SP_PH = PH, SP_IH = sp_rows(PH);
     extern __shared__ __align__(16) unsigned char smem[];
     T* s_w = reinterpret_cast<T*>(smem);
     unsigned char* s_in = smem + SW_BYTES;
@@ -620,17 +626,26 @@ __global__ __launch_bounds__(WG) void k_pool_blocks(Geo g, const uint8_t* __rest
 
 inline bool al(const void* p, uintptr_t n) { return (reinterpret_cast<uintptr_t>(p) & (n - 1)) == 0; }
 
+template <typename T, int C, int PH>
+hipError_t stem_pool_ph(const void* x, int N, int H, int W, const void* w, const void* bias, int C_out, void* y,
+                        hipStream_t st) {
+    const int Ho = (H - 1) / 2 + 1, Wo = (W - 1) / 2 + 1, Hp = (Ho - 1) / 2 + 1, Wp = (Wo - 1) / 2 + 1;
+    const int TY = (Hp + PH - 1) / PH, TX = (Wp + SP_PW - 1) / SP_PW;
+    hipError_t e = ensure_dyn_lds((const void*)k_stem_pool<T, C, PH>, sp_lds(PH));
+    if (e != hipSuccess) return e;
+    const dim3 grid((unsigned)((long long)N * TY * TX), (unsigned)((C_out + 63) / 64));
+    hipLaunchKernelGGL((k_stem_pool<T, C, PH>), grid, dim3(sp_wg(PH)), sp_lds(PH), st, (const T*)x, H, W, (const T*)w,
+                       (const T*)bias, C_out, (T*)y, Ho, Wo, Hp, Wp, TY, TX);
+    return hipGetLastError();
+}
+
 template <typename T, int C>
 hipError_t stem_pool_c(const void* x, int N, int H, int W, const void* w, const void* bias, int C_out, void* y,
                        hipStream_t st) {
-    const int Ho = (H - 1) / 2 + 1, Wo = (W - 1) / 2 + 1, Hp = (Ho - 1) / 2 + 1, Wp = (Wo - 1) / 2 + 1;
-    const int TY = (Hp + SP_PH - 1) / SP_PH, TX = (Wp + SP_PW - 1) / SP_PW;
-    hipError_t e = ensure_dyn_lds((const void*)k_stem_pool<T, C>, SP_LDS);
-    if (e != hipSuccess) return e;
-    const dim3 grid((unsigned)((long long)N * TY * TX), (unsigned)((C_out + 63) / 64));
-    hipLaunchKernelGGL((k_stem_pool<T, C>), grid, dim3(SP_WG), SP_LDS, st, (const T*)x, H, W, (const T*)w,
-                       (const T*)bias, C_out, (T*)y, Ho, Wo, Hp, Wp, TY, TX);
-    return hipGetLastError();
+    const long long Hp = (H - 1) / 2 / 2 + 1, Wp = (W - 1) / 2 / 2 + 1;
+    const long long tiles16 = N * ((Hp + 15) / 16) * ((Wp + SP_PW - 1) / SP_PW) * ((C_out + 63) / 64);
+    if (tiles16 <= device_cus()) return stem_pool_ph<T, C, 16>(x, N, H, W, w, bias, C_out, y, st);
+    return stem_pool_ph<T, C, 8>(x, N, H, W, w, bias, C_out, y, st);
 }
 
 template <typename T>

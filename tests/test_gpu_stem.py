@@ -40,7 +40,8 @@ def image(seed, N, C, H, W, dtype):
 
 @pytest.mark.parametrize("dtype,N,C,Co,H,W", [
     ("f16", 1, 3, 64, 64, 128), ("bf16", 2, 3, 64, 130, 266), ("f16", 2, 3, 72, 67, 70), ("bf16", 1, 4, 8, 1, 2),
-    ("f16", 1, 1, 40, 9, 514), ("bf16", 3, 2, 128, 61, 62)])
+    ("f16", 1, 1, 40, 9, 514), ("bf16", 3, 2, 128, 61, 62),
+    ("f16", 24, 3, 64, 131, 386)])  # more 16-row tiles than CUs: the 8-row tiles
 def test_stem_pool_equals_its_two_calls(dtype, N, C, Co, H, W):
     import paper_2011_12025_amd as sb
     log(f"[stem pool] {dtype} {N}x{C}x{H}x{W} -> {Co}")
