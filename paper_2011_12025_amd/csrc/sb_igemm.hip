@@ -183,6 +183,7 @@ struct GParams {
     int tiles;      // M tiles of the grid (both classes)
     int tiles_n;    // output-channel tiles
     int tile_major; // grid order: 1 = M tile slowest, 0 = M tile fastest
+    int per_tile;   // tile-major order: workgroups of an M tile
     int whole;      // units (M tile x channel tile, in grid order) below this one are not split
     int splits;     // workgroups sharing the K steps of each other unit
     float* part;    // fp32 partial tiles [unit - whole][split][TM * TN] when splits > 1
@@ -360,7 +361,10 @@ __device__ __forceinline__ size_t gpart_off(int tile_lin, int split, int splits,
     return ((size_t)tile_lin * splits + split) * TILE + ((size_t)((wave * MS + ms) * NS + ns) * 64 + lane) * 4;
 }
 
-template <typename T, int KS, int ST, int WM, int MS, int NS>
+// EXT: a shortcut in the same launch, or the full convolution (GParams sc_*,
+// org); without it their selects stay out of the start-up (0.3 us of a 31 us
+// layer).
+template <typename T, int KS, int ST, int WM, int MS, int NS, bool EXT>
 __global__ __launch_bounds__(GWG, 1) void k_igemm(Geo g, const uint8_t* __restrict__ mask, ConvArgs a, GParams gp) {
     typedef GMF<T> mf;
     typedef typename mf::frag frag;
@@ -392,17 +396,29 @@ __global__ __launch_bounds__(GWG, 1) void k_igemm(Geo g, const uint8_t* __restri
     // the fastest, so that the channel tiles and splits of a tile, which
     // share its pixels, run on one XCD when the tile count is a multiple of 8
     // (workgroups go to the XCDs round-robin).
-    const int units = gp.tiles * gp.tiles_n;
-    const bool sc = KS == 3 && (int)blockIdx.x >= gp.main_wgs;
-    int unit = (int)blockIdx.x - (sc ? gp.main_wgs : 0), z = 0, splits = 1;
-    if (!sc && unit >= gp.whole) {
-        const int l = unit - gp.whole, r = units - gp.whole;
-        splits = gp.splits;
-        z = gp.tile_major ? l % splits : l / r;
-        unit = gp.whole + (gp.tile_major ? l / splits : l - z * r);
+    const bool sc = EXT && (int)blockIdx.x >= gp.main_wgs;
+    const int org = EXT ? gp.org : KS / 2;
+    int lin = (int)blockIdx.x, z = 0, splits = 1, tx, ny;
+    if (gp.tile_major) {  // (every unit is split alike)
+        const int per_tile = gp.per_tile;
+        if (sc) lin -= gp.main_wgs;
+        else splits = gp.splits;
+        tx = lin / (sc ? gp.tiles_n : per_tile);
+        const int rq = lin - tx * (sc ? gp.tiles_n : per_tile);
+        ny = splits > 1 ? rq / splits : rq;
+        z = rq - ny * splits;
+    } else {
+        if (sc) {
+            lin -= gp.main_wgs;
+        } else if (lin >= gp.whole) {
+            const int l = lin - gp.whole, r = gp.tiles * gp.tiles_n - gp.whole;
+            splits = gp.splits;
+            z = splits > 1 ? l / r : 0;
+            lin = gp.whole + l - z * r;
+        }
+        ny = gp.tiles_n > 1 ? lin / gp.tiles : 0;
+        tx = lin - ny * gp.tiles;
     }
-    const int ny = gp.tile_major ? unit % gp.tiles_n : unit / gp.tiles;
-    const int tx = gp.tile_major ? unit / gp.tiles_n : unit - ny * gp.tiles;
     const int co0 = ny * TN;
     const int C_in = a.C_in, C_out = a.C_out;
     const int cpt = gp.cpt;
@@ -572,7 +588,7 @@ __global__ __launch_bounds__(GWG, 1) void k_igemm(Geo g, const uint8_t* __restri
         const int idx = tid + it * GWG, t = idx - (idx / KT) * KT;
         const int pij = pijv[it];
         const int b = pij >> 22, i = (pij >> 11) & 2047, j = pij & 2047;
-        const int uu = ST * i + t / KS - gp.org, vv = ST * j + (t - (t / KS) * KS) - gp.org;
+        const int uu = ST * i + t / KS - org, vv = ST * j + (t - (t / KS) * KS) - org;
         const int dy = uu < 0 ? -1 : (uu >= e_in ? 1 : 0);
         const int dx = vv < 0 ? -1 : (vv >= e_in ? 1 : 0);
         nbv[it] = (pij >= 0 && !lpad) ? s_nb[b * 9 + (dy + 1) * 3 + dx + 1] : gdesc(GK_ZERO, 0);
@@ -587,7 +603,7 @@ __global__ __launch_bounds__(GWG, 1) void k_igemm(Geo g, const uint8_t* __restri
         if (pij >= 0) {
             const int b = pij >> 22, i = (pij >> 11) & 2047, j = pij & 2047;
             const int ky = t / KS, kx = t - (t / KS) * KS;
-            const int uu = ST * i + ky - gp.org, vv = ST * j + kx - gp.org;
+            const int uu = ST * i + ky - org, vv = ST * j + kx - org;
             if (lpad) {  // a low tile over the padded low stack: every source is a copy
                 ds = gdesc(GK_LO, ((slot0 + b) * (lb + 2) + uu + 1) * (lb + 2) + vv + 1);
             } else {
@@ -703,24 +719,25 @@ __global__ __launch_bounds__(GWG, 1) void k_igemm(Geo g, const uint8_t* __restri
     }
     __builtin_amdgcn_s_waitcnt(0);  // the padding DMAs
 
-    if (sc) {
+    if (splits == 1) {
         ConvArgs b = a;
-        b.bias = gp.sc_bias;
-        b.res_hi = b.res_lo = nullptr;
-        b.out_hi = gp.sc_hi;
-        b.out_lo = gp.sc_lo;
-        b.flags = 0;
-        gepilogue<T, WM, MS, NS>(acc, b, high, m0, rows_valid, co0, nullptr, g.W, nullptr, -1);
-    } else if (splits == 1) {
-        gepilogue<T, WM, MS, NS>(acc, a, high, m0, rows_valid, co0, dense ? s_dout : nullptr, g.W,
-                                 high && gp.hs_lg >= 0 ? (T*)a.out_hs : nullptr, gp.hs_lg);
+        if (sc) {
+            b.bias = gp.sc_bias;
+            b.res_hi = b.res_lo = nullptr;
+            b.out_hi = gp.sc_hi;
+            b.out_lo = gp.sc_lo;
+            b.flags = 0;
+        }
+        gepilogue<T, WM, MS, NS>(acc, b, high, m0, rows_valid, co0, dense ? s_dout : nullptr, g.W,
+                                 !sc && high && gp.hs_lg >= 0 ? (T*)a.out_hs : nullptr, gp.hs_lg);
     } else {
+        const int su = (gp.tile_major ? tx * gp.tiles_n + ny : ny * gp.tiles + tx) - gp.whole;  // among the split units
 #pragma unroll
         for (int ms = 0; ms < MS; ++ms)
 #pragma unroll
             for (int ns = 0; ns < NS; ++ns)
-                *reinterpret_cast<floatx4*>(gp.part + gpart_off<TM * TN, MS, NS>(unit - gp.whole, z, splits, wave, ms, ns,
-                                                                                lane)) = acc[ms][ns];
+                *reinterpret_cast<floatx4*>(gp.part +
+                                            gpart_off<TM * TN, MS, NS>(su, z, splits, wave, ms, ns, lane)) = acc[ms][ns];
     }
 }
 
@@ -1008,11 +1025,15 @@ hipError_t igemm_run(const Geo& g, const uint8_t* mask, ConvArgs a, Ws ws, hipSt
     gp.eo_l = (g.bs / 2) / ST + (full ? KS - 1 : 0);
     gp.cpt = a.C_in / GKC;
     const int smem = igemm_smem_fixed<TM, TN, KS * KS>() + igemm_hb_bytes(g);
-    hipError_t e = ensure_dyn_lds((const void*)k_igemm<T, KS, ST, WM, MS, NS>, smem);
+    const bool ext = KS == 3 && (full || a.sc_weight);
+    const void* kernel = ext ? (const void*)k_igemm<T, KS, ST, WM, MS, NS, KS == 3>
+                             : (const void*)k_igemm<T, KS, ST, WM, MS, NS, false>;
+    hipError_t e = ensure_dyn_lds(kernel, smem);
     if (e != hipSuccess) return e;
     const int tiles_n = pl.tiles_n;
     const int S = pl.splits;
     gp.splits = S;
+    gp.per_tile = tiles_n * S;
     gp.whole = S > 1 ? pl.whole : tiles * tiles_n;
     const long long split_units = (long long)tiles * tiles_n - gp.whole;
     gp.tiles = tiles;
@@ -1049,7 +1070,8 @@ hipError_t igemm_run(const Geo& g, const uint8_t* mask, ConvArgs a, Ws ws, hipSt
     }
     gp.main_wgs = (int)(gp.whole + split_units * S);
     const dim3 grid((unsigned)(gp.main_wgs + (a.sc_weight ? tiles * tiles_n : 0)));
-    hipLaunchKernelGGL((k_igemm<T, KS, ST, WM, MS, NS>), grid, dim3(GWG), smem, st, g, mask, a, gp);
+    if (ext) hipLaunchKernelGGL((k_igemm<T, KS, ST, WM, MS, NS, KS == 3>), grid, dim3(GWG), smem, st, g, mask, a, gp);
+    else hipLaunchKernelGGL((k_igemm<T, KS, ST, WM, MS, NS, false>), grid, dim3(GWG), smem, st, g, mask, a, gp);
     if (S > 1) {
         e = hipGetLastError();
         if (e != hipSuccess) return e;
