@@ -984,9 +984,8 @@ IgPlan igemm_plan(const Geo& g, const ConvArgs& a, int ks, int stride, bool dens
     if (p.splits == 1) p.whole = 0;
     // A low block's halo across a resolution change, with average sampling, is
     // the 2x2 average of a high neighbour's cell: a 3 x 3 convolution with
-    // both classes pads the low stack once beforehand (BlockPad of the low
-    // blocks, one extra launch), so that every source of the K loop is a plain
-    // copy.  (Averaging in the K loop instead measured 6-12 us slower at the
+    // both classes prepares these cells once beforehand (one extra launch: see
+    // own_hs below), so that every source of the K loop is a plain copy.  (Averaging in the K loop instead measured 6-12 us slower at the
     // ResNet-18 stage shapes with 25 % low blocks or 128 channels, within
     // 3 us either way elsewhere.)
     // In dense mode the padded low stack comes straight from the dense map and
@@ -998,11 +997,12 @@ IgPlan igemm_plan(const Geo& g, const ConvArgs& a, int ks, int stride, bool dens
     // What a low block needs of its high neighbours is only the border cells of
     // their half-resolution stack, which the K loop reads like a stack given as
     // in_hs: that is less to write than the padded low stack unless low blocks
-    // are few (the rule is the two sizes; so the workspace is never larger).
+    // are few (the rule is the two sizes).  The workspace stays that of the
+    // padded low stack for both, so a call needs what its shapes always needed.
     const size_t lb = g.bs / 2;
     const size_t pad = (size_t)a.lo_cap * (lb + 2) * (lb + 2), hs = (size_t)a.hi_cap * lb * lb;
     p.own_hs = p.pad_low && !dense && hs <= pad && a.C_in % 8 == 0;
-    p.pad_bytes = p.pad_low ? ground256((p.own_hs ? hs : pad) * a.C_in * 2) : 0;
+    p.pad_bytes = p.pad_low ? ground256(pad * a.C_in * 2) : 0;
     return p;
 }
 

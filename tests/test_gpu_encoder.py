@@ -131,6 +131,51 @@ def test_block_conv_ex(c):
     assert_conv_close(lo_o, ref64[1], c.dtype, K, f"{c.name} low")
 
 
+# More tiles than whole rounds of 256 workgroups hold: with the workspace
+# that the size query asks for, only the remainder is split over K; with room for nothing but
+# the padded low stack, nothing is.
+@pytest.mark.parametrize("dtype,nh", [("bf16", 125), ("f16", 140)])
+@pytest.mark.parametrize("least", [False, True])
+def test_block_conv_remainder_split(dtype, nh, least):
+    import ctypes
+
+    from paper_2011_12025_amd import _binding as B
+    N, C, Co, H, W, bs = 1, 128, 64, 192, 240, 16
+    nb = (H // bs) * (W // bs)
+    nl = nb - nh
+    log(f"[remainder split] {dtype} nh={nh} least={least}")
+    rng = np.random.default_rng(nh)
+    mask = (rng.permutation(nb) < nh).astype(np.uint8).reshape(1, H // bs, W // bs)
+    code, t = (B.SB_F16 if dtype == "f16" else B.SB_BF16), TDT[dtype]
+    n = ctypes.c_size_t(0)
+    assert B.lib().segblocks_block_conv_ex_workspace_size(code, B.SB_NHWC, N, C, H, W, bs, Co, 3, 1, nh, nl,
+                                                          ctypes.byref(n)) == 0
+    lb = bs // 2
+    padded_low = nl * (lb + 2) ** 2 * C * 2
+    assert n.value > padded_low
+    need = -(-padded_low // 256) * 256 if least else n.value
+    x = inputs.feature_map(nh, N, C, H, W, dtype)
+    w, b = inputs.conv_weight(nh, Co, C, 3, dtype), inputs.conv_bias(nh, Co, 9 * C, dtype)
+    hi, lo = oracle.split(x.float().numpy(), mask, bs, dtype)
+    ref = [np.maximum(oracle.conv_block(P, w.float().numpy(), 1, b.float().numpy()), 0.0)
+           for P in oracle.pad(hi, lo, mask, bs, H, W, dtype)]
+    dhi, dlo, dw = _cl(torch.from_numpy(hi).to(t)), _cl(torch.from_numpy(lo).to(t)), _cl(w)
+    out = [_cl(torch.full((k, Co, e, e), float("nan"), dtype=t)) for k, e in ((nh, bs), (nl, lb))]
+    ws = torch.full((need + 256,), 255, dtype=torch.uint8, device="cuda")  # NaN in every type
+    off = -ws.data_ptr() % 256
+    db, dm = b.cuda(), torch.from_numpy(mask).cuda()
+    P = lambda a: ctypes.c_void_p(a.data_ptr())
+    rc = B.lib().segblocks_block_conv_ex(P(dhi), P(dlo), code, B.SB_NHWC, N, C, H, W, P(dm), bs, P(dw), P(db), Co, 3, 1,
+                                         1, None, None, P(out[0]), P(out[1]), nh, nl,
+                                         ctypes.c_void_p(ws.data_ptr() + off), need,
+                                         ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0, B.lib().segblocks_last_error().decode()
+    torch.cuda.synchronize()
+    assert bool((ws[off + need:] == 255).all()) and bool((ws[:off] == 255).all())
+    for o, r, name in zip(out, ref, ("high", "low")):
+        assert_conv_close(o, r, dtype, 9 * C, f"remainder split {name}")
+
+
 @dataclasses.dataclass
 class DCase:
     name: str
