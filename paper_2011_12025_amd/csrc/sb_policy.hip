@@ -110,17 +110,22 @@ __global__ __launch_bounds__(NT) void k_policy_score(const T* __restrict__ x, in
             acc += cell_norms(d2);
         }
     }
-    // fixed-order reduction: lanes of a wave, then the waves in order
+    // fixed-order reduction: lanes of a wave, then the waves
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
     __shared__ float s_part[NT / 64];
     if ((threadIdx.x & 63) == 0) s_part[threadIdx.x >> 6] = acc;
     __syncthreads();
     if (threadIdx.x == 0) {
-        float t = 0.0f;
+        // in pairs: sixteen waves' sums one after the other round half as much again
+        float t[NT / 64];
 #pragma unroll
-        for (int w = 0; w < NT / 64; ++w) t += s_part[w];
-        score[k] = t / (float)(bs * bs);
+        for (int w = 0; w < NT / 64; ++w) t[w] = s_part[w];
+#pragma unroll
+        for (int h = NT / 128; h > 0; h >>= 1)
+#pragma unroll
+            for (int w = 0; w < h; ++w) t[w] += t[w + h];
+        score[k] = t[0] / (float)(bs * bs);
     }
 }
 
