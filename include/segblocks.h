@@ -404,7 +404,8 @@ int segblocks_pad_split_backward(const void* dhp, const void* dlp, int dtype, in
  *   dP[s,ci,u,v] = sum_{co,ky,kx} w[co,ci,ky,kx] * dO[s,co,u-ky,v-kx]
  * dho [nh,C_out,bs,bs], dlo [nl,C_out,lb,lb] -> dhp [nh,C_in,bs+2,bs+2],
  * dlp [nl,C_in,lb+2,lb+2]; weight as in segblocks_conv3x3.  Needs a
- * workspace (the gradients padded by two zeros, the transposed filters):
+ * workspace (the transposed filters and the implicit GEMM's partial sums, or
+ * for the general kernel the gradients padded by two zeros):
  * segblocks_conv3x3_backward_data_workspace_size. */
 int segblocks_conv3x3_backward_data(const void* dho, const void* dlo, int dtype, int layout, int N,
                                     int C_in, int H, int W, const uint8_t* mask, int bs,

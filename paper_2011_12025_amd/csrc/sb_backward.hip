@@ -16,13 +16,12 @@
 //                 sums run in a fixed order, so results do not depend on
 //                 timing.
 //   dgrad         the gradient of the valid 3x3 convolution of a padded block
-//                 is a valid 3x3 convolution of the output gradient padded by
-//                 two zeros, with the filters transposed (in <-> out) and
-//                 rotated by 180 degrees, i.e. a zero-padded "same"
-//                 convolution of the gradient padded by one: run on the
-//                 implicit GEMM (channels-last fp16 / bf16, 64k output
-//                 channels, blocks of 4k), else on the general block
-//                 convolution kernel.
+//                 is the full 3x3 convolution of the output gradient, with the
+//                 filters transposed (in <-> out) and rotated by 180 degrees:
+//                 on the implicit GEMM (channels-last fp16 / bf16, 64k output
+//                 channels) one launch over both stacks as they are, else a
+//                 valid convolution of the gradient padded by two zeros on the
+//                 general block convolution kernel.
 //   k_wgrad_mfma  the weight and bias gradients: sums over every output pixel
 //                 of both stacks of outer products of the output gradient and
 //                 the padded input around the pixel, as a GEMM whose K is the
@@ -854,7 +853,8 @@ ConvArgs dgrad_args(int C_in, int C_out, int hi_cap, int lo_cap) {
 
 struct DgradLayout {
     bool ig_shape;  // the implicit GEMM takes these shapes
-    size_t qh, ql, wt, masks, ig, total;
+    size_t qh, ql, wt, masks, ig;
+    size_t gemm, general;  // bytes of either route
 };
 
 DgradLayout dgrad_layout(int dtype, int layout, const Geo& g, int C_in, int C_out, int hi_cap, int lo_cap) {
@@ -868,8 +868,9 @@ DgradLayout dgrad_layout(int dtype, int layout, const Geo& g, int C_in, int C_ou
     D.ig_shape = igemm_full_fits_shape(dtype, layout, g, a);
     D.ig = D.ig_shape ? r256(igemm_full_ws_bytes(g, a)) : 0;
     // either route in one workspace: [filters][GEMM], or [padded gradients][filters][masks] where
-    // less aligned buffers take the general kernel
-    D.total = std::max(D.wt + D.ig, D.qh + D.ql + D.wt + D.masks);
+    // less aligned buffers, or a workspace that holds no more, take the general kernel
+    D.gemm = D.wt + D.ig;
+    D.general = D.qh + D.ql + D.wt + D.masks;
     return D;
 }
 
@@ -991,7 +992,7 @@ hipError_t dgrad_t(const Geo& g, const void* dho, const void* dlo, const uint8_t
                    int C_out, void* dhp, void* dlp, int hi_cap, int lo_cap, Ws ws, hipStream_t st) {
     constexpr int dt = sizeof(T) == 4 ? 0 : (std::is_same<T, f16>::value ? 1 : 2);
     const DgradLayout D = dgrad_layout(dt, L, g, C_in, C_out, hi_cap, lo_cap);
-    if (ws.bytes < D.total || !ws.p) return hipErrorInvalidValue;
+    if (!ws.p || ws.bytes < D.general) return hipErrorInvalidValue;
     char* base = (char*)ws.p;
     const int grid = device_cus() * 4;
     hipError_t e;
@@ -1001,7 +1002,7 @@ hipError_t dgrad_t(const Geo& g, const void* dho, const void* dlo, const uint8_t
     ga.weight = base;
     ga.out_hi = dhp;
     ga.out_lo = dlp;
-    if (D.ig_shape && igemm_fits(dt, L, g, ga)) {
+    if (D.ig_shape && ws.bytes >= D.gemm && igemm_fits(dt, L, g, ga)) {
         const int total = C_in * C_out * 9;
         hipLaunchKernelGGL((k_dgrad_prep<T, L>), dim3((unsigned)std::min<long long>(grid, (total + WG - 1) / WG)), dim3(WG),
                            0, st, (const T*)w, C_out, C_in, (T*)base, nullptr, nullptr, 0LL, (const T*)nullptr, 0,
@@ -1108,8 +1109,9 @@ hipError_t launch_pad_split_bwd(int dtype, int layout, const Geo& g, const void*
     }
 }
 
-size_t dgrad_ws_bytes(int dtype, int layout, const Geo& g, int C_in, int C_out, int hi_cap, int lo_cap) {
-    return dgrad_layout(dtype, layout, g, C_in, C_out, hi_cap, lo_cap).total;
+size_t dgrad_ws_bytes(int dtype, int layout, const Geo& g, int C_in, int C_out, int hi_cap, int lo_cap, bool frugal) {
+    const DgradLayout D = dgrad_layout(dtype, layout, g, C_in, C_out, hi_cap, lo_cap);
+    return frugal ? D.general : std::max(D.gemm, D.general);
 }
 
 hipError_t launch_dgrad(int dtype, int layout, const Geo& g, const void* dho, const void* dlo, const uint8_t* mask,

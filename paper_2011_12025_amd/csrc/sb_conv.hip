@@ -35,7 +35,7 @@
 // run of words), other channels-last ones element by element.
 //
 // Bounds: fp32 by MFMA issue and by the staging beside it
-// (the 256x512, 64-channel layer, half low, NCHW: 179 -> 112 us, 39 us of MFMA
+// (the 256x512, 64-channel layer, half low, NCHW: 178 -> 109 us, 39 us of MFMA
 // issue; a 64x64 layer of 16 channels 31 -> 11 us), small and ragged 16-bit
 // calls by the latency of the chain mask -> descriptors -> inputs -> MFMAs (two
 // 96x180 maps, 48 -> 72 channels, 12-pixel blocks: 22 -> 20 us; one 128x256

@@ -2,7 +2,8 @@
 // the image to the last stage (the stem and its max-pool included): a K x K
 // convolution (K odd) at stride 1 or 2 with dilation, and K x K max-pooling,
 // on stacks padded by BlockPad with a halo of `halo` pixels (segblocks_pad
-// with a wider halo).  Output pixel (i, j) of a block is the window centred
+// with a wider halo).  The ResNet stem on 16-bit channels-last images has fused
+// kernels of its own; this file takes everything else.  Output pixel (i, j) of a block is the window centred
 // on block pixel (stride * i, stride * j).
 //
 // Direct kernels: a thread computes four consecutive output channels of one

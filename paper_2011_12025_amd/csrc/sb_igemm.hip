@@ -1129,8 +1129,11 @@ bool igemm_fits(int dtype, int layout, const Geo& g, const ConvArgs& a) {
 }
 
 size_t igemm_ws_bytes(const Geo& g, const ConvArgs& a, int ksize, int stride, bool frugal) {
-    const IgPlan p = igemm_plan(g, a, ksize, stride, false, false, frugal);
-    return p.part_bytes + p.pad_bytes;
+    const IgPlan f = igemm_plan(g, a, ksize, stride, false, false, true);
+    if (frugal) return f.part_bytes + f.pad_bytes;
+    // (splitting the remainder alone may also need less than the plan without it)
+    const IgPlan p = igemm_plan(g, a, ksize, stride);
+    return std::max(p.part_bytes + p.pad_bytes, f.part_bytes + f.pad_bytes);
 }
 
 hipError_t launch_igemm(int dtype, const Geo& g, const uint8_t* mask, const ConvArgs& a, int ksize, int stride, Ws ws,

@@ -137,7 +137,8 @@ hipError_t launch_maxpool(int dtype, const void* x, int N, int C, int H, int W, 
 
 // Backward pass (sb_backward.hip): BlockPad transposed, the block
 // convolution's gradient with respect to its padded input (dgrad, on the
-// general kernel; workspace: dgrad_ws_bytes) and to its weights and bias
+// implicit GEMM or the general kernel; workspace: dgrad_ws_bytes, of which the
+// general kernel needs the frugal part) and to its weights and bias
 // (wgrad; workspace: wgrad_ws_bytes).  BlockCombine / BlockSample transposed
 // are launch_split / launch_combine with bwd.
 hipError_t launch_pad_bwd(int dtype, int layout, const Geo& g, const void* dhp, const void* dlp, const uint8_t* mask,
@@ -148,7 +149,8 @@ hipError_t launch_split_pad(int dtype, int layout, const Geo& g, const void* x, 
                             int hi_cap, int lo_cap, int pm, hipStream_t st);
 hipError_t launch_pad_split_bwd(int dtype, int layout, const Geo& g, const void* dhp, const void* dlp,
                                 const uint8_t* mask, void* dx, int hi_cap, int lo_cap, int pm, hipStream_t st);
-size_t dgrad_ws_bytes(int dtype, int layout, const Geo& g, int C_in, int C_out, int hi_cap, int lo_cap);
+size_t dgrad_ws_bytes(int dtype, int layout, const Geo& g, int C_in, int C_out, int hi_cap, int lo_cap,
+                      bool frugal = false);
 hipError_t launch_dgrad(int dtype, int layout, const Geo& g, const void* dho, const void* dlo, const uint8_t* mask,
                         const void* w, int C_in, int C_out, void* dhp, void* dlp, int hi_cap, int lo_cap, Ws ws,
                         hipStream_t st);

@@ -119,6 +119,42 @@ def test_conv_gradients(c, layout):
     assert_conv_close(db, rb, c.dtype, npx, "bias grad")
 
 
+# The implicit GEMM's partial sums take more than the general kernel's padded
+# gradients: a workspace that holds only the latter runs the general kernel.
+@pytest.mark.parametrize("least", [False, True])
+def test_data_gradient_in_either_workspace(least):
+    import ctypes
+
+    from paper_2011_12025_amd import _binding as B
+    c = Case("c16_co256_bs2", "f16", 1, 16, 256, 12, 20, 2, seed=170)
+    mask, _, w, _ = make_inputs(c)
+    nh = int(mask.sum())
+    nl = mask.size - nh
+    n = ctypes.c_size_t(0)
+    shape = (B.SB_F16, B.SB_NHWC, 1, c.C, c.H, c.W)
+    assert B.lib().segblocks_conv3x3_backward_data_workspace_size(*shape, c.bs, c.Co, nh, nl, ctypes.byref(n)) == 0
+    parts = (nh * c.Co * 36 * 2, nl * c.Co * 25 * 2, c.C * c.Co * 9 * 2, mask.size * 2)
+    general = sum(-(-p // 256) * 256 for p in parts)
+    assert general < n.value
+    need = general if least else n.value
+    log(f"[backward data] {c.name} nh={nh} nl={nl} workspace {need}")
+    gho, glo = _grad(c.seed + 5, (nh, c.Co, 2, 2), c.dtype), _grad(c.seed + 6, (nl, c.Co, 1, 1), c.dtype)
+    dho, dlo, dw, dm = up(gho, "f16", "nhwc"), up(glo, "f16", "nhwc"), to_dev(w, "nhwc"), torch.from_numpy(mask).cuda()
+    out = [up(np.full((k, c.C, e, e), np.nan, np.float32), "f16", "nhwc") for k, e in ((nh, 4), (nl, 3))]
+    ws = torch.full((need + 512,), 255, dtype=torch.uint8, device="cuda")
+    off = -ws.data_ptr() % 256
+    P = lambda a: ctypes.c_void_p(a.data_ptr())
+    rc = B.lib().segblocks_conv3x3_backward_data(P(dho), P(dlo), *shape, P(dm), c.bs, P(dw), c.Co, P(out[0]), P(out[1]),
+                                                 nh, nl, ctypes.c_void_p(ws.data_ptr() + off), need,
+                                                 ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0, B.lib().segblocks_last_error().decode()
+    torch.cuda.synchronize()
+    assert bool((ws[off + need:] == 255).all()) and bool((ws[:off] == 255).all())
+    wf = w.float().numpy()
+    assert_conv_close(out[0], oracle.conv3x3_backward_data(gho, wf), "f16", 9 * c.Co, "dgrad hi")
+    assert_conv_close(out[1], oracle.conv3x3_backward_data(glo, wf), "f16", 9 * c.Co, "dgrad lo")
+
+
 @pytest.mark.parametrize("sampling", ["avg", "strided", "zero"])
 @pytest.mark.parametrize("c", [CASES[0], CASES[2], CASES[4],
                                Case("stage1_full", "f16", 1, 64, 64, 256, 512, 32, seed=167)],
