@@ -617,7 +617,8 @@ __global__ __launch_bounds__(WG) void k_pool_blocks(Geo g, const uint8_t* __rest
         row_max(b, prev);
         Vec<T, 8> o;
 #pragma unroll
-        for (int x = 0; x < 8; ++x) o.e[x] = from_f32<T>(fmaxf(m[x], prev[x]));
+        for (int x = 0; x < 8; ++x)  // (a window of nothing but NaN: -inf, as the direct kernel starts from)
+            o.e[x] = from_f32<T>(fmaxf(fmaxf(m[x], prev[x]), -INFINITY));
         vstore<T, 8>(out + (size_t)i * eo * g.C, o);
         a = a2;
         b = b2;

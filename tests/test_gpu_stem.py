@@ -108,3 +108,21 @@ def test_maxpool_blocks_equals_its_two_calls(dtype, N, C, grid, bs, p_low, short
     torch.cuda.synchronize()
     for g, r in zip(got, ref):
         assert g.shape == r.shape and torch.equal(g, r)
+
+
+def test_maxpool_blocks_nan_and_infinity():
+    import paper_2011_12025_amd as sb
+    H, W, bs = 64, 96, 32
+    mask = torch.tensor([[[1, 0, 1], [0, 1, 0]]], dtype=torch.uint8, device="cuda")
+    x = image(194, 1, 8, H, W, "f16")
+    x[0, 1, 3:12, 5:14] = float("nan")  # whole windows and parts of some, in a high block
+    x[0, 2, 20:30, 40:52] = float("nan")  # ... and in a low one
+    x[0, 3, 28:36, 26:70] = float("-inf")  # across blocks
+    x[0, 4, 33, 33] = float("inf")
+    hi, lo = sb.split(x, mask, bs, counts=(3, 3))
+    got = sb.maxpool_blocks(hi, lo, mask, bs, H, W)
+    ref = sb.maxpool_halo(*sb.pad_halo(hi, lo, mask, bs, H, W, 1), mask, bs, H, W, 1, 3, 2)
+    torch.cuda.synchronize()
+    for g, r in zip(got, ref):
+        assert torch.equal(g, r) and not torch.isnan(g).any()
+    assert any(bool((r[:, 1] == float("-inf")).any()) for r in ref)
