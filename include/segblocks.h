@@ -13,20 +13,28 @@
  * Conventions shared by every entry point
  * ---------------------------------------
  *  - Pointers are DEVICE pointers unless stated otherwise.  The caller owns
- *    every buffer; the library allocates no device memory.  Four calls may
+ *    every buffer; the library allocates no device memory.  Five calls may
  *    need scratch memory beyond their inputs and outputs (fp32 partial tiles
  *    of a reduction split over several workgroups, a padded copy of the low
  *    stack, the packed stacks of a fused layer with many channels):
  *    segblocks_block_conv3x3, segblocks_block_conv_ex,
- *    segblocks_block_conv_chain and segblocks_layer take it as a `workspace` pointer with its size `ws_bytes`.  The size a
- *    call needs depends only on its shapes, capacities and device, and is
- *    given by segblocks_block_conv3x3_workspace_size,
+ *    segblocks_block_conv_chain, segblocks_block_conv_down and segblocks_layer
+ *    take it as a `workspace` pointer with its size `ws_bytes` (and so do the
+ *    two gradients of the convolution).  The size of a call depends only on
+ *    its shapes, capacities and device, and is given by
+ *    segblocks_block_conv3x3_workspace_size,
  *    segblocks_block_conv_ex_workspace_size,
- *    segblocks_block_conv_chain_workspace_size and
- *    segblocks_layer_workspace_size (0 = none needed; NULL is then fine).  A
- *    workspace must be 256-byte aligned and must not overlap any argument;
- *    a smaller one (or NULL when one is needed) fails with SB_ENOMEM before
- *    anything is launched.  The workspace holds no state between calls, but
+ *    segblocks_block_conv_chain_workspace_size (also for
+ *    segblocks_block_conv_down) and segblocks_layer_workspace_size (0 = none
+ *    needed; NULL is then fine).  A workspace must be 256-byte aligned and
+ *    must not overlap any argument.  A packed convolution, or the gradient of
+ *    one with respect to its input, whose workspace is smaller than that runs
+ *    with less where a plan with less scratch exists (a reduction that is not
+ *    split further, another kernel): the same results up to the order of the
+ *    fp32 sums, slower.  Below the least that any plan takes (or with NULL
+ *    where one is needed) a call fails with SB_ENOMEM before anything is
+ *    launched.  So results are reproducible bit for bit among calls with the
+ *    queried size or more.  The workspace holds no state between calls, but
  *    it is in use until the call's kernels finish on `stream`: calls that
  *    may overlap need workspaces of their own.
  *  - Logical dimensions are always N, C, H, W.  `layout` selects the memory
@@ -224,14 +232,16 @@ int segblocks_block_conv_ex(const void* hi, const void* lo, int dtype, int layou
 /* segblocks_block_conv_ex for callers that cannot allocate device memory
  * (code under HIP graph capture, tight serving loops, harnesses that forbid
  * allocation): the same arguments, results and kernels, without the
- * workspace.  Scratch space comes from a fixed buffer of
+ * workspace: the results are those of segblocks_block_conv_ex with a workspace
+ * of the queried size, bit for bit.  Scratch space comes from a fixed buffer of
  * SB_NOALLOC_SCRATCH_BYTES that the library holds on every device it runs on
  * until the process ends; a call that would need more (see
- * segblocks_block_conv_ex_workspace_size) fails with SB_ENOMEM before
+ * segblocks_block_conv_ex_workspace_size; with strided or zero padding a call
+ * needs less than that size) fails with SB_ENOMEM before
  * anything is launched.  The call allocates nothing.  Every call on one
- * device shares that device's buffer: calls that may overlap on one device
- * (different streams, or host threads) race and must be ordered by the
- * caller.  The buffer keeps the last call's contents; each call writes every
+ * device whose queried size is not 0 shares that device's buffer: such calls
+ * that may overlap on one device (different streams, or host threads) race and
+ * must be ordered by the caller.  The buffer keeps the last call's contents; each call writes every
  * scratch byte it reads, so nothing has to be cleared. */
 #define SB_NOALLOC_SCRATCH_BYTES (16u << 20)
 int segblocks_block_conv_ex_noalloc(const void* hi, const void* lo, int dtype, int layout,

@@ -54,6 +54,7 @@
 #include "sb_common.h"
 #include "sb_kernels.h"
 #include "sb_pixel.h"
+#include "segblocks.h"
 
 namespace sb {
 
@@ -892,9 +893,17 @@ struct IgPlan {
 };
 
 // full: the full convolution of every block on its own (outputs ks - 1 pixels wider).
-// frugal: without splitting a remainder (its partial tiles may need more
-// workspace than a plan without it: a call whose workspace is only enough for
-// the frugal plan runs that).
+// frugal: without splitting a remainder (a call whose workspace is only enough
+// for that runs it).
+//
+// The remainder is split only in calls that take a workspace anyway (a padded
+// low stack), and only as far as the whole workspace stays within the fixed
+// scratch of the entry point without a workspace or within the padded low stack
+// alone: so a call that needs no scratch shares none with other streams, that
+// entry point refuses what the size query puts above its scratch and nothing
+// else, and what it accepts runs the plan that a queried workspace gets.  Both
+// are a matter of shapes and sampling, not of a half-resolution stack given:
+// with or without one the sums are the same.
 IgPlan igemm_plan(const Geo& g, const ConvArgs& a, int ks, int stride, bool dense = false, bool full = false,
                   bool frugal = false) {
     IgPlan p;
@@ -933,6 +942,12 @@ IgPlan igemm_plan(const Geo& g, const ConvArgs& a, int ks, int stride, bool dens
     p.splits = 1;
     p.whole = 0;
     const bool room = (long long)a.hi_cap + a.lo_cap > g.B;  // surplus tiles
+    const bool pads = ks == 3 && a.lo_cap > 0 && a.hi_cap > 0 && pad_mode(a.flags) == PM_AVG;
+    // pixels of the padded low stack, or of the high stack at half resolution instead (see own_hs below)
+    const size_t lb = g.bs / 2;
+    const size_t pad = (size_t)a.lo_cap * (lb + 2) * (lb + 2), hs = (size_t)a.hi_cap * lb * lb;
+    const size_t pad_bytes = ground256(pad * a.C_in * 2), prep_bytes = ground256(std::min(hs, pad) * a.C_in * 2);
+    const size_t most = std::max<size_t>(SB_NOALLOC_SCRATCH_BYTES, pad_bytes);
     for (int cand = 0; cand < 4; ++cand) {
         int TM = 128, tn;
         if (cand < 3) {
@@ -960,10 +975,10 @@ IgPlan igemm_plan(const Geo& g, const ConvArgs& a, int ks, int stride, bool dens
             }
             // whole rounds of unsplit tiles, then the remainder split c ways: a
             // 128-channel convolution of four images, 60 % low (281 tiles of
-            // 256 x 128), 56 -> 45 us with its pass; it pays while the remainder
-            // is small (320 tiles: 59 -> 57)
+            // 256 x 128), 56 -> 45 us with its pass
             const long long whole = wgs / cus * cus, rest = wgs - whole;
-            if (c == 1 || frugal || dense || room || whole == 0 || rest == 0) continue;
+            if (c == 1 || frugal || dense || room || !pads || whole == 0 || rest == 0) continue;
+            if (ground256((size_t)rest * c * TM * tn * 4 + (size_t)(wgs / tiles_n) * 8) + prep_bytes > most) continue;
             const double tail = (double)(whole / cus) * (nsteps * w + GSTART_COST) +
                                 (double)((rest * c + cus - 1) / cus) * ((nsteps + c - 1) / c * w + GSTART_COST) +
                                 GTAIL_COST + c * wr * rest / cus;
@@ -990,19 +1005,18 @@ IgPlan igemm_plan(const Geo& g, const ConvArgs& a, int ks, int stride, bool dens
     // 3 us either way elsewhere.)
     // In dense mode the padded low stack comes straight from the dense map and
     // the high tiles read their low neighbours from it as well.
-    p.pad_low = dense || (ks == 3 && p.tiles_l > 0 && a.hi_cap > 0 && pad_mode(a.flags) == PM_AVG && !a.in_hs);
+    p.pad_low = dense || (pads && !a.in_hs);
     p.part_bytes = p.splits > 1 ? ground256(((size_t)tiles * p.tiles_n - p.whole) * p.splits * p.TM * p.TN * 4 +
                                             (size_t)tiles * 8 + (dense ? (size_t)tiles * p.TM * 4 : 0))
                                 : 0;
     // What a low block needs of its high neighbours is only the border cells of
     // their half-resolution stack, which the K loop reads like a stack given as
     // in_hs: that is less to write than the padded low stack unless low blocks
-    // are few (the rule is the two sizes).  The workspace stays that of the
-    // padded low stack for both, so a call needs what its shapes always needed.
-    const size_t lb = g.bs / 2;
-    const size_t pad = (size_t)a.lo_cap * (lb + 2) * (lb + 2), hs = (size_t)a.hi_cap * lb * lb;
+    // are few (the rule is the two sizes).  What a call insists on stays that of
+    // the padded low stack for both, so it needs what its shapes always needed;
+    // only a split remainder's partial tiles take the room that is left.
     p.own_hs = p.pad_low && !dense && hs <= pad && a.C_in % 8 == 0;
-    p.pad_bytes = p.pad_low ? ground256(pad * a.C_in * 2) : 0;
+    p.pad_bytes = !p.pad_low ? 0 : p.whole > 0 ? prep_bytes : pad_bytes;
     return p;
 }
 

@@ -177,6 +177,20 @@ def test_calls_reject_missing_or_small_workspace(lib):
     assert lib.segblocks_block_conv3x3(*bargs, NULL, 0, None) == b.SB_ENOMEM
 
 
+@pytest.mark.parametrize("nh", [0, 129, 204, 257, 300, 384, 510])
+@pytest.mark.parametrize("nl", [0, 1, 56, 308, 770])
+def test_split_remainder_stays_within_the_fixed_scratch(lib, nh, nl):
+    """Tiles that leave a remainder (128 channels, blocks of 16): a call that
+    would need no scratch otherwise needs none, and the others no more than the
+    entry point without a workspace holds, or than the padded low stack alone."""
+    pad = -(-nl * 100 * 128 * 2 // 256) * 256 if nh else 0  # (nothing to pad from without high blocks)
+    r, n = _ws_query(lib, "segblocks_block_conv_ex_workspace_size", 2, 1, 1, 128, 16, 16 * 1280, 16, 128, 3, 1, nh, nl)
+    assert r == 0 and pad <= n <= max(16 << 20, pad)
+    assert (n == 0) == (nh == 0 or nl == 0) or nh < 256  # (fewer tiles than workgroups: all are split)
+    if (nh, nl) == (204, 308):
+        assert n > pad  # 281 tiles: the remainder is split
+
+
 def test_chain_queries_and_validation(lib):
     """segblocks_block_conv_chain: its workspace is what block_conv_ex /
     block_conv3x3 need for the same shapes; the host query tells whether a

@@ -105,3 +105,39 @@ def test_noalloc_matches_workspace_entry_point():
         assert torch.isfinite(ref_h).all() and torch.isfinite(ref_l).all()
         assert torch.equal(got_h, ref_h), f"call {i}: high stack differs"
         assert torch.equal(got_l, ref_l), f"call {i}: low stack differs"
+
+
+@pytest.mark.gpu
+def test_noalloc_splits_a_remainder_alike():
+    """281 tiles on 256 CUs (four images, 128 channels, 60 % low): the entry
+    point without a workspace, the one with the queried workspace and the chain
+    that is given the half-resolution stack split the remainder alike, so they
+    agree bit for bit."""
+    import paper_2011_12025_amd as sb
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    N, C, H, W, bs, nh, nl = 4, 128, 128, 256, 16, 204, 308
+    n = ctypes.c_size_t(0)
+    assert B.lib().segblocks_block_conv_ex_workspace_size(B.SB_BF16, B.SB_NHWC, N, C, H, W, bs, C, 3, 1, nh, nl,
+                                                          ctypes.byref(n)) == 0
+    assert nl * 100 * C * 2 < n.value <= 16 << 20  # more than the padded low stack, less than the fixed buffer
+    print(f"[no-alloc] remainder: scratch {n.value} B", flush=True)
+    g = torch.Generator().manual_seed(122)
+    bf = lambda *s, std=1.0: (torch.randn(*s, generator=g) * std).bfloat16()
+    hi, lo, w = _cl(bf(nh, C, bs, bs)), _cl(bf(nl, C, bs // 2, bs // 2)), _cl(bf(C, C, 3, 3, std=(9 * C) ** -0.5))
+    b = bf(C).cuda()
+    m = torch.zeros(nh + nl, dtype=torch.uint8)
+    m[torch.randperm(nh + nl, generator=g)[:nh]] = 1
+    md = m.reshape(N, H // bs, W // bs).cuda()
+    ref = sb.block_conv_ex(hi, lo, md, bs, H, W, w, b)
+    half = _cl(((hi[:, :, ::2, ::2].float() + hi[:, :, ::2, 1::2].float())
+                + (hi[:, :, 1::2, ::2].float() + hi[:, :, 1::2, 1::2].float())).mul(0.25).bfloat16())
+    chain = sb.block_conv_chain(hi, lo, md, bs, H, W, w, b, hi_half=half)
+    got = [torch.full_like(r, float("nan")) for r in ref]
+    rc = B.lib().segblocks_block_conv_ex_noalloc(
+        _P(hi), _P(lo), B.SB_BF16, B.SB_NHWC, N, C, H, W, _P(md), bs, _P(w), _P(b), C, 3, 1, 0, None, None, _P(got[0]),
+        _P(got[1]), nh, nl, ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0, B.lib().segblocks_last_error().decode()
+    torch.cuda.synchronize()
+    for r, q, k in zip(ref, got, chain):
+        assert torch.isfinite(r).all() and torch.equal(r, q) and torch.equal(r, k)
