@@ -853,7 +853,13 @@ namespace {
 // partial tiles.
 constexpr int GSTART_COST = 10;
 constexpr int GSPLIT_COST = 12;  // plus one per split
-constexpr int GTAIL_COST = 7;    // the same pass over a remainder's tiles only: mostly its launch
+// The pass over a remainder's tiles only: its launch, and writing and reading
+// back the partial tiles (of 128 x 128), in units of 0.47 us; a unit of the
+// wider tiles' rounds was 0.59.  Fitted to 62 pairs of the same call with and
+// without the split (64 to 320 channels, 64 to 256 outputs, blocks of 8 and 16,
+// 30 and 60 % low, 2 to 120 tiles left over): saved rounds of 12 to 40 units
+// against -3.4 to 19 us gained.
+constexpr double GTAIL_COST = 6.0, GTAIL_PART = 0.05, GTAIL_WIDE = 0.8;
 
 inline bool galigned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 inline size_t ground256(size_t b) { return (b + 255) / 256 * 256; }
@@ -975,13 +981,13 @@ IgPlan igemm_plan(const Geo& g, const ConvArgs& a, int ks, int stride, bool dens
             }
             // whole rounds of unsplit tiles, then the remainder split c ways: a
             // 128-channel convolution of four images, 60 % low (281 tiles of
-            // 256 x 128), 56 -> 45 us with its pass
+            // 256 x 128), 52.0 -> 47.5 us with its pass
             const long long whole = wgs / cus * cus, rest = wgs - whole;
             if (c == 1 || frugal || dense || room || !pads || whole == 0 || rest == 0) continue;
             if (ground256((size_t)rest * c * TM * tn * 4 + (size_t)(wgs / tiles_n) * 8) + prep_bytes > most) continue;
             const double tail = (double)(whole / cus) * (nsteps * w + GSTART_COST) +
                                 (double)((rest * c + cus - 1) / cus) * ((nsteps + c - 1) / c * w + GSTART_COST) +
-                                GTAIL_COST + c * wr * rest / cus;
+                                (GTAIL_COST + GTAIL_PART * c * wr * rest) * (wide ? GTAIL_WIDE : 1.0);
             if (tail < best) {
                 best = tail;
                 p.TM = TM;

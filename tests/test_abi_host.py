@@ -191,6 +191,15 @@ def test_split_remainder_stays_within_the_fixed_scratch(lib, nh, nl):
         assert n > pad  # 281 tiles: the remainder is split
 
 
+@pytest.mark.parametrize("nh,nl,split", [(118, 50, True), (163, 69, False)])
+def test_large_remainders_are_not_split(lib, nh, nl, split):
+    """128 -> 72 channels, blocks of 16: 261 tiles are 256 and a split
+    remainder; with 361 the partial tiles cost more than the short round saves."""
+    r, n = _ws_query(lib, "segblocks_block_conv_ex_workspace_size", 1, 1, 1, 128, 16, 16 * (nh + nl), 16, 72, 3, 1, nh,
+                     nl)
+    assert r == 0 and (n > -(-nl * 100 * 128 * 2 // 256) * 256) == split
+
+
 def test_chain_queries_and_validation(lib):
     """segblocks_block_conv_chain: its workspace is what block_conv_ex /
     block_conv3x3 need for the same shapes; the host query tells whether a
