@@ -515,7 +515,7 @@ __device__ __forceinline__ void chunk_mfma(floatx4 (&acc)[MS][4], const unsigned
 
 template <typename T, int L, int SRC, int DST, int STG, int MS>
 __global__ __launch_bounds__(WG, 2) void k_conv(Geo g, const uint8_t* __restrict__ mask, ConvArgs a, int Rh,
-                                                int Rl, int G, int w_off, int d_off, int nt, int vec_out) {
+                                                int Rl, int w_off, int d_off, int nt, int vec_out) {
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr int KC = ROWB / (int)sizeof(T);  // channels per K chunk
     constexpr bool NEED_SLOTS = !(SRC == SRC_DENSE && DST == DST_DENSE);
@@ -523,8 +523,19 @@ __global__ __launch_bounds__(WG, 2) void k_conv(Geo g, const uint8_t* __restrict
     unsigned char* s_in = smem;
     unsigned char* s_w = smem + w_off;
     unsigned long long* s_desc = reinterpret_cast<unsigned long long*>(smem + d_off);
-    const int k = (int)blockIdx.x / G;
-    const int grp = (int)blockIdx.x - k * G;
+    // Tile grp of block k, the blocks fastest: the class with fewer tiles fills
+    // only the first of a block's places, and workgroups go to the XCDs
+    // round-robin, so with the tiles fastest all-low maps ran on two of the eight
+    // XCDs.
+    const int B = (int)g.B, grp = (int)blockIdx.x / B;
+    int k = (int)blockIdx.x - grp * B;
+    if constexpr (L == NCHW) {
+        // runs of four blocks on one XCD: a halo column of a plane is a line of the
+        // neighbour's for every row
+        constexpr int RUN = 4;
+        const int base = k & ~(8 * RUN - 1), o = k - base;
+        if (base + 8 * RUN <= B) k = base + (o & 7) * RUN + (o >> 3);
+    }
     const int co0 = blockIdx.y * nt;
     const int nsn = (min(nt, a.C_out - co0) + 15) >> 4;  // 16-channel sub-tiles that hold channels
     Tile t;
@@ -736,7 +747,7 @@ inline ConvPlan conv_plan(const Geo& g, const ConvArgs& a, bool dense) {
         if (mt < 256 && (nh * Gh + nl * Gl) * p.ny > 2LL * device_cus()) break;
         p.Rh = Rh;
         p.Rl = Rl;
-        p.G = std::max(Gh, Gl);
+        p.G = std::max(nh > 0 ? Gh : 0, dense || nl > 0 ? Gl : 0);
         p.M = std::max(Rh * eh, Rl * el);
     }
     return p;
@@ -751,9 +762,9 @@ hipError_t run_conv_ms(const Geo& g, const uint8_t* mask, const ConvArgs& a, con
     const int vec_out = (a.C_out % 4 == 0) && aligned(a.out_hi, ob) && aligned(a.out_lo, ob) &&
                         aligned(a.res_hi, ob) && aligned(a.res_lo, ob);
     hipError_t e = ensure_dyn_lds((const void*)k_conv<T, L, SRC, DST, STG, MS>, smem);
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess || p.G == 0) return e;
     const dim3 grid((unsigned)(g.B * p.G), (unsigned)p.ny);
-    hipLaunchKernelGGL((k_conv<T, L, SRC, DST, STG, MS>), grid, dim3(WG), smem, st, g, mask, a, p.Rh, p.Rl, p.G, w_off,
+    hipLaunchKernelGGL((k_conv<T, L, SRC, DST, STG, MS>), grid, dim3(WG), smem, st, g, mask, a, p.Rh, p.Rl, w_off,
                        d_off, p.nt, vec_out);
     return hipGetLastError();
 }
