@@ -171,13 +171,13 @@ __device__ __forceinline__ int tid_here() {
 }
 
 // ---- channels-last staging in 16-byte vectors: item it is sub-chunk it % 4 of
-// pixel it / 4.  issue() requests every item's (first) vector, commit() the
-// three others of the averages, then writes LDS: what is in flight across
-// the MFMAs is one vector an item.
+// pixel it / 4.  issue() requests every item's (first) vector, rest() the
+// three others of the averages, finish() writes LDS.
 template <typename T>
 struct VecIn {
     static constexpr int KC = ROWB / (int)sizeof(T), VQ = 16 / (int)sizeof(T);
     Vec<T, VQ> v[UI];
+    bool avg[UI];  // (kept: only an average's descriptor is read again)
 
     static __device__ __forceinline__ unsigned long long desc(const unsigned long long* s_desc, int C_in, int in_px,
                                                               int it, int kc) {
@@ -190,6 +190,7 @@ struct VecIn {
         for (int u = 0; u < UI; ++u) {
             const int it = base + u * WG + tid;
             const unsigned long long d = desc(s_desc, C_in, in_px, it, kc);
+            avg[u] = (d & SD_AVG) != 0;
             v[u] = vzero<T, VQ>();
             if (d) v[u] = vload<T, VQ>(st.at(d) + kc * KC + (it & 3) * VQ);
         }
@@ -197,18 +198,15 @@ struct VecIn {
     // the other three vectors of the averages among items u0 .. u0 + UA - 1, and those items to LDS
     struct Rest {
         Vec<T, VQ> r[UA][3];
-        bool avg[UA];
     };
     __device__ __forceinline__ void rest(Rest& q, int u0, const unsigned long long* s_desc, const Strides<T>& st,
-                                         int C_in, int in_px, int base, int kc) const {
+                                         int base, int kc) const {
         const int tid = tid_here();
 #pragma unroll
         for (int u = 0; u < UA; ++u) {
             const int it = base + (u0 + u) * WG + tid;
-            const unsigned long long d = desc(s_desc, C_in, in_px, it, kc);
-            q.avg[u] = (d & SD_AVG) != 0;
-            if (q.avg[u]) {
-                const T* p = st.at(d) + kc * KC + (it & 3) * VQ;
+            if (avg[u0 + u]) {
+                const T* p = st.at(s_desc[it >> 2]) + kc * KC + (it & 3) * VQ;
                 q.r[u][0] = vload<T, VQ>(p + st.d1);
                 q.r[u][1] = vload<T, VQ>(p + st.d2);
                 q.r[u][2] = vload<T, VQ>(p + st.d2 + st.d1);
@@ -220,18 +218,17 @@ struct VecIn {
 #pragma unroll
         for (int u = 0; u < UA; ++u) {
             const int it = base + (u0 + u) * WG + tid;
-            if (q.avg[u]) v[u0 + u] = vavg4<T, VQ>(v[u0 + u], q.r[u][0], q.r[u][1], q.r[u][2]);
+            if (avg[u0 + u]) v[u0 + u] = vavg4<T, VQ>(v[u0 + u], q.r[u][0], q.r[u][1], q.r[u][2]);
             if (it < in_px * 4) *reinterpret_cast<uint4*>(s_in + swz(it >> 2, it & 3)) = v[u0 + u].raw;
         }
         __builtin_amdgcn_sched_barrier(0);
     }
-    __device__ __forceinline__ void commit(int u0, const unsigned long long* s_desc, const Strides<T>& st, int C_in,
-                                           int in_px, int base, int kc, unsigned char* s_in) {
+    __device__ __forceinline__ void commit(const unsigned long long* s_desc, const Strides<T>& st, int in_px, int base,
+                                           int kc, unsigned char* s_in) {
 #pragma unroll
         for (int u = 0; u < UI; u += UA) {
-            if (u < u0) continue;
             Rest q;
-            rest(q, u, s_desc, st, C_in, in_px, base, kc);
+            rest(q, u, s_desc, st, base, kc);
             finish(q, u, in_px, base, s_in);
         }
     }
@@ -426,38 +423,49 @@ __device__ __forceinline__ void stage_w_scalar(const ConvArgs& a, int co0, int n
 // stage() writes them to LDS and stages the other inputs.
 enum Stage { ST_VEC = 0, ST_SCALAR = 1, ST_PLANE = 2 };
 
-template <typename T, int STG>
+// (MS: pixel sub-tiles per wave, whose accumulators share the registers.)
+template <typename T, int STG, int MS>
 struct Stager;
-template <typename T>
-struct Stager<T, ST_VEC> {
+template <typename T, int MS>
+struct Stager<T, ST_VEC, MS> {
     VecW<T> w;
     VecIn<T> in;
+    // Small tiles have registers left for every vector of their averages, so
+    // all of them are in flight across the MFMAs; larger ones request the first
+    // of each, and the others after the MFMAs, two items at a time (before the
+    // first chunk, when there are no sums yet, all at once as well).
+    static constexpr bool AHEAD = MS <= 2;
+    typename VecIn<T>::Rest q[UI / UA];
+    __device__ __forceinline__ void rests(const unsigned long long* s_desc, const Strides<T>& st, int kc) {
+#pragma unroll
+        for (int i = 0; i < UI / UA; ++i) in.rest(q[i], i * UA, s_desc, st, 0, kc);
+    }
     __device__ __forceinline__ void weights(const ConvArgs& a, int co0, int nt, int kc) { w.issue(a, co0, nt, kc); }
     __device__ __forceinline__ void inputs(const unsigned long long* s_desc, const Strides<T>& st, int C_in, int in_px,
                                            int kc) {
         in.issue(s_desc, st, C_in, in_px, 0, kc);
+        if constexpr (AHEAD) rests(s_desc, st, kc);
     }
     template <bool FIRST>
     __device__ __forceinline__ void stage(const ConvArgs& a, int, int nt, int kc, const unsigned long long* s_desc,
                                           const Strides<T>& st, int in_px, unsigned char* s_in, unsigned char* s_w) {
-        if constexpr (FIRST) {  // nothing has run yet: the first averages' loads join the others in flight
-            typename VecIn<T>::Rest q;
-            in.rest(q, 0, s_desc, st, a.C_in, in_px, 0, kc);
-            w.commit(s_w, nt);
-            in.finish(q, 0, in_px, 0, s_in);
+        if constexpr (FIRST && !AHEAD) rests(s_desc, st, kc);
+        w.commit(s_w, nt);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (FIRST || AHEAD) {
+#pragma unroll
+            for (int i = 0; i < UI / UA; ++i) in.finish(q[i], i * UA, in_px, 0, s_in);
         } else {
-            w.commit(s_w, nt);
-            __builtin_amdgcn_sched_barrier(0);
+            in.commit(s_desc, st, in_px, 0, kc, s_in);
         }
-        in.commit(FIRST ? UA : 0, s_desc, st, a.C_in, in_px, 0, kc, s_in);
         for (int base = WG * UI; base < in_px * 4; base += WG * UI) {
             in.issue(s_desc, st, a.C_in, in_px, base, kc);
-            in.commit(0, s_desc, st, a.C_in, in_px, base, kc, s_in);
+            in.commit(s_desc, st, in_px, base, kc, s_in);
         }
     }
 };
-template <typename T>
-struct Stager<T, ST_PLANE> {
+template <typename T, int MS>
+struct Stager<T, ST_PLANE, MS> {
     PlaneW<T> w;
     PlaneIn<T> in;
     __device__ __forceinline__ void weights(const ConvArgs& a, int co0, int nt, int kc) { w.issue(a, co0, nt, kc); }
@@ -477,8 +485,8 @@ struct Stager<T, ST_PLANE> {
         }
     }
 };
-template <typename T>
-struct Stager<T, ST_SCALAR> {
+template <typename T, int MS>
+struct Stager<T, ST_SCALAR, MS> {
     __device__ __forceinline__ void weights(const ConvArgs&, int, int, int) {}
     __device__ __forceinline__ void inputs(const unsigned long long*, const Strides<T>&, int, int, int) {}
     template <bool FIRST>
@@ -565,7 +573,7 @@ __global__ __launch_bounds__(WG, 2) void k_conv(Geo g, const uint8_t* __restrict
     const int l16 = lane & 15, kg = lane >> 4;
 
     // -- chunk 0's weights, and the tile's source descriptors
-    Stager<T, STG> sg;
+    Stager<T, STG, MS> sg;
     sg.weights(a, co0, nt, 0);
     for (int p = tid; p < t.in_px; p += WG) {
         const Src<T> s = tile_src<T, L, SRC>(g, a, nb, t, p);

@@ -24,6 +24,9 @@ CASES = [
     Case("full_tiles_f32", "f32", 1, 32, 24, 264, 480, 24, seed=205),         # tiles of 256 pixels (rows 8 of 24)
     Case("bs256_f32", "f32", 1, 8, 8, 256, 256, 256, seed=206, mask_kind="high"),
     Case("bs4_bf16", "bf16", 2, 72, 8, 32, 32, 4, p_low=0.6, seed=207),
+    Case("runs_and_rest_f16", "f16", 2, 24, 40, 84, 60, 12, seed=210),        # 70 blocks: runs of four, then single ones
+    Case("all_low_f16", "f16", 1, 72, 40, 96, 64, 16, seed=211, mask_kind="low"),
+    Case("all_low_f32", "f32", 1, 20, 72, 64, 128, 32, seed=212, mask_kind="low"),
 ]
 
 
