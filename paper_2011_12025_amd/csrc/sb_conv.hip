@@ -497,27 +497,36 @@ struct Stager<T, ST_SCALAR, MS> {
     }
 };
 
-// The nine taps of one staged chunk, NS channel sub-tiles by nms <= MS pixel sub-tiles.
-template <typename T, int NS, int MS>
-__device__ __forceinline__ void chunk_mfma(floatx4 (&acc)[MS][4], const unsigned char* wlane, const unsigned char* s_in,
-                                           const int (&pbase)[MS], int pe, int kg, int nt, int nms) {
+// The nine taps of one staged chunk, NS channel sub-tiles by NM pixel sub-tiles.
+// (Straight code for every count: a test per sub-tile between the reads and the
+// MFMAs of a lone wave cost a quarter of this phase.)
+template <typename T, int NS, int NM, int MS>
+__device__ __forceinline__ void chunk_taps(floatx4 (&acc)[MS][4], const unsigned char* wlane, const unsigned char* s_in,
+                                           const int (&pbase)[MS], int pe, int kg, int nt) {
 #pragma unroll 1
     for (int tap = 0; tap < 9; ++tap) {
         const int toff = (tap / 3) * pe + (tap % 3);
-        uint4 wf[NS], pf[MS];
+        uint4 wf[NS], pf[NM];
 #pragma unroll
         for (int ns = 0; ns < NS; ++ns) wf[ns] = *reinterpret_cast<const uint4*>(wlane + (tap * nt + ns * 16) * ROWB);
 #pragma unroll
-        for (int ms = 0; ms < MS; ++ms)
-            if (ms < nms) pf[ms] = *reinterpret_cast<const uint4*>(s_in + swz(pbase[ms] + toff, kg));
+        for (int ms = 0; ms < NM; ++ms) pf[ms] = *reinterpret_cast<const uint4*>(s_in + swz(pbase[ms] + toff, kg));
 #pragma unroll
-        for (int ms = 0; ms < MS; ++ms)
-            if (ms < nms) {
+        for (int ms = 0; ms < NM; ++ms)
 #pragma unroll
-                for (int i = 0; i < MF<T>::STEPS; ++i)
+            for (int i = 0; i < MF<T>::STEPS; ++i)
 #pragma unroll
-                    for (int ns = 0; ns < NS; ++ns) acc[ms][ns] = MF<T>::mma(wf[ns], pf[ms], i, acc[ms][ns]);
-            }
+                for (int ns = 0; ns < NS; ++ns) acc[ms][ns] = MF<T>::mma(wf[ns], pf[ms], i, acc[ms][ns]);
+    }
+}
+template <typename T, int NS, int MS>
+__device__ __forceinline__ void chunk_mfma(floatx4 (&acc)[MS][4], const unsigned char* wlane, const unsigned char* s_in,
+                                           const int (&pbase)[MS], int pe, int kg, int nt, int nms) {
+    if (nms == 1) return chunk_taps<T, NS, 1, MS>(acc, wlane, s_in, pbase, pe, kg, nt);
+    if (nms == 2) return chunk_taps<T, NS, 2, MS>(acc, wlane, s_in, pbase, pe, kg, nt);
+    if constexpr (MS > 2) {
+        if (nms == 3) return chunk_taps<T, NS, 3, MS>(acc, wlane, s_in, pbase, pe, kg, nt);
+        if (nms == 4) return chunk_taps<T, NS, 4, MS>(acc, wlane, s_in, pbase, pe, kg, nt);
     }
 }
 
@@ -531,12 +540,15 @@ __global__ __launch_bounds__(WG, 2) void k_conv(Geo g, const uint8_t* __restrict
     unsigned char* s_in = smem;
     unsigned char* s_w = smem + w_off;
     unsigned long long* s_desc = reinterpret_cast<unsigned long long*>(smem + d_off);
-    // Tile grp of block k, the blocks fastest: the class with fewer tiles fills
-    // only the first of a block's places, and workgroups go to the XCDs
-    // round-robin, so with the tiles fastest all-low maps ran on two of the eight
-    // XCDs.
-    const int B = (int)g.B, grp = (int)blockIdx.x / B;
-    int k = (int)blockIdx.x - grp * B;
+    // Tile grp of block k, the blocks fastest, then the channel tiles: the class
+    // with fewer tiles fills only the first of a block's places, and workgroups
+    // go to the XCDs and their CUs in turn.  With the tiles fastest all-low maps
+    // ran on two of the eight XCDs, with the channel tiles slowest on half of the CUs.
+    const int B = (int)g.B, ny = (a.C_out + nt - 1) / nt;
+    int k = (int)blockIdx.x;
+    const int first = k / B, row = first + (int)blockIdx.y, grp = row / ny;  // (one of the two is 0)
+    k -= first * B;
+    const int co0 = (row - grp * ny) * nt;
     if constexpr (L == NCHW) {
         // runs of four blocks on one XCD: a halo column of a plane is a line of the
         // neighbour's for every row
@@ -544,7 +556,6 @@ __global__ __launch_bounds__(WG, 2) void k_conv(Geo g, const uint8_t* __restrict
         const int base = k & ~(8 * RUN - 1), o = k - base;
         if (base + 8 * RUN <= B) k = base + (o & 7) * RUN + (o >> 3);
     }
-    const int co0 = blockIdx.y * nt;
     const int nsn = (min(nt, a.C_out - co0) + 15) >> 4;  // 16-channel sub-tiles that hold channels
     Tile t;
     {
@@ -771,7 +782,10 @@ hipError_t run_conv_ms(const Geo& g, const uint8_t* mask, const ConvArgs& a, con
                         aligned(a.res_hi, ob) && aligned(a.res_lo, ob);
     hipError_t e = ensure_dyn_lds((const void*)k_conv<T, L, SRC, DST, STG, MS>, smem);
     if (e != hipSuccess || p.G == 0) return e;
-    const dim3 grid((unsigned)(g.B * p.G), (unsigned)p.ny);
+    // one row of workgroups per (tile, channel tile), one after the other, or down
+    // the grid where a launch's 2^32 threads in x do not hold them
+    const bool flat = g.B * p.G * p.ny * WG < (1LL << 32);
+    const dim3 grid((unsigned)(flat ? g.B * p.G * p.ny : g.B), (unsigned)(flat ? 1 : p.G * p.ny));
     hipLaunchKernelGGL((k_conv<T, L, SRC, DST, STG, MS>), grid, dim3(WG), smem, st, g, mask, a, p.Rh, p.Rl, w_off,
                        d_off, p.nt, vec_out);
     return hipGetLastError();
