@@ -499,11 +499,12 @@ struct Stager<T, ST_SCALAR, MS> {
 
 // The nine taps of one staged chunk, NS channel sub-tiles by NM pixel sub-tiles.
 // (Straight code for every count: a test per sub-tile between the reads and the
-// MFMAs of a lone wave cost a quarter of this phase.)
-template <typename T, int NS, int NM, int MS>
+// MFMAs of a lone wave cost a quarter of this phase.)  TAPS taps at a time where
+// there is one pixel sub-tile: its few MFMAs don't cover the reads of the next.
+template <typename T, int NS, int NM, int MS, int TAPS>
 __device__ __forceinline__ void chunk_taps(floatx4 (&acc)[MS][4], const unsigned char* wlane, const unsigned char* s_in,
                                            const int (&pbase)[MS], int pe, int kg, int nt) {
-#pragma unroll 1
+#pragma unroll TAPS
     for (int tap = 0; tap < 9; ++tap) {
         const int toff = (tap / 3) * pe + (tap % 3);
         uint4 wf[NS], pf[NM];
@@ -519,14 +520,14 @@ __device__ __forceinline__ void chunk_taps(floatx4 (&acc)[MS][4], const unsigned
                 for (int ns = 0; ns < NS; ++ns) acc[ms][ns] = MF<T>::mma(wf[ns], pf[ms], i, acc[ms][ns]);
     }
 }
-template <typename T, int NS, int MS>
+template <typename T, int NS, int MS, int TAPS>
 __device__ __forceinline__ void chunk_mfma(floatx4 (&acc)[MS][4], const unsigned char* wlane, const unsigned char* s_in,
                                            const int (&pbase)[MS], int pe, int kg, int nt, int nms) {
-    if (nms == 1) return chunk_taps<T, NS, 1, MS>(acc, wlane, s_in, pbase, pe, kg, nt);
-    if (nms == 2) return chunk_taps<T, NS, 2, MS>(acc, wlane, s_in, pbase, pe, kg, nt);
+    if (nms == 1) return chunk_taps<T, NS, 1, MS, TAPS>(acc, wlane, s_in, pbase, pe, kg, nt);
+    if (nms == 2) return chunk_taps<T, NS, 2, MS, 1>(acc, wlane, s_in, pbase, pe, kg, nt);
     if constexpr (MS > 2) {
-        if (nms == 3) return chunk_taps<T, NS, 3, MS>(acc, wlane, s_in, pbase, pe, kg, nt);
-        if (nms == 4) return chunk_taps<T, NS, 4, MS>(acc, wlane, s_in, pbase, pe, kg, nt);
+        if (nms == 3) return chunk_taps<T, NS, 3, MS, 1>(acc, wlane, s_in, pbase, pe, kg, nt);
+        if (nms == 4) return chunk_taps<T, NS, 4, MS, 1>(acc, wlane, s_in, pbase, pe, kg, nt);
     }
 }
 
@@ -536,6 +537,9 @@ __global__ __launch_bounds__(WG, 2) void k_conv(Geo g, const uint8_t* __restrict
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr int KC = ROWB / (int)sizeof(T);  // channels per K chunk
     constexpr bool NEED_SLOTS = !(SRC == SRC_DENSE && DST == DST_DENSE);
+    // (not where it costs registers that the staging needs: fp32 and NCHW tiles
+    // of four sub-tiles got 3 to 4 % slower, the others up to 6 % faster)
+    constexpr int TAPS = MS <= 2 || (STG == ST_VEC && MF<T>::STEPS == 1) ? 3 : 1;
 
     unsigned char* s_in = smem;
     unsigned char* s_w = smem + w_off;
@@ -627,10 +631,10 @@ __global__ __launch_bounds__(WG, 2) void k_conv(Geo g, const uint8_t* __restrict
         }
         // -- MFMA over the 9 taps of this chunk
         switch (nsn) {
-        case 1: chunk_mfma<T, 1, MS>(acc, wlane, s_in, pbase, t.pe, kg, nt, nms); break;
-        case 2: chunk_mfma<T, 2, MS>(acc, wlane, s_in, pbase, t.pe, kg, nt, nms); break;
-        case 3: chunk_mfma<T, 3, MS>(acc, wlane, s_in, pbase, t.pe, kg, nt, nms); break;
-        default: chunk_mfma<T, 4, MS>(acc, wlane, s_in, pbase, t.pe, kg, nt, nms); break;
+        case 1: chunk_mfma<T, 1, MS, TAPS>(acc, wlane, s_in, pbase, t.pe, kg, nt, nms); break;
+        case 2: chunk_mfma<T, 2, MS, TAPS>(acc, wlane, s_in, pbase, t.pe, kg, nt, nms); break;
+        case 3: chunk_mfma<T, 3, MS, TAPS>(acc, wlane, s_in, pbase, t.pe, kg, nt, nms); break;
+        default: chunk_mfma<T, 4, MS, TAPS>(acc, wlane, s_in, pbase, t.pe, kg, nt, nms); break;
         }
         __syncthreads();
         if (more) {
