@@ -187,7 +187,7 @@ struct GParams {
     int per_tile;   // tile-major order: workgroups of an M tile
     int whole;      // units (M tile x channel tile, in grid order) below this one are not split
     int splits;     // workgroups sharing the K steps of each other unit
-    float* part;    // fp32 partial tiles [unit - whole][split][TM * TN] when splits > 1
+    float* part;    // fp32 partial tiles [split unit][split][TM * TN] when splits > 1
     int* rows;      // per M tile with split units: valid output rows of its class's stack and its
                     // tile number in that class (-1 - number for the low class)
     const void* lo_pad;  // the low stack with its 1-pixel halo [lo_cap][lb+2][lb+2][C_in], or nullptr
@@ -400,25 +400,38 @@ __global__ __launch_bounds__(GWG, 1) void k_igemm(Geo g, const uint8_t* __restri
     const bool sc = EXT && (int)blockIdx.x >= gp.main_wgs;
     const int org = EXT ? gp.org : KS / 2;
     int lin = (int)blockIdx.x, z = 0, splits = 1, tx, ny;
-    if (gp.tile_major) {  // (every unit is split alike)
-        const int per_tile = gp.per_tile;
-        if (sc) lin -= gp.main_wgs;
-        else splits = gp.splits;
-        tx = lin / (sc ? gp.tiles_n : per_tile);
-        const int rq = lin - tx * (sc ? gp.tiles_n : per_tile);
-        ny = splits > 1 ? rq / splits : rq;
-        z = rq - ny * splits;
-    } else {
-        if (sc) {
-            lin -= gp.main_wgs;
-        } else if (lin >= gp.whole) {
+    if (sc) {
+        lin -= gp.main_wgs;
+        tx = gp.tile_major ? lin / gp.tiles_n : lin % gp.tiles;
+        ny = gp.tile_major ? lin - tx * gp.tiles_n : lin / gp.tiles;
+    } else if (gp.whole == 0) {  // every unit is split alike
+        splits = gp.splits;
+        if (gp.tile_major) {
+            const int per_tile = gp.per_tile;
+            tx = lin / per_tile;
+            const int rq = lin - tx * per_tile;
+            ny = rq / splits;
+            z = rq - ny * splits;
+        } else {
+            const int rq = lin / gp.tiles;
+            tx = lin - rq * gp.tiles;
+            z = rq / gp.tiles_n;
+            ny = rq - z * gp.tiles_n;
+        }
+    } else {  // whole units, then the parts of the others (none, or M tile fastest)
+        if (lin >= gp.whole) {
             const int l = lin - gp.whole, r = gp.tiles * gp.tiles_n - gp.whole;
             splits = gp.splits;
-            z = splits > 1 ? l / r : 0;
+            z = l / r;
             lin = gp.whole + l - z * r;
         }
-        ny = gp.tiles_n > 1 ? lin / gp.tiles : 0;
-        tx = lin - ny * gp.tiles;
+        if (gp.tile_major) {
+            tx = gp.tiles_n > 1 ? lin / gp.tiles_n : lin;
+            ny = lin - tx * gp.tiles_n;
+        } else {
+            ny = gp.tiles_n > 1 ? lin / gp.tiles : 0;
+            tx = lin - ny * gp.tiles;
+        }
     }
     const int co0 = ny * TN;
     const int C_in = a.C_in, C_out = a.C_out;
@@ -732,7 +745,7 @@ __global__ __launch_bounds__(GWG, 1) void k_igemm(Geo g, const uint8_t* __restri
         gepilogue<T, WM, MS, NS>(acc, b, high, m0, rows_valid, co0, dense ? s_dout : nullptr, g.W,
                                  !sc && high && gp.hs_lg >= 0 ? (T*)a.out_hs : nullptr, gp.hs_lg);
     } else {
-        const int su = (gp.tile_major ? tx * gp.tiles_n + ny : ny * gp.tiles + tx) - gp.whole;  // among the split units
+        const int su = (gp.tile_major ? tx * gp.tiles_n + ny : ny * gp.tiles + tx) - gp.whole;
 #pragma unroll
         for (int ms = 0; ms < MS; ++ms)
 #pragma unroll
@@ -780,8 +793,14 @@ __global__ __launch_bounds__(256) void k_igemm_reduce(ConvArgs a, GParams gp) {
     }
     const int wave = r;
     const int unit = gp.whole + tile_lin;
-    const int ty = gp.tile_major ? unit % gp.tiles_n : unit / gp.tiles;
-    const int tx = gp.tile_major ? unit / gp.tiles_n : unit - ty * gp.tiles;
+    int tx, ty;
+    if (gp.tile_major) {
+        tx = unit / gp.tiles_n;
+        ty = unit - tx * gp.tiles_n;
+    } else {
+        ty = unit / gp.tiles;
+        tx = unit - ty * gp.tiles;
+    }
     const int rows_valid = gp.rows[2 * tx];
     const int code = gp.rows[2 * tx + 1];
     const int high = code >= 0;
