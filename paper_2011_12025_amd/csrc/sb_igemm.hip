@@ -873,12 +873,14 @@ namespace {
 constexpr int GSTART_COST = 10;
 constexpr int GSPLIT_COST = 12;  // plus one per split
 // The pass over a remainder's tiles only: its launch, and writing and reading
-// back the partial tiles (of 128 x 128), in units of 0.47 us; a unit of the
-// wider tiles' rounds was 0.59.  Fitted to 62 pairs of the same call with and
-// without the split (64 to 320 channels, 64 to 256 outputs, blocks of 8 and 16,
-// 30 and 60 % low, 2 to 120 tiles left over): saved rounds of 12 to 40 units
-// against -3.4 to 19 us gained.
-constexpr double GTAIL_COST = 6.0, GTAIL_PART = 0.05, GTAIL_WIDE = 0.8;
+// back the partial tiles (per 128 x 128 of them), in units of 0.47 us.  A unit
+// of the wider tiles' rounds is 0.59, of the 64-channel tiles' 0.3 to 0.4 us.
+// Fitted to pairs of the same call with and without the split (64 to 320
+// channels, 40 to 256 outputs, blocks of 8 and 16, 30 and 60 % low, 2 to 120
+// tiles left over): what is split of them gains up to 19 us and, at the limit,
+// loses up to 0.7; without the term for the partial tiles 128 -> 72 channels lost
+// 3 us with 50 to 100 tiles left over.
+constexpr double GTAIL_COST = 6.0, GTAIL_PART = 0.05, GTAIL_WIDE = 0.8, GTAIL_NARROW = 1.25;
 
 inline bool galigned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 inline size_t ground256(size_t b) { return (b + 255) / 256 * 256; }
@@ -1006,7 +1008,8 @@ IgPlan igemm_plan(const Geo& g, const ConvArgs& a, int ks, int stride, bool dens
             if (ground256((size_t)rest * c * TM * tn * 4 + (size_t)(wgs / tiles_n) * 8) + prep_bytes > most) continue;
             const double tail = (double)(whole / cus) * (nsteps * w + GSTART_COST) +
                                 (double)((rest * c + cus - 1) / cus) * ((nsteps + c - 1) / c * w + GSTART_COST) +
-                                (GTAIL_COST + GTAIL_PART * c * wr * rest) * (wide ? GTAIL_WIDE : 1.0);
+                                (GTAIL_COST + GTAIL_PART * c * rest * TM * tn / (128 * 128)) *
+                                    (wide ? GTAIL_WIDE : tn < 128 ? GTAIL_NARROW : 1.0);
             if (tail < best) {
                 best = tail;
                 p.TM = TM;
