@@ -71,16 +71,20 @@ struct PixPair {
 // together.  Bound by the latency of those loads: at 1x3x1024x2048 fp16 with
 // 128-pixel blocks there are 128 workgroups, so each takes 1024 threads
 // (16 waves a CU) instead of 256: 17.4 -> 7.3 us, the selection 4.3 -> 2.5.
-template <typename T, int L, int C, int NT>
+// How many blocks the other images of the call add must not show in a score, so
+// both sum a block alike: 256 threads with V = 4 keep the four sums of threads
+// t, t + 256, ... of the 1024 apart and add them as those would.
+template <typename T, int L, int C, int NT, int V>
 __global__ __launch_bounds__(NT) void k_policy_score(const T* __restrict__ x, int Cn, int H, int W, int bs, int GH,
                                                      int GW, float* __restrict__ score) {
     const int k = (int)blockIdx.x;
     const int per = GH * GW;
     const int n = k / per, r = k - n * per, gy = r / GW, gx = r - gy * GW;
     const int lb = bs >> 1, cells = lb * lb;
-    float acc = 0.0f;
+    float acc[V] = {};
     if constexpr (C > 0) {
         constexpr int U = 4;
+        static_assert(U % V == 0, "a sum's cells come in order");
         for (int base = (int)threadIdx.x; base < cells; base += U * NT) {
             PixPair<T, L, C> t[U], b[U];
 #pragma unroll
@@ -91,38 +95,58 @@ __global__ __launch_bounds__(NT) void k_policy_score(const T* __restrict__ x, in
                 t[u].load(x, n, H, W, Y, X);
                 b[u].load(x, n, H, W, Y + 1, X);
             }
+            __builtin_amdgcn_sched_barrier(0);  // (every load before the first use)
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 float d2[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int c = 0; c < C; ++c) cell_channel(t[u].at(0, c), t[u].at(1, c), b[u].at(0, c), b[u].at(1, c), d2);
-                acc += base + u * NT < cells ? cell_norms(d2) : 0.0f;
+                acc[u % V] += base + u * NT < cells ? cell_norms(d2) : 0.0f;
             }
         }
     } else {
-        for (int cell = (int)threadIdx.x; cell < cells; cell += NT) {
-            const int ci = cell / lb, cj = cell - ci * lb;
-            const int Y = gy * bs + 2 * ci, X = gx * bs + 2 * cj;
-            float d2[4] = {0.f, 0.f, 0.f, 0.f};
-            for (int c = 0; c < Cn; ++c)
-                cell_channel(px<T, L>(x, n, Cn, H, W, Y, X, c), px<T, L>(x, n, Cn, H, W, Y, X + 1, c),
-                             px<T, L>(x, n, Cn, H, W, Y + 1, X, c), px<T, L>(x, n, Cn, H, W, Y + 1, X + 1, c), d2);
-            acc += cell_norms(d2);
+        for (int base = (int)threadIdx.x; base < cells; base += V * NT) {
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                const int cell = base + v * NT;
+                if (cell >= cells) break;
+                const int ci = cell / lb, cj = cell - ci * lb;
+                const int Y = gy * bs + 2 * ci, X = gx * bs + 2 * cj;
+                float d2[4] = {0.f, 0.f, 0.f, 0.f};
+                for (int c = 0; c < Cn; ++c)
+                    cell_channel(px<T, L>(x, n, Cn, H, W, Y, X, c), px<T, L>(x, n, Cn, H, W, Y, X + 1, c),
+                                 px<T, L>(x, n, Cn, H, W, Y + 1, X, c), px<T, L>(x, n, Cn, H, W, Y + 1, X + 1, c), d2);
+                acc[v] += cell_norms(d2);
+            }
         }
     }
-    // fixed-order reduction: lanes of a wave, then the waves
+    // fixed-order reduction: lanes of a wave, then the waves (of the NT * V sums)
+    constexpr int WAVES = NT * V / 64;
+    __shared__ float s_part[WAVES];
+    const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
+    if constexpr (V == 4) {  // four sums: half of the lanes go on with two of them, then a quarter with each
+        const bool up = lane & 32, upper = lane & 16;
+        float k[2];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
-    __shared__ float s_part[NT / 64];
-    if ((threadIdx.x & 63) == 0) s_part[threadIdx.x >> 6] = acc;
+        for (int i = 0; i < 2; ++i) k[i] = (up ? acc[2 + i] : acc[i]) + __shfl_xor(up ? acc[i] : acc[2 + i], 32, 64);
+        float a = (upper ? k[1] : k[0]) + __shfl_xor(upper ? k[0] : k[1], 16, 64);
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) a += __shfl_xor(a, o, 64);
+        if ((lane & 15) == 0) s_part[(lane >> 4) * (NT / 64) + wave] = a;
+    } else {
+        static_assert(V == 1, "one sum or four");
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) acc[0] += __shfl_xor(acc[0], o, 64);
+        if (lane == 0) s_part[wave] = acc[0];
+    }
     __syncthreads();
     if (threadIdx.x == 0) {
-        // in pairs: sixteen waves' sums one after the other round half as much again
-        float t[NT / 64];
+        // in pairs: sixteen sums one after the other round half as much again
+        float t[WAVES];
 #pragma unroll
-        for (int w = 0; w < NT / 64; ++w) t[w] = s_part[w];
+        for (int w = 0; w < WAVES; ++w) t[w] = s_part[w];
 #pragma unroll
-        for (int h = NT / 128; h > 0; h >>= 1)
+        for (int h = WAVES / 2; h > 0; h >>= 1)
 #pragma unroll
             for (int w = 0; w < h; ++w) t[w] += t[w + h];
         score[k] = t[0] / (float)(bs * bs);
@@ -157,14 +181,17 @@ __global__ __launch_bounds__(WG) void k_policy_select(const float* __restrict__ 
 
 template <typename T, int L, int C>
 void score_run(const void* x, int Cn, int H, int W, int bs, int GH, int GW, long long B, float* score, hipStream_t st) {
-    // 1024 threads where the blocks alone would leave less than two
-    // workgroups of 256 for every CU, and a block has cells for them
-    if (B < 2LL * device_cus() && (bs / 2) * (bs / 2) >= 1024)
-        hipLaunchKernelGGL((k_policy_score<T, L, C, 1024>), dim3((unsigned)B), dim3(1024), 0, st, (const T*)x, Cn, H, W,
-                           bs, GH, GW, score);
-    else
-        hipLaunchKernelGGL((k_policy_score<T, L, C, WG>), dim3((unsigned)B), dim3(WG), 0, st, (const T*)x, Cn, H, W, bs,
-                           GH, GW, score);
+    // 1024 threads where a block has four cells for each (1024x2048 images with
+    // 128-pixel blocks, four at once: 16.5 -> 14.5 us), or one and the blocks
+    // alone would leave less than two workgroups of 256 for every CU (512 blocks
+    // of 64 pixels a image, three images: 14.6 us with 256 threads, 19.2 with 1024)
+    auto run = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)B), dim3(threads), 0, st, (const T*)x, Cn, H, W, bs, GH, GW, score);
+    };
+    const int cells = (bs / 2) * (bs / 2);
+    if (cells < 1024) run(k_policy_score<T, L, C, WG, 1>, WG);
+    else if (cells >= 4096 || B < 2LL * device_cus()) run(k_policy_score<T, L, C, 1024, 1>, 1024);
+    else run(k_policy_score<T, L, C, WG, 4>, WG);
 }
 
 template <typename T, int L>

@@ -123,3 +123,17 @@ def test_policy_small_images(dtype, layout, offset, C):
         sc = sc.cpu().numpy().astype(np.float64)
         assert np.all(np.abs(sc - ref_sc) <= SCORE_RTOL * np.abs(ref_sc) + 1e-6)
         np.testing.assert_array_equal(mask.cpu().numpy(), oracle.policy_select(sc, tau))
+
+
+@pytest.mark.parametrize("dtype,layout,C", [("f16", "nhwc", 3), ("f32", "nchw", 3), ("bf16", "nhwc", 5)])
+def test_policy_scores_do_not_depend_on_the_batch(dtype, layout, C):
+    """Eight images of 8 x 8 blocks of 64 pixels at once (512 blocks: 256 threads
+    each) and one by one (1024 threads each): the same scores and masks, bit for bit."""
+    import paper_2011_12025_amd as sb
+    x = inputs.feature_map(160, 8, C, 512, 512, dtype).cuda()
+    lay = 1 if layout == "nhwc" else 0
+    fmt = torch.channels_last if lay else torch.contiguous_format
+    mask, sc = sb.policy_heuristic(x.contiguous(memory_format=fmt), 64, 0.4, layout=lay)
+    for n in range(8):
+        m1, s1 = sb.policy_heuristic(x[n:n + 1].contiguous(memory_format=fmt), 64, 0.4, layout=lay)
+        assert torch.equal(sc[n:n + 1], s1) and torch.equal(mask[n:n + 1], m1)
