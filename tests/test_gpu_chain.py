@@ -190,3 +190,23 @@ def test_down_equals_convolution_and_shortcut(dtype, N, C, Co, grid, bs, stride,
     for g, r, n in ((h[0], ref[0], nh), (h[1], ref[1], nl), (h[2], ref[2], nh), (sc[0], rsc[0], nh), (sc[1], rsc[1], nl)):
         if g is not None:
             assert g.shape == r.shape and torch.equal(g[:n], r[:n])
+
+
+@pytest.mark.parametrize("sampling", ["strided", "zero"])
+@pytest.mark.parametrize("dtype,N,C,Co,grid,bs,stride", [("f16", 2, 64, 128, (4, 6), 16, 2), ("bf16", 1, 64, 128, (3, 4), 8, 1)])
+def test_down_samplings(dtype, N, C, Co, grid, bs, stride, sampling):
+    """The shortcut's workgroups take the centre tap whatever the padding does."""
+    import paper_2011_12025_amd as sb
+    GH, GW = grid
+    H, W = GH * bs, GW * bs
+    log(f"[down] {sampling} {dtype} {N}x{C}->{Co} grid {grid} bs={bs} s={stride}")
+    mask = torch.from_numpy(inputs.mask_bernoulli(322, N, GH, GW, 0.5)).cuda()
+    hi, lo = sb.split(_cl(inputs.feature_map(322, N, C, H, W, dtype)), mask, bs)
+    w3, b3 = _cl(inputs.conv_weight(322, Co, C, 3, dtype)), inputs.conv_bias(322, Co, 9 * C, dtype).cuda()
+    w1, b1 = _cl(inputs.conv_weight(323, Co, C, 1, dtype)), inputs.conv_bias(323, Co, C, dtype).cuda()
+    h, sc = sb.block_conv_down(hi, lo, mask, bs, H, W, w3, b3, w1, b1, stride=stride, sampling=sampling)
+    ref = sb.block_conv_ex(hi, lo, mask, bs, H, W, w3, b3, stride=stride, relu=True, sampling=sampling)
+    rsc = sb.block_conv_ex(hi, lo, mask, bs, H, W, w1, b1, stride=stride)
+    torch.cuda.synchronize()
+    for g, r in zip((*h[:2], *sc), (*ref, *rsc)):
+        assert torch.equal(g, r)
