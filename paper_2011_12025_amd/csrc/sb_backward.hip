@@ -173,8 +173,11 @@ __global__ __launch_bounds__(WG) void k_pad_bwd(const T* __restrict__ dhp, const
 // the layer's first and last step: BlockSample + BlockPad, and both transposed
 // ---------------------------------------------------------------------------
 // Vectors per thread, their loads in flight together.  Measured for 1 / 2 / 4,
-// 256x512, 64 channels, half low, fp16: split_pad 18.4 / 14.8 / 17.9 us,
-// pad_split_bwd 22.8 / 19.0 / 18.6.
+// 256x512, 64 channels, half low: fp16 split_pad 19.6 / 15.2 / 18.2 us,
+// pad_split_bwd 22.5 / 18.7 / 18.8; fp32 33.0 / 21.7 / 19.0 and 34.0 / 28.8 /
+// 27.5; NCHW (single elements, either type) 111 / 65 / 44 and 122 / 83 / 73, but
+// an NCHW 64x64 map of 16 channels 6.7 / 9.4 / 15.7 in pad_split_bwd.  Two is
+// never slower than the two calls it stands for.
 constexpr int FU = 2;
 
 // Whole 16-byte vectors are streamed (non-temporal), single elements are not.

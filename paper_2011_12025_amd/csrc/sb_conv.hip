@@ -34,12 +34,15 @@
 // plane, a 2x2 cell is two loads of two pixels, the weights of a filter are one
 // run of words), other channels-last ones element by element.
 //
-// Bounds: fp32 by MFMA issue and by the staging beside it
-// (the 256x512, 64-channel layer, half low, NCHW: 178 -> 109 us, 39 us of MFMA
-// issue; a 64x64 layer of 16 channels 31 -> 11 us), small and ragged 16-bit
-// calls by the latency of the chain mask -> descriptors -> inputs -> MFMAs (two
-// 96x180 maps, 48 -> 72 channels, 12-pixel blocks: 22 -> 20 us; one 128x256
-// map of 96 channels, 16-pixel blocks: 37 -> 26 us).
+// Bounds: fp32 by MFMA issue and by the staging beside it (the 256x512,
+// 64-channel layer, half low, NCHW: 178 -> 101 us, 39 us of MFMA issue; a 64x64
+// layer of 16 channels 31 -> 8 us), small and ragged 16-bit calls by the
+// latency of the chain mask -> descriptors -> inputs -> MFMAs (two 96x180 maps,
+// 48 -> 72 channels, 12-pixel blocks: 21.5 -> 18.0 us; one 128x256 map of 96
+// channels, 16-pixel blocks: 36 -> 22 us).  All-low maps are a few small tiles
+// of averages, one wave a SIMD: 96 channels 22.6 -> 19.5 us.  The 16-bit NCHW
+// kernels of four sub-tiles a wave are at the 256 registers and spill one or two
+// of them (8 to 12 bytes a lane).
 //
 // The tile loader is where the block modules live:
 //   SRC_PADDED : reads padded stacks (plain conv of segblocks_conv3x3)
@@ -547,7 +550,9 @@ __global__ __launch_bounds__(WG, 2) void k_conv(Geo g, const uint8_t* __restrict
     // Tile grp of block k, the blocks fastest, then the channel tiles: the class
     // with fewer tiles fills only the first of a block's places, and workgroups
     // go to the XCDs and their CUs in turn.  With the tiles fastest all-low maps
-    // ran on two of the eight XCDs, with the channel tiles slowest on half of the CUs.
+    // ran on two of the eight XCDs (conv3x3 of 64 channels on 256x512 fp32 NHWC
+    // 116 us, now 33), with the channel tiles slowest on half of the CUs (96
+    // channels, 16-pixel blocks, fp16: 25.5 us, now 19.5).
     const int B = (int)g.B, ny = (a.C_out + nt - 1) / nt;
     int k = (int)blockIdx.x;
     const int first = k / B, row = first + (int)blockIdx.y, grp = row / ny;  // (one of the two is 0)
@@ -555,7 +560,8 @@ __global__ __launch_bounds__(WG, 2) void k_conv(Geo g, const uint8_t* __restrict
     const int co0 = (row - grp * ny) * nt;
     if constexpr (L == NCHW) {
         // runs of four blocks on one XCD: a halo column of a plane is a line of the
-        // neighbour's for every row
+        // neighbour's for every row (all-high fp16 256x512 of 64 channels: 37.2 us
+        // without, 34.3 with; longer runs would put a map's low region on few XCDs)
         constexpr int RUN = 4;
         const int base = k & ~(8 * RUN - 1), o = k - base;
         if (base + 8 * RUN <= B) k = base + (o & 7) * RUN + (o >> 3);
@@ -745,11 +751,13 @@ inline bool aligned(const void* p, int bytes) { return (reinterpret_cast<uintptr
 // Rows per tile and output channels per workgroup.  About 256 pixels a tile
 // read the fewest halo pixels and weights; 128 or 64 where that many smaller
 // tiles still find a place at once (two workgroups a CU), so that more of the
-// chip works.  Measured, 256 / 128 / 64 pixels a tile: one 128x256 map of 96
-// channels, 16-pixel blocks, fp16 (256 / 512 / 1024 workgroups) 30 / 26 / 48
-// us; the 256x512 fp32 layer of 64 channels, 32-pixel blocks (512 / 1024 / 2048)
-// 112 / 141 / 144 us.  The channel tiles of a call are equal, so that 72
-// channels are 48 + 24 and not 64 + 8.
+// chip works.  Measured, half low, 256 / 128 / 64 pixels a tile: one 128x256 map
+// of 96 channels, 16-pixel blocks, fp16 (256 / 512 / 1024 workgroups) 27.6 /
+// 22.2 / 34.4 us; the 256x512 fp32 layer of 64 channels, 32-pixel blocks (512 /
+// 1024 / 2048) 98 / 108 / 130 us.  (A fused layer counts every block as high,
+// so an all-low map may run with larger tiles than its own count would take:
+// that fp32 layer 75 us where 128 pixels a tile give 45.)  The channel tiles of
+// a call are equal, so that 72 channels are 48 + 24 and not 64 + 8.
 struct ConvPlan {
     int Rh, Rl, G, nt, ny, M;
 };
