@@ -184,13 +184,14 @@ void score_run(const void* x, int Cn, int H, int W, int bs, int GH, int GW, long
     // 1024 threads where a block has four cells for each (1024x2048 images with
     // 128-pixel blocks, four at once: 16.5 -> 14.5 us), or one and the blocks
     // alone would leave less than two workgroups of 256 for every CU (512 blocks
-    // of 64 pixels a image, three images: 14.6 us with 256 threads, 19.2 with 1024)
+    // of 64 pixels an image, three images: 15.1 us with 256 threads, 19.2 with
+    // 1024).  A launch holds 2^32 threads.
     auto run = [&](auto kernel, int threads) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)B), dim3(threads), 0, st, (const T*)x, Cn, H, W, bs, GH, GW, score);
     };
     const int cells = (bs / 2) * (bs / 2);
     if (cells < 1024) run(k_policy_score<T, L, C, WG, 1>, WG);
-    else if (cells >= 4096 || B < 2LL * device_cus()) run(k_policy_score<T, L, C, 1024, 1>, 1024);
+    else if ((cells >= 4096 && B < (1LL << 22)) || B < 2LL * device_cus()) run(k_policy_score<T, L, C, 1024, 1>, 1024);
     else run(k_policy_score<T, L, C, WG, 4>, WG);
 }
 
